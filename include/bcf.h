@@ -45,12 +45,13 @@ typedef enum {
 /* Arithmetic of the decoder MLP f_eta. Fetch, BC6H unpacking (exact integer
  * work) and trilinear filtering (binary32) are identical in every mode. */
 typedef enum {
-    BCF_FP32 = 0,       /* plain binary32 vector ALU MLP */
+    BCF_FP32 = 0,       /* binary32 weights, activations and accumulation (MFMA) */
     BCF_FP16 = 1,       /* MFMA, fp16 weights and activations, fp32 accumulation */
     BCF_BF16 = 2,       /* MFMA, bf16 weights and activations, fp32 accumulation */
     BCF_FP8 = 3,        /* MFMA, OCP e4m3 weights and activations with per-layer
                            scales, fp32 accumulation; needs act_absmax */
-    BCF_FP32_MFMA = 4   /* MFMA on binary32 operands, fp32 accumulation */
+    BCF_FP32_MFMA = 4   /* the same arithmetic as BCF_FP32, without bcf_calibrate's
+                           share of the workspace; single materials only */
 } bcf_precision;
 
 /* One feature pyramid T_i (Section 4.3, "Hardware compliant filtering").

@@ -73,7 +73,7 @@ size_t chain_blocks(uint32_t w, uint32_t h, uint32_t levels, uint32_t *per_level
 bool kind_of(bcf_precision p, bcf::MlpKind *k)
 {
     switch (p) {
-    case BCF_FP32: *k = bcf::MLP_VALU_F32; return true;
+    case BCF_FP32: *k = bcf::MLP_MFMA_F32; return true;
     case BCF_FP16: *k = bcf::MLP_MFMA_F16; return true;
     case BCF_BF16: *k = bcf::MLP_MFMA_BF16; return true;
     case BCF_FP8: *k = bcf::MLP_MFMA_FP8; return true;
@@ -316,6 +316,16 @@ bcf::WsLayout layout(const bcf::MaterialDesc &d, const bcf::MlpShape &sh, bcf::M
     return lay;
 }
 
+// Where a BCF_FP32 workspace keeps the calibration's operands (bcf_calibrate
+// writes them itself): after everything the decode reads.
+bcf::WsLayout calibration_layout(const bcf::WsLayout &decode, const bcf::MlpShape &sh)
+{
+    bcf::WsLayout lay = weights_layout(sh, bcf::MLP_VALU_F32, decode.total);
+    lay.scratch_off = decode.scratch_off;
+    lay.scratch_bytes = decode.scratch_bytes;
+    return lay;
+}
+
 bcf::PredecodePlan predecode_plan(const bcf::MaterialDesc &d)
 {
     bcf::PredecodePlan p;
@@ -485,7 +495,7 @@ bcf_status describe_batch(const bcf_material *mats, uint32_t n_mats, bcf_precisi
     if (!mats) return fail(BCF_ERR_INVALID_ARG, "materials is NULL");
     if (n_mats < 1 || n_mats > kMaxBatch) return fail(BCF_ERR_INVALID_ARG, "n_mats = %u, expected 1..%u", n_mats, kMaxBatch);
     if (!kind_of(p, &b->kind)) return fail(BCF_ERR_UNSUPPORTED, "precision %d not supported", (int)p);
-    if (b->kind != bcf::MLP_MFMA_F16 && b->kind != bcf::MLP_VALU_F32)
+    if (p != BCF_FP16 && p != BCF_FP32)
         return fail(BCF_ERR_UNSUPPORTED, "batched decode runs BCF_FP16 or BCF_FP32");
     b->descs.resize(n_mats);
     b->slots.resize(n_mats);
@@ -573,19 +583,20 @@ bcf_status bcf_prepare(const bcf_material *m, bcf_precision p, void *ws, size_t 
     if (!kind_of(p, &kind)) return fail(BCF_ERR_UNSUPPORTED, "precision %d not supported", (int)p);
     if (!ws_bytes) return fail(BCF_ERR_INVALID_ARG, "ws_bytes is NULL");
     const bcf::WsLayout lay = layout(d, sh, kind);
+    const size_t total = p == BCF_FP32 ? calibration_layout(lay, sh).total : lay.total;
     if (!ws) {
-        *ws_bytes = lay.total;
+        *ws_bytes = total;
         return BCF_OK;
     }
-    if (*ws_bytes < lay.total)
-        return fail(BCF_ERR_INVALID_ARG, "workspace of %zu bytes, need %zu", *ws_bytes, lay.total);
+    if (*ws_bytes < total)
+        return fail(BCF_ERR_INVALID_ARG, "workspace of %zu bytes, need %zu", *ws_bytes, total);
     if (!aligned(ws, 256)) return fail(BCF_ERR_INVALID_ARG, "workspace not 256-byte aligned");
     if (kind == bcf::MLP_MFMA_FP8 && !m->act_absmax)
         return fail(BCF_ERR_INVALID_ARG, "BCF_FP8 needs act_absmax (see bcf_calibrate)");
     if (m->act_absmax && !aligned(m->act_absmax, 4))
         return fail(BCF_ERR_INVALID_ARG, "act_absmax not 4-byte aligned");
     const uint64_t hash = material_hash(kFnvOffset, m, p);
-    const bcf::WsHeader header = ws_header(p, 1, hash, lay.scratch_off, lay.scratch_bytes, lay.total);
+    const bcf::WsHeader header = ws_header(p, 1, hash, lay.scratch_off, lay.scratch_bytes, total);
     st = device_status(bcf::launch_prepare_weights(m->params, m->act_absmax, sh, kind, lay, ws, &header,
                                                    static_cast<hipStream_t>(stream)),
                        "prepare launch");
@@ -628,7 +639,7 @@ bcf_status bcf_unpack(const bcf_material *m, void *ws, void *stream)
             return fail(BCF_ERR_INVALID_ARG,
                         "workspace %p was prepared for another material: prepare it again for this one", ws);
     }
-    const bcf::WsLayout lay = layout(d, sh, bcf::MLP_VALU_F32);
+    const bcf::WsLayout lay = layout(d, sh, bcf::MLP_MFMA_F32);
     return unpack(d, lay, ws, static_cast<hipStream_t>(stream));
 }
 
@@ -659,8 +670,11 @@ bcf_status bcf_calibrate(const bcf_material *m, void *ws, const float *queries, 
         return fail(BCF_ERR_INVALID_ARG, "queries NULL or misaligned");
     if ((st = check_ws(ws, BCF_FP32, 1u, material_hash(kFnvOffset, m, BCF_FP32), "bcf_prepare")) != BCF_OK)
         return st;
-    const bcf::WsLayout lay = layout(d, sh, bcf::MLP_VALU_F32);
+    const bcf::WsLayout lay = calibration_layout(layout(d, sh, bcf::MLP_MFMA_F32), sh);
     hipStream_t s = static_cast<hipStream_t>(stream);
+    st = device_status(bcf::launch_prepare_weights(m->params, nullptr, sh, bcf::MLP_VALU_F32, lay, ws, nullptr, s),
+                       "prepare launch");
+    if (st != BCF_OK) return st;
     st = unpack(d, lay, ws, s);
     if (st != BCF_OK) return st;
     return device_status(bcf::launch_calibrate(d, sh, lay, ws, queries, n, act_absmax, s), "calibrate launch");

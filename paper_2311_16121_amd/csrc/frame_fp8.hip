@@ -6,9 +6,9 @@ namespace bcf {
 hipError_t launch_frame_fp8(const FrameArgs &a, const MlpShape &sh, int layout, hipStream_t s)
 {
     switch (layout) {
-    case kLayoutPacked: return launch_frame_kind<MLP_MFMA_FP8, 16, kLayoutPacked>(a, sh, s);
-    case kLayoutShared: return launch_frame_kind<MLP_MFMA_FP8, 16, kLayoutShared>(a, sh, s);
-    default: return launch_frame_kind<MLP_MFMA_FP8, 16, kLayoutSplit>(a, sh, s);
+    case kLayoutPacked: return launch_frame_kind<MLP_MFMA_FP8, kLayoutPacked>(a, sh, s);
+    case kLayoutShared: return launch_frame_kind<MLP_MFMA_FP8, kLayoutShared>(a, sh, s);
+    default: return launch_frame_kind<MLP_MFMA_FP8, kLayoutSplit>(a, sh, s);
     }
 }
 

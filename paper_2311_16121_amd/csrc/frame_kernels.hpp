@@ -17,13 +17,17 @@ namespace bcf {
 typedef uint32_t uint4_t __attribute__((ext_vector_type(4)));
 
 // ---------------------------------------------------------------------------
+// BCF_FP32 takes the fp32 MFMAs too (the same binary32 operands and
+// accumulation as fp32 FMAs in the lanes, and the same error against binary64:
+// 1.2e-7 relative): at 64 FMA lanes a CU clock the vector ALU was its bound.
+// A 1920 x 1080 frame with 12-32-32-10: 154 -> 86 us; 501 queries of
+// 12-16-16-9: 17 -> 13 us with the unpack.
+//
 // The decode kernel: one query per lane filters the four pyramid slots, then
-// the MLP:
-//  * plain fp32: in the lane, with wave-uniform (scalar) weight operands;
-//  * MFMA: the wave's 64 feature vectors go through LDS into the operand
-//    layout of mlp_device.hpp, four groups of 16 queries per wave.
-// Outputs are staged in LDS so each wave writes its 64 rows with coalesced
-// buffer stores.
+// the MLP on the matrix cores: the wave's 64 feature vectors go through LDS
+// into the operand layout of mlp_device.hpp, four groups of 16 queries per
+// wave. Outputs are staged in LDS so each wave writes its 64 rows with
+// coalesced buffer stores.
 
 constexpr int kFrameThreads = 256;
 constexpr int kFrameWaves = kFrameThreads / 64;
@@ -189,83 +193,68 @@ __device__ __forceinline__ void copy_lut(const LevelLut &src, LevelLut &dst)
 }
 
 // MLP (eq. 3) of a wave's 64 feature vectors z (one per lane); the outputs
-// land in the wave's LDS stage, lane L's at st[L * out_dim ...]. The MFMA path
-// passes the feature vectors through `feats`, which may be the same LDS as st
-// (both 4 KB).
-template <MlpKind K, int H, int NH, int C>
-__device__ __forceinline__ void mlp_stage(const float z[12], const uint8_t *wbase, const WsLayout &lay,
-                                          const MfmaMlp<K == MLP_VALU_F32 ? MLP_MFMA_F16 : K, H, NH> &mlp,
-                                          float4_t (*feats)[4], float *st, uint32_t out_dim, uint32_t lane)
+// land in the wave's LDS stage, lane L's at st[L * out_dim ...]. The feature
+// vectors pass through `feats`, which may be the same LDS as st (both 4 KB).
+template <MlpKind K, int H, int NH>
+__device__ __forceinline__ void mlp_stage(const float z[12], const MfmaMlp<K, H, NH> &mlp, float4_t (*feats)[4],
+                                          float *st, uint32_t out_dim, uint32_t lane)
 {
-    constexpr bool VALU = K == MLP_VALU_F32;
     const uint32_t g = lane >> 4, qi = lane & 15;
-    if (VALU) {
-        float o[C];
-        mlp_valu<H, NH, C>(wbase, lay, z, o, nullptr);
 #pragma unroll
-        for (int j = 0; j < C; ++j)
-            if ((uint32_t)j < out_dim) st[lane * out_dim + j] = o[j];
-    } else {
+    for (int t = 0; t < 4; ++t) {
+        const float4_t v4 = {z[3 * t], z[3 * t + 1], z[3 * t + 2], 0.0f};
+        feats[lane][t] = v4;
+    }
+    wave_lds_sync();
+    float4_t fin[4];
 #pragma unroll
-        for (int t = 0; t < 4; ++t) {
-            const float4_t v4 = {z[3 * t], z[3 * t + 1], z[3 * t + 2], 0.0f};
-            feats[lane][t] = v4;
-        }
-        wave_lds_sync();
-        float4_t fin[4];
+    for (int grp = 0; grp < 4; ++grp) fin[grp] = feats[16 * grp + qi][g];
+    wave_lds_sync();                      // feats and st share the wave's LDS
+    // lane (g, qi) holds outputs 4g .. 4g + 3 of its query; those past
+    // out_dim go to the stage's last float, which 64 rows of fewer than
+    // kMaxOut outputs never use (a select, not a branch per output)
+    constexpr uint32_t kSpare = 64 * kMaxOut - 1;
+    float f[4][4];
 #pragma unroll
-        for (int grp = 0; grp < 4; ++grp) fin[grp] = feats[16 * grp + qi][g];
-        wave_lds_sync();                      // feats and st share the wave's LDS
-        // lane (g, qi) holds outputs 4g .. 4g + 3 of its query; those past
-        // out_dim go to the stage's last float, which 64 rows of fewer than
-        // kMaxOut outputs never use (a select, not a branch per output)
-        constexpr uint32_t kSpare = 64 * kMaxOut - 1;
-        float f[4][4];
+    for (int grp = 0; grp < 4; ++grp)
 #pragma unroll
-        for (int grp = 0; grp < 4; ++grp)
+        for (int i = 0; i < 4; ++i) f[grp][i] = fin[grp][i];
+    float4_t o[4];
+    mlp.template run_groups<4>(f, o);
 #pragma unroll
-            for (int i = 0; i < 4; ++i) f[grp][i] = fin[grp][i];
-        float4_t o[4];
-        mlp.template run_groups<4>(f, o);
+    for (int grp = 0; grp < 4; ++grp) {
+        const float4_t o4 = o[grp];
+        const uint32_t row = (16 * grp + qi) * out_dim;
 #pragma unroll
-        for (int grp = 0; grp < 4; ++grp) {
-            const float4_t o4 = o[grp];
-            const uint32_t row = (16 * grp + qi) * out_dim;
-#pragma unroll
-            for (int j = 0; j < 4; ++j)
-                st[4 * g + j < out_dim ? row + 4 * g + j : kSpare] = o4[j];
-        }
+        for (int j = 0; j < 4; ++j)
+            st[4 * g + j < out_dim ? row + 4 * g + j : kSpare] = o4[j];
     }
     wave_lds_sync();
 }
 
 // One wave's 64 queries: filter (eqs. 9, 10), concatenate, MLP.
-template <MlpKind K, int H, int NH, int C, int LAYOUT>
+template <MlpKind K, int H, int NH, int LAYOUT>
 __device__ __forceinline__ void decode_wave(const Query &qq, __amdgpu_buffer_rsrc_t rs, const LevelLut &lut,
-                                            const float *levels_bias, uint32_t stride, const uint8_t *wbase,
-                                            const WsLayout &lay,
-                                            const MfmaMlp<K == MLP_VALU_F32 ? MLP_MFMA_F16 : K, H, NH> &mlp,
-                                            float4_t (*feats)[4], float *st, uint32_t out_dim, uint32_t lane)
+                                            const float *levels_bias, uint32_t stride,
+                                            const MfmaMlp<K, H, NH> &mlp, float4_t (*feats)[4], float *st, uint32_t out_dim, uint32_t lane)
 {
     float z[12];
     filter4<LAYOUT>(rs, lut, levels_bias, stride, qq.u, qq.v, qq.s, z);
-    mlp_stage<K, H, NH, C>(z, wbase, lay, mlp, feats, st, out_dim, lane);
+    mlp_stage<K, H, NH>(z, mlp, feats, st, out_dim, lane);
 }
 
 // decode_wave for a material with a position-interleaved scratch
-template <MlpKind K, int H, int NH, int C>
+template <MlpKind K, int H, int NH>
 __device__ __forceinline__ void decode_wave_interleaved(const Query &qq, __amdgpu_buffer_rsrc_t rs,
                                                         const LevelLut &lut, const float *levels_bias,
-                                                        const uint8_t *wbase, const WsLayout &lay,
-                                                        const MfmaMlp<K == MLP_VALU_F32 ? MLP_MFMA_F16 : K, H, NH> &mlp,
-                                                        float4_t (*feats)[4], float *st, uint32_t out_dim,
-                                                        uint32_t lane)
+                                                        const MfmaMlp<K, H, NH> &mlp, float4_t (*feats)[4],
+                                                        float *st, uint32_t out_dim, uint32_t lane)
 {
     PendingPacked taps;
     fetch4_packed(rs, lut, levels_bias, qq.u, qq.v, qq.s, taps);
     float z[12];
     filter_pending_packed(taps, z);
-    mlp_stage<K, H, NH, C>(z, wbase, lay, mlp, feats, st, out_dim, lane);
+    mlp_stage<K, H, NH>(z, mlp, feats, st, out_dim, lane);
 }
 
 // Item `it` of a run of n consecutive queries: its (up to) 64 staged rows go
@@ -353,10 +342,9 @@ struct Width {
     static constexpr int value = V;
 };
 
-template <MlpKind K, int H, int NH, int C, int LAYOUT>
+template <MlpKind K, int H, int NH, int LAYOUT>
 __global__ void __launch_bounds__(kFrameThreads) k_frame(FrameArgs a)
 {
-    constexpr bool VALU = K == MLP_VALU_F32;
     __shared__ LevelLut lut;
     // per wave 4 KB: the feature vectors, then the staged output rows
     __shared__ float4_t stage[kFrameWaves][64 * kMaxOut / 4];
@@ -368,8 +356,8 @@ __global__ void __launch_bounds__(kFrameThreads) k_frame(FrameArgs a)
     const __amdgpu_buffer_rsrc_t rs = make_rsrc(a.ws + a.lay.scratch_off, (uint32_t)a.lay.scratch_bytes);
     const __amdgpu_buffer_rsrc_t rq = make_rsrc(a.queries, a.n * 12u);
     const __amdgpu_buffer_rsrc_t ro = make_rsrc(a.out, a.n * a.out_dim * 4u);
-    MfmaMlp<VALU ? MLP_MFMA_F16 : K, H, NH> mlp;
-    if (!VALU) mlp.load(a.ws, a.lay, lane);
+    MfmaMlp<K, H, NH> mlp;
+    mlp.load(a.ws, a.lay, lane);
     float *st = reinterpret_cast<float *>(&stage[wv][0]);
     float4_t (*feats)[4] = reinterpret_cast<float4_t (*)[4]>(&stage[wv][0]);
 
@@ -430,7 +418,7 @@ __global__ void __launch_bounds__(kFrameThreads) k_frame(FrameArgs a)
                 float z[12];
                 if constexpr (LAYOUT == kLayoutPacked) filter_pending_packed(taps, z);
                 else filter_pending(taps, z);
-                mlp_stage<K, H, NH, C>(z, a.ws, a.lay, mlp, feats, st, a.out_dim, lane);
+                mlp_stage<K, H, NH>(z, mlp, feats, st, a.out_dim, lane);
                 fetch(qnext, taps);
                 qnext = load_query(rq, query_of(clamp_item(k + 2 * items.step), i_, r_, c_));
                 store_item<V>(a, oob, st, ro, it, row0, col0, lane);
@@ -443,8 +431,8 @@ __global__ void __launch_bounds__(kFrameThreads) k_frame(FrameArgs a)
                 query_of(k, it, row0, col0);
                 const Query qq = next;
                 if (k + items.step < items.end) next = load_query(rq, query_of(k + items.step, i_, r_, c_));
-                decode_wave<K, H, NH, C, kLayoutSplit>(qq, rs, lut, a.levels_bias, a.stride, a.ws, a.lay, mlp, feats,
-                                                 st, a.out_dim, lane);
+                decode_wave<K, H, NH, kLayoutSplit>(qq, rs, lut, a.levels_bias, a.stride, mlp, feats, st, a.out_dim,
+                                                    lane);
                 store_item<V>(a, oob, st, ro, it, row0, col0, lane);
                 wave_lds_sync();
             }
@@ -529,10 +517,9 @@ __device__ __forceinline__ void batch_range(const BatchArgs &a, uint32_t k, uint
 }
 
 // W waves per workgroup (the autotuner picks 2 or 4).
-template <MlpKind K, int H, int NH, int C, int W>
+template <MlpKind K, int H, int NH, int W>
 __global__ void __launch_bounds__(64 * W) k_batch(BatchArgs a)
 {
-    constexpr bool VALU = K == MLP_VALU_F32;
     __shared__ LevelLut lut[W];                           // each wave's current material
     __shared__ float4_t stage[W][64 * kMaxOut / 4];       // features, then output rows
     // the wave index is uniform across the wave: say so, so that everything
@@ -558,10 +545,9 @@ __global__ void __launch_bounds__(64 * W) k_batch(BatchArgs a)
         items.step = 1;
     }
 
-    MfmaMlp<VALU ? MLP_MFMA_F16 : K, H, NH> mlp;
+    MfmaMlp<K, H, NH> mlp;
     uint32_t cur = 0xFFFFFFFFu, first_item = 0, n_k = 0, shared = 0, interleaved = 0, stride = 0;
     float lb[2 * kMaxTextures];
-    const uint8_t *wbase = a.ws;
     __amdgpu_buffer_rsrc_t rs = make_rsrc(a.ws, 0), rq = rs, ro = rs;
     for (uint32_t it0 = items.first; it0 < items.end; it0 += items.step)
     for (uint32_t it = it0; it < min(it0 + run, items.end); ++it) {
@@ -591,34 +577,30 @@ __global__ void __launch_bounds__(64 * W) k_batch(BatchArgs a)
             n_k = uniform(n_k);
             rq = make_rsrc(a.queries + 3ull * q0, n_k * 12u);
             ro = make_rsrc(a.out + (uint64_t)a.out_dim * q0, n_k * a.out_dim * 4u);
-            wbase = a.ws + uniform64(M.weights_off);
-            if (!VALU) mlp.load(wbase, a.lay, lane);
+            mlp.load(a.ws + uniform64(M.weights_off), a.lay, lane);
             first_item = uniform(a.items[cur]);
             wave_lds_sync();
         }
         const uint32_t j = it - first_item;
         const Query qq = load_query(rq, j * 64 + lane);   // past n_k: zeros, not stored
         if (interleaved)
-            decode_wave_interleaved<K, H, NH, C>(qq, rs, lut[wv], lb, wbase, a.lay, mlp, feats, st, a.out_dim,
-                                                 lane);
+            decode_wave_interleaved<K, H, NH>(qq, rs, lut[wv], lb, mlp, feats, st, a.out_dim, lane);
         else if (shared)
-            decode_wave<K, H, NH, C, kLayoutShared>(qq, rs, lut[wv], lb, stride, wbase, a.lay, mlp, feats, st,
-                                           a.out_dim, lane);
+            decode_wave<K, H, NH, kLayoutShared>(qq, rs, lut[wv], lb, stride, mlp, feats, st, a.out_dim, lane);
         else
-            decode_wave<K, H, NH, C, kLayoutSplit>(qq, rs, lut[wv], lb, stride, wbase, a.lay, mlp, feats, st,
-                                            a.out_dim, lane);
+            decode_wave<K, H, NH, kLayoutSplit>(qq, rs, lut[wv], lb, stride, mlp, feats, st, a.out_dim, lane);
         store_run(stage[wv], ro, j, n_k, a.out_dim, lane);
         wave_lds_sync();
     }
 }
 
-template <MlpKind K, int C>
+template <MlpKind K>
 hipError_t launch_batch_kind(const BatchArgs &a, const MlpShape &sh, unsigned grid, uint32_t waves, hipStream_t s)
 {
 #define BCF_CASE(H, NH)                                                                       \
     if (sh.hidden == H && sh.n_hidden == NH) {                                               \
-        if (waves == 2) k_batch<K, H, NH, C, 2><<<grid, 128, 0, s>>>(a);                      \
-        else k_batch<K, H, NH, C, 4><<<grid, 256, 0, s>>>(a);                                 \
+        if (waves == 2) k_batch<K, H, NH, 2><<<grid, 128, 0, s>>>(a);                      \
+        else k_batch<K, H, NH, 4><<<grid, 256, 0, s>>>(a);                                 \
         return hipGetLastError();                                                             \
     }
     BCF_CASE(16, 1) BCF_CASE(16, 2) BCF_CASE(16, 3)
@@ -651,11 +633,9 @@ unsigned resident_workgroups()
 }
 
 // One workgroup per kFrameWaves items, at most `cap`, a multiple of the XCDs.
-// The cap is a small multiple of the workgroups resident at once: twice for
-// the MFMA kernels, four times for the fp32 vector-ALU kernel (measured on
-// the frame benchmark: the MFMA kernels run fastest when their waves sweep
-// the image nearly together, the ALU-bound one with more waves queued behind
-// the resident ones to fill the tail).
+// The cap is twice the workgroups resident at once (measured on the frame
+// benchmark: the kernels run fastest when their waves sweep the image nearly
+// together).
 inline unsigned frame_launch_grid(uint32_t n_items, unsigned cap)
 {
     const unsigned want = (n_items + kFrameWaves - 1) / kFrameWaves;
@@ -663,14 +643,14 @@ inline unsigned frame_launch_grid(uint32_t n_items, unsigned cap)
     return std::min(std::max(kXcds, (want + kXcds - 1) / kXcds * kXcds), cap);
 }
 
-template <MlpKind K, int C, int SH>
+template <MlpKind K, int SH>
 hipError_t launch_frame_kind(const FrameArgs &a, const MlpShape &sh, hipStream_t s)
 {
-    constexpr unsigned kOversub = K == MLP_VALU_F32 ? 4 : 2;
+    constexpr unsigned kOversub = 2;
 #define BCF_CASE(H, NH)                                                                       \
     if (sh.hidden == H && sh.n_hidden == NH) {                                               \
-        const unsigned res = resident_workgroups<k_frame<K, H, NH, C, SH>>();                \
-        k_frame<K, H, NH, C, SH>                                                              \
+        const unsigned res = resident_workgroups<k_frame<K, H, NH, SH>>();                \
+        k_frame<K, H, NH, SH>                                                                 \
             <<<frame_launch_grid(a.n_items, res ? kOversub * res : 4096u), kFrameThreads, 0, s>>>(a); \
         return hipGetLastError();                                                             \
     }
@@ -687,7 +667,6 @@ hipError_t launch_frame_f32(const FrameArgs &a, const MlpShape &sh, int layout, 
 hipError_t launch_frame_f16(const FrameArgs &a, const MlpShape &sh, int layout, hipStream_t s);
 hipError_t launch_frame_bf16(const FrameArgs &a, const MlpShape &sh, int layout, hipStream_t s);
 hipError_t launch_frame_fp8(const FrameArgs &a, const MlpShape &sh, int layout, hipStream_t s);
-hipError_t launch_frame_f32_mfma(const FrameArgs &a, const MlpShape &sh, int layout, hipStream_t s);
 hipError_t launch_calibrate_kernel(const FrameArgs &a, const MlpShape &sh, int layout, unsigned grid,
                                    hipStream_t s);
 hipError_t launch_batch_f16(const BatchArgs &a, const MlpShape &sh, unsigned grid, uint32_t waves, hipStream_t s);

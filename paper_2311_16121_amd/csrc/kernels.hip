@@ -386,7 +386,7 @@ hipError_t launch_predecode(const MaterialDesc &m, const PredecodePlan &p, uint2
 // ---------------------------------------------------------------------------
 // MLP operand layouts (see mlp_device.hpp for the MFMA slot order)
 //
-// VALU: layer l is W[rows][cols] fp32 row-major then b[rows], rows/cols padded
+// VALU (the fp8 calibration): layer l is W[rows][cols] fp32 row-major then b[rows], rows/cols padded
 // (layer 0 cols = 12: z0 index 3 * pyramid + channel).
 // MFMA: per layer [mblock][kchunk][lane][P] operand elements; the bias stays
 // fp32 in natural order, padded to the M blocks.
@@ -601,13 +601,6 @@ static FrameArgs frame_args(const MaterialDesc &m, const WsLayout &lay, const vo
     return a;
 }
 
-// The calibration's grid: at most 16 workgroups of 4 waves per CU, a multiple of the XCD count.
-static unsigned frame_grid(uint32_t items)
-{
-    const uint32_t blocks = std::min<uint32_t>((items + kFrameWaves - 1) / kFrameWaves, 256u * 16u);
-    return std::max(kXcds, (blocks + kXcds - 1) / kXcds * kXcds);
-}
-
 // tile rows per strip of a tiled frame (16 x 4 tiles: 16 image rows)
 constexpr uint32_t kStripRows = 4;
 
@@ -619,11 +612,10 @@ hipError_t launch_filter_mlp(const MaterialDesc &m, const MlpShape &sh, MlpKind 
     FrameArgs a = frame_args(m, lay, ws, sh.out, &layout);
     auto launch = [&]() -> hipError_t {
         switch (kind) {
-        case MLP_VALU_F32: return launch_frame_f32(a, sh, layout, s);
         case MLP_MFMA_F16: return launch_frame_f16(a, sh, layout, s);
         case MLP_MFMA_BF16: return launch_frame_bf16(a, sh, layout, s);
         case MLP_MFMA_FP8: return launch_frame_fp8(a, sh, layout, s);
-        case MLP_MFMA_F32: return launch_frame_f32_mfma(a, sh, layout, s);
+        case MLP_MFMA_F32: return launch_frame_f32(a, sh, layout, s);
         default: return hipErrorInvalidValue;
         }
     };
@@ -922,7 +914,7 @@ hipError_t launch_batch(void *ws, size_t table_off, size_t items_off, const WsLa
     const unsigned grid = std::max(kXcds, (std::min(shape.workgroups, cap) + kXcds - 1) / kXcds * kXcds);
     switch (kind) {
     case MLP_MFMA_F16: return launch_batch_f16(a, sh, grid, waves, s);
-    case MLP_VALU_F32: return launch_batch_f32(a, sh, grid, waves, s);
+    case MLP_MFMA_F32: return launch_batch_f32(a, sh, grid, waves, s);
     default: return hipErrorInvalidValue;
     }
 }

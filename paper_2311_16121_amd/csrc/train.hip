@@ -393,7 +393,7 @@ __global__ void __launch_bounds__(kTrainThreads) k_train_forward_mfma(TrainDesc 
         float z[12];
         features(d, lut, live ? queries[3u * q] : 0.0f, live ? queries[3u * q + 1u] : 0.0f,
                  live ? queries[3u * q + 2u] : 0.0f, z);
-        mlp_stage<MLP_MFMA_F32, H, NH, kMaxOut>(z, d.ops_ws, d.ops, mlp, feats, st, c, lane);
+        mlp_stage<MLP_MFMA_F32, H, NH>(z, mlp, feats, st, c, lane);
         if (live)
             for (uint32_t j = 0; j < c; ++j) out[(size_t)q * c + j] = st[lane * c + j];
         wave_lds_sync();                              // the stage is rewritten by the next chunk

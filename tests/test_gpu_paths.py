@@ -1,0 +1,55 @@
+"""The kernels' size and layout edges: each path a dispatch can take, at the
+sizes where it can go wrong, against the oracle or the general path."""
+import numpy as np
+import pytest
+
+import oracle
+import synth
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def bcf():
+    if not torch.cuda.is_available():
+        pytest.fail("GPU tests need a visible MI355X")
+    import paper_2311_16121_amd as bcf
+    return bcf
+
+
+def dev(x):
+    return torch.from_numpy(np.ascontiguousarray(x)).cuda()
+
+
+def material(bcf, sizes, levels, dims, seed, bias=None, signed=False):
+    """(device material, oracle material) of bounded random blocks."""
+    g = synth.rng(seed)
+    texs = [synth.bounded_blocks(synth.chain_blocks(w, h, L), g, signed=signed).reshape(-1)
+            for (w, h), L in zip(sizes, levels)]
+    params = synth.mlp_params(dims, synth.rng(seed + 1))
+    bias = bias or [0.0] * len(sizes)
+    return (bcf.Material.from_host(texs, sizes, levels, dims, params, bias, signed),
+            oracle.Material(texs, sizes, levels, dims, params, bias, signed))
+
+
+@pytest.mark.parametrize("sizes,dims", [([(64, 64)] * 4, (12, 16, 16, 9)), ([(64, 32)] * 2, (6, 64, 24, 16)),
+                                        ([(64, 64), (32, 32), (16, 16)], (9, 33, 11))])
+def test_fp32_decode_and_calibration_share_a_workspace(bcf, sizes, dims):
+    """BCF_FP32 evaluates what BCF_FP32_MFMA does, bit for bit, also after a
+    calibration wrote its own operands into the same workspace."""
+    levels = [max(s).bit_length() for s in sizes]
+    mat, host = material(bcf, sizes, levels, dims, seed=90)
+    q = synth.uniform_queries(501, synth.rng(91), float(levels[0] - 1))
+    ws, wsm = bcf.prepare(mat, bcf.Precision.FP32), bcf.prepare(mat, bcf.Precision.FP32_MFMA)
+    want = bcf.decode(mat, wsm, dev(q), bcf.Precision.FP32_MFMA).cpu().numpy()
+    assert np.array_equal(bcf.decode(mat, ws, dev(q)).cpu().numpy(), want)
+    absmax = torch.empty(len(dims) - 1, device="cuda")
+    import ctypes as C
+    assert bcf.lib.bcf_calibrate(C.byref(mat.c), C.c_void_p(ws.data_ptr()), C.c_void_p(dev(q).data_ptr()), len(q),
+                                 C.c_void_p(absmax.data_ptr()), None) == 0
+    torch.cuda.synchronize()
+    assert np.array_equal(bcf.decode(mat, ws, dev(q)).cpu().numpy(), want)
+    assert np.abs(want - oracle.decode(host, q)).max() <= 1e-5
+    # z0's largest magnitude: one binary32 filter against binary64, so a few ulp
+    assert abs(float(absmax[0]) - np.abs(oracle.sample(host, q)).max()) <= 1e-6
