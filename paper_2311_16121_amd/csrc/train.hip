@@ -334,38 +334,7 @@ __device__ __forceinline__ void features(const TrainDesc &d, const TrainLevelLut
     }
 }
 
-// The MLP's parameters in LDS, one padded row per neuron: its weights, its
-// bias, zeros (layer 0's inputs padded to 12, the output layer to kMaxOut
-// rows). The backward's matrix-core products read a weight (or, for the
-// deltas, its transpose) per lane from these rows.
-template <int H, int NH>
-struct __align__(16) MlpLds {
-    float w0[H][16];                          // inputs 0..11, bias at 12
-    float wh[NH > 1 ? NH - 1 : 1][H][H + 4];  // inputs 0..H-1, bias at H
-    float wl[kMaxOut][H + 4];
-};
-
 typedef float f32x4 __attribute__((ext_vector_type(4)));
-// Every thread of the workgroup takes part; synchronises the workgroup.
-template <int H, int NH>
-__device__ __forceinline__ void load_mlp(const TrainDesc &d, MlpLds<H, NH> &m)
-{
-    const uint32_t n0 = d.dims[0], c = d.dims[NH + 1];
-    const float *P = d.params;
-    for (uint32_t e = threadIdx.x; e < (uint32_t)(H * 16); e += blockDim.x) {
-        const uint32_t j = e / 16u, i = e % 16u;
-        m.w0[j][i] = i < n0 ? P[d.w_off[0] + j * n0 + i] : (i == 12 ? P[d.b_off[0] + j] : 0.0f);
-    }
-    for (uint32_t e = threadIdx.x; e < (uint32_t)((NH - 1) * H * (H + 4)); e += blockDim.x) {
-        const uint32_t l = e / (H * (H + 4)), r = e % (H * (H + 4)), j = r / (H + 4), i = r % (H + 4);
-        m.wh[l][j][i] = i < H ? P[d.w_off[l + 1] + j * H + i] : (i == H ? P[d.b_off[l + 1] + j] : 0.0f);
-    }
-    for (uint32_t e = threadIdx.x; e < (uint32_t)(kMaxOut * (H + 4)); e += blockDim.x) {
-        const uint32_t j = e / (H + 4), i = e % (H + 4);
-        m.wl[j][i] = j >= c ? 0.0f : i < H ? P[d.w_off[NH] + j * H + i] : (i == H ? P[d.b_off[NH] + j] : 0.0f);
-    }
-    __syncthreads();
-}
 
 // The forward with the MLP on the matrix cores (fp32 16x16x4 MFMAs, the
 // decode kernels' operand layout, prepared from the parameters per call): a
@@ -399,77 +368,6 @@ __global__ void __launch_bounds__(kTrainThreads) k_train_forward_mfma(TrainDesc 
         wave_lds_sync();                              // the stage is rewritten by the next chunk
     }
 }
-
-// A layer's parameter gradients, dL/dW[j][i] = sum over queries of
-// delta[q][j] * a[q][i], summed per wave on the matrix cores: 16 x 16 tiles
-// (rows j = 16 m + .., columns i = 16 n + ..) of fp32 16x16x4 MFMAs, K running
-// over the wave's 64 queries; at step s lane L supplies dl[4 s + L / 16][16 m
-// + L % 16] and a[4 s + L / 16][16 n + L % 16], and tile register k of lane L
-// holds row 4 (L / 16) + k, column L % 16. The bias gradients (sum over
-// queries of delta[q][j]) are the per-lane sums of the same dl reads, added
-// across the four lane groups when flushed.
-template <int MT, int NT>
-struct LayerGrad {
-    f32x4 w[MT][NT];
-    float b[MT];
-};
-
-template <int MT, int NT>
-__device__ __forceinline__ void grad_zero(LayerGrad<MT, NT> &g)
-{
-#pragma unroll
-    for (int m = 0; m < MT; ++m) {
-        g.b[m] = 0.0f;
-#pragma unroll
-        for (int n = 0; n < NT; ++n) g.w[m][n] = (f32x4){0.0f, 0.0f, 0.0f, 0.0f};
-    }
-}
-
-template <int MT, int NT>
-__device__ __forceinline__ void accumulate(LayerGrad<MT, NT> &g, const float (*a)[kTrainMaxHidden + 1],
-                                           const float (*dl)[kTrainMaxHidden], uint32_t lane)
-{
-    static_assert(16 * MT <= kTrainMaxHidden && 16 * NT <= kTrainMaxHidden, "tiles inside the LDS rows");
-    const uint32_t r = lane >> 4, c = lane & 15u;
-#pragma unroll 4
-    for (uint32_t s = 0; s < 16; ++s) {
-        float av[NT], dv[MT];
-#pragma unroll
-        for (int n = 0; n < NT; ++n) av[n] = a[4 * s + r][16 * n + c];
-#pragma unroll
-        for (int m = 0; m < MT; ++m) {
-            dv[m] = dl[4 * s + r][16 * m + c];
-            g.b[m] += dv[m];
-        }
-#pragma unroll
-        for (int m = 0; m < MT; ++m)
-#pragma unroll
-            for (int n = 0; n < NT; ++n) g.w[m][n] = __builtin_amdgcn_mfma_f32_16x16x4f32(dv[m], av[n], g.w[m][n], 0, 0, 0);
-    }
-}
-
-// Adds a wave's layer gradients to gw (W[n_out][n_in], row-major) and gb (b[n_out]).
-template <int MT, int NT>
-__device__ __forceinline__ void flush(const LayerGrad<MT, NT> &g, float *gw, float *gb, uint32_t n_in,
-                                      uint32_t n_out, uint32_t lane)
-{
-    const uint32_t r = lane >> 4, c = lane & 15u;
-#pragma unroll
-    for (int m = 0; m < MT; ++m) {
-#pragma unroll
-        for (int n = 0; n < NT; ++n)
-#pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                const uint32_t j = 16u * m + 4u * r + k, i = 16u * n + c;
-                if (j < n_out && i < n_in) unsafeAtomicAdd(gw + j * n_in + i, g.w[m][n][k]);
-            }
-        float b = g.b[m];
-        b += __shfl_xor(b, 16);
-        b += __shfl_xor(b, 32);
-        if (r == 0 && 16u * m + c < n_out) unsafeAtomicAdd(gb + 16u * m + c, b);
-    }
-}
-
 
 // ---------------------------------------------------------------------------
 // the backward's sample order
@@ -574,62 +472,195 @@ __global__ void __launch_bounds__(kBinThreads) k_train_bin_scatter(const float *
     }
 }
 
-// Y[s][m] = f(sum over k of Wt(m, k) X[s][k] + bias) for the wave's 64
-// samples s (rows of the LDS arrays X and Y), m < 16 MT, k < 4 KC, on the
-// matrix cores (fp32 16x16x4, K in steps of 4): Wt(m, k) = W[m ldw + k], or
-// W[k ldw + m] when TRANS; the bias W[m ldw + bias_col] when BIAS; f = ReLU
-// when RELU. Lane L supplies Wt(16 mb + L % 16, 4 kc + L / 16) and X[16 grp
-// + L % 16][4 kc + L / 16], and receives rows 4 (L / 16) .. + 3 of sample
-// 16 grp + L % 16.
-template <int MT, int KC, bool TRANS, bool BIAS, bool RELU, int LDX, int LDY>
-__device__ __forceinline__ void rows_product(const float *W, int ldw, int bias_col, const float (*X)[LDX],
-                                             float (*Y)[LDY], uint32_t lane)
+// The MLP backward works on groups of 16 samples in the matrix cores' fp32
+// 16x16x4 layout: lane L = (g, i), g = L / 16, holds of sample i the units
+// 16 mb + 4 r + g (register r of tile mb) of every hidden activation and delta.
+// A product's output rows are numbered so that this is also the operand the
+// next product reads (K chunk kc: lane (g, i) supplies unit 4 kc + g = register
+// kc % 4 of tile kc / 4), so the chain forward through the hidden layers and
+// back through the transposes stays in registers. Row m of a tile is therefore
+// unit hidden_unit(m). Only the parameter gradients, whose K runs over the
+// samples, need the other operand order: 16 x 16 tiles go through the wave's
+// LDS, written and read without bank conflicts.
+//
+// What bounds it: 5.5K multiply-adds a sample on the fp32 matrix cores (73 us
+// of 2^20 samples with 12-32-32-10 at their rate) and the filter's texel
+// reads, which two waves per SIMD overlap. The version before kept one row per
+// sample in LDS between all products, at strides of 32 and 33 floats (up to
+// 16 lanes on one bank): 390 -> 170 us for those 2^20 samples, 173 -> 36 us
+// for 2^18 with 12-16-16-8 (where the waves' own flushes, 3072 atomics a
+// parameter, weighed more; now one per workgroup, 512).
+__host__ __device__ constexpr uint32_t hidden_unit(uint32_t m) { return 4u * (m & 3u) + (m >> 2); }
+
+constexpr int kBwdWaves = 4;
+// floats per sample of the z and dL/dG rows: 16 and a pad that spreads the 64
+// lanes (16 rows, 4 columns) of an operand read over all 64 banks
+constexpr int kRowPad = 20;
+
+// The weights as A operands in LDS, four K chunks of a lane per 16 bytes:
+// forward rows for layer 0 (3 chunks) and the hidden layers, transposes for
+// the way back, and the biases in the order of a lane's registers.
+template <int H, int NH>
+struct BwdOps {
+    static constexpr int T = H / 16, NHID = NH > 1 ? NH - 1 : 1;
+    f32x4 f0[T][64], fh[NHID][T][T][64];          // W_0, W_l rows: [tile][K chunks / 4][lane]
+    f32x4 bo[T][64], bh[NHID][T][T][64], b0[T][64];   // W_out^T, W_l^T, W_0^T
+    f32x4 bias[NH][T][4];                         // [layer][tile][g]
+};
+
+// A wave's share of LDS: z and dL/dG of its 64 samples, one row each, and a
+// group's hidden activations and deltas, 16 x 16 tiles with one row per sample
+// (column 4 g + r: register r of lane group g).
+template <int H>
+struct __align__(16) BwdWave {
+    float z[64][kRowPad], go[64][kRowPad];
+    float act[H / 16][16][16], del[H / 16][16][16];
+};
+
+template <int H, int NH>
+__device__ __forceinline__ void load_ops(const TrainDesc &d, BwdOps<H, NH> &m)
 {
-    const uint32_t g = lane >> 4, i16 = lane & 15u;
+    constexpr int T = H / 16;
+    const uint32_t n0 = d.dims[0], c = d.dims[NH + 1];
+    const float *P = d.params;
+    for (uint32_t e = threadIdx.x; e < (uint32_t)(T * 64); e += blockDim.x) {
+        const uint32_t mb = e >> 6, L = e & 63u, g = L >> 4, i = L & 15u, u = 16u * mb + hidden_unit(i);
+        f32x4 a, b, w;
 #pragma unroll
-    for (int grp = 0; grp < 4; ++grp) {
+        for (uint32_t k = 0; k < 4; ++k) {
+            const uint32_t in = 4u * k + g, hid = 16u * mb + 4u * k + g;
+            a[k] = in < n0 && k < 3 ? P[d.w_off[0] + u * n0 + in] : 0.0f;
+            b[k] = in < c ? P[d.w_off[NH] + in * H + u] : 0.0f;
+            w[k] = i < n0 ? P[d.w_off[0] + hid * n0 + i] : 0.0f;     // rows 0 .. 11: the inputs in order
+        }
+        m.f0[mb][L] = a;
+        m.bo[mb][L] = b;
+        m.b0[mb][L] = w;
+    }
+    for (uint32_t e = threadIdx.x; e < (uint32_t)((NH - 1) * T * T * 64); e += blockDim.x) {
+        const uint32_t l = e / (T * T * 64), mb = e / (T * 64) % T, kq = e / 64 % T, L = e & 63u;
+        const uint32_t g = L >> 4, u = 16u * mb + hidden_unit(L & 15u);
+        const float *W = P + d.w_off[l + 1];
+        f32x4 a, b;
 #pragma unroll
-        for (int mb = 0; mb < MT; ++mb) {
-            f32x4 acc;
+        for (uint32_t k = 0; k < 4; ++k) {
+            const uint32_t in = 16u * kq + 4u * k + g;
+            a[k] = W[u * H + in];
+            b[k] = W[in * H + u];
+        }
+        m.fh[l][mb][kq][L] = a;
+        m.bh[l][mb][kq][L] = b;
+    }
+    for (uint32_t e = threadIdx.x; e < (uint32_t)(NH * T * 4); e += blockDim.x) {
+        const uint32_t l = e / (T * 4), mb = e / 4 % T, g = e & 3u;
+        f32x4 a;
 #pragma unroll
-            for (int r = 0; r < 4; ++r) acc[r] = BIAS ? W[(16 * mb + 4 * g + r) * ldw + bias_col] : 0.0f;
+        for (uint32_t r = 0; r < 4; ++r) a[r] = P[d.b_off[l] + 16u * mb + 4u * r + g];
+        m.bias[l][mb][g] = a;
+    }
+}
+
+__device__ __forceinline__ f32x4 mma4(f32x4 a, const float *b, f32x4 acc)
+{
 #pragma unroll
-            for (int kc = 0; kc < KC; ++kc) {
-                const uint32_t m = 16 * mb + i16, k = 4 * kc + g;
-                const float a = TRANS ? W[k * ldw + m] : W[m * ldw + k];
-                acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a, X[16 * grp + i16][k], acc, 0, 0, 0);
-            }
+    for (int k = 0; k < 4; ++k) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a[k], b[k], acc, 0, 0, 0);
+    return acc;
+}
+
+// A layer's parameter gradients, dL/dW[j][i] = sum over samples of delta[j] *
+// a[i], summed per wave on the matrix cores in 16 x 16 tiles, K running over
+// the samples (step s of a group: lane (g, i) supplies column i of sample
+// 4 s + g of both). The bias gradients are the per-lane sums of the delta
+// reads, added across the four lane groups at the end.
+template <int MT, int NT>
+struct LayerGrad {
+    f32x4 w[MT][NT];
+    float b[MT];
+};
+
+template <int MT, int NT>
+__device__ __forceinline__ void grad_zero(LayerGrad<MT, NT> &g)
+{
 #pragma unroll
-            for (int r = 0; r < 4; ++r) Y[16 * grp + i16][16 * mb + 4 * g + r] = RELU ? fmaxf(acc[r], 0.0f) : acc[r];
+    for (int m = 0; m < MT; ++m) {
+        g.b[m] = 0.0f;
+#pragma unroll
+        for (int n = 0; n < NT; ++n) g.w[m][n] = (f32x4){0.0f, 0.0f, 0.0f, 0.0f};
+    }
+}
+
+// dl, a: this lane's first element (sample g, column i) of the deltas and the
+// inputs, LD floats per sample, tiles 256 floats apart
+template <int MT, int NT, int LDD, int LDA>
+__device__ __forceinline__ void accumulate(LayerGrad<MT, NT> &g, const float *dl, const float *a)
+{
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+        float av[NT], dv[MT];
+#pragma unroll
+        for (int n = 0; n < NT; ++n) av[n] = a[256 * n + 4 * s * LDA];
+#pragma unroll
+        for (int m = 0; m < MT; ++m) {
+            dv[m] = dl[256 * m + 4 * s * LDD];
+            g.b[m] += dv[m];
+        }
+#pragma unroll
+        for (int m = 0; m < MT; ++m)
+#pragma unroll
+            for (int n = 0; n < NT; ++n) g.w[m][n] = __builtin_amdgcn_mfma_f32_16x16x4f32(dv[m], av[n], g.w[m][n], 0, 0, 0);
+    }
+}
+
+// Adds the workgroup's layer gradients to gw (W[n_out][n_in], row-major) and
+// gb (b[n_out]): the waves' tiles are summed through LDS (red: 1024 floats), so
+// that one float atomic per parameter and workgroup goes to memory. HO / HI:
+// the rows / columns are hidden units (in register order), else in order.
+template <bool HO, bool HI, int MT, int NT>
+__device__ __forceinline__ void flush(const LayerGrad<MT, NT> &gr, float *red, float *gw, float *gb, uint32_t n_in,
+                                      uint32_t n_out, uint32_t lane, uint32_t wv)
+{
+    static_assert(kBwdWaves == 4, "wave k sums register k of the four waves' tiles");
+    const uint32_t g = lane >> 4, i = lane & 15u;
+#pragma unroll
+    for (int m = 0; m < MT; ++m) {
+#pragma unroll
+        for (int n = 0; n < NT; ++n) {
+            __syncthreads();
+            *reinterpret_cast<f32x4 *>(red + 256 * wv + 4 * lane) = gr.w[m][n];
+            __syncthreads();
+            const float v = (red[4 * lane + wv] + red[256 + 4 * lane + wv]) +
+                            (red[512 + 4 * lane + wv] + red[768 + 4 * lane + wv]);
+            const uint32_t row = 4u * g + wv;
+            const uint32_t j = 16u * m + (HO ? hidden_unit(row) : row), k = 16u * n + (HI ? hidden_unit(i) : i);
+            if (j < n_out && k < n_in) unsafeAtomicAdd(gw + j * n_in + k, v);
+        }
+        float b = gr.b[m];
+        b += __shfl_xor(b, 16);
+        b += __shfl_xor(b, 32);
+        __syncthreads();
+        if (g == 0) red[16 * wv + i] = b;
+        __syncthreads();
+        if (threadIdx.x < 16) {
+            const uint32_t j = 16u * m + (HO ? hidden_unit(i) : i);
+            if (j < n_out) unsafeAtomicAdd(gb + j, (red[i] + red[16 + i]) + (red[32 + i] + red[48 + i]));
         }
     }
 }
 
-// Waves per workgroup of the backward: four when its LDS (per-wave rows for
-// the parameter-gradient products, the MLP, the level table) lets two
-// workgroups share a CU -- two waves per SIMD, as its registers allow --
-// else three.
 template <int H, int NH>
-constexpr int bwd_waves()
-{
-    constexpr int rows = 64 * (2 * kTrainMaxHidden + 1) * 4;
-    return 4 * rows + (int)sizeof(MlpLds<H, NH>) + (int)sizeof(TrainLevelLut) <= 80 * 1024 ? 4 : 3;
-}
-
-template <int H, int NH>
-__global__ void __launch_bounds__((64 * bwd_waves<H, NH>()), 2) k_train_backward(TrainDesc d, const float *queries, uint32_t n,
-                                                                const float *grad_out, const uint32_t *perm)
+__global__ void __launch_bounds__(64 * kBwdWaves, 2) k_train_backward(TrainDesc d, const float *queries, uint32_t n,
+                                                                      const float *grad_out, const uint32_t *perm)
 {
     constexpr int T = H / 16;                 // 16-wide tiles of a hidden layer
-    constexpr int kBwdWaves = bwd_waves<H, NH>();
-    __shared__ float lds_a[kBwdWaves][64][kTrainMaxHidden + 1];
-    __shared__ float lds_d[kBwdWaves][64][kTrainMaxHidden];
-    __shared__ MlpLds<H, NH> mlp;
+    __shared__ BwdWave<H> waves[kBwdWaves];
+    __shared__ BwdOps<H, NH> ops;
     __shared__ TrainLevelLut lut;
     load_level_lut(d, lut);
-    load_mlp<H, NH>(d, mlp);                  // synchronises, also for `lut`
+    load_ops<H, NH>(d, ops);
+    __syncthreads();
 
-    const uint32_t lane = threadIdx.x & 63u, wv = threadIdx.x >> 6;
+    const uint32_t lane = threadIdx.x & 63u, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const uint32_t g = lane >> 4, i16 = lane & 15u;
     const uint32_t n0 = d.dims[0], c = d.dims[NH + 1];
     // layer 0 (at most 12 inputs), the hidden layers, the output layer (at most 16 rows)
     LayerGrad<T, 1> g0;
@@ -640,8 +671,7 @@ __global__ void __launch_bounds__((64 * bwd_waves<H, NH>()), 2) k_train_backward
     for (int l = 0; l < (NH > 1 ? NH - 1 : 1); ++l) grad_zero(gh[l]);
     grad_zero(gl);
 
-    float (*a)[kTrainMaxHidden + 1] = lds_a[wv];
-    float (*dl)[kTrainMaxHidden] = lds_d[wv];
+    BwdWave<H> &w = waves[wv];
     // Samples in the sorted order, 64 per wave; workgroups are dealt to the
     // 8 XCDs in turn (the grid is a multiple of 8), and XCD x takes the x-th
     // eighth of the order.
@@ -655,94 +685,122 @@ __global__ void __launch_bounds__((64 * bwd_waves<H, NH>()), 2) k_train_backward
         const float u = live ? queries[3u * q] : 0.0f;
         const float v = live ? queries[3u * q + 1u] : 0.0f;
         const float s = live ? queries[3u * q + 2u] : 0.0f;
-        float z[12], act[NH][H];
+        float go[kMaxOut];
+#pragma unroll
+        for (int j = 0; j < kMaxOut; ++j) go[j] = live && (uint32_t)j < c ? grad_out[(size_t)q * c + j] : 0.0f;
+        float z[12];
         features(d, lut, u, v, s, z);
-        // the hidden layers on the matrix cores, layer by layer through the
-        // wave's LDS rows (inputs in one array, outputs in the other)
 #pragma unroll
-        for (int i = 0; i < 12; ++i) a[lane][i] = z[i];
+        for (int k = 0; k < 3; ++k)
+            *reinterpret_cast<f32x4 *>(&w.z[lane][4 * k]) = (f32x4){z[4 * k], z[4 * k + 1], z[4 * k + 2], z[4 * k + 3]};
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+            *reinterpret_cast<f32x4 *>(&w.go[lane][4 * k]) =
+                (f32x4){go[4 * k], go[4 * k + 1], go[4 * k + 2], go[4 * k + 3]};
         wave_sync_lds();
-        rows_product<T, 3, false, true, true>(&mlp.w0[0][0], 16, 12, a, dl, lane);
-        wave_sync_lds();
+#pragma unroll 1
+        for (uint32_t grp = 0; grp < 4; ++grp) {
+            const uint32_t row = 16u * grp + i16;
+            // the hidden layers
+            f32x4 act[NH][T];
+            {
+                float zb[4];
 #pragma unroll
-        for (int i = 0; i < H; ++i) act[0][i] = dl[lane][i];
+                for (int k = 0; k < 3; ++k) zb[k] = w.z[row][4 * k + g];
 #pragma unroll
-        for (int l = 1; l < NH; ++l) {
-            if (l & 1) rows_product<T, H / 4, false, true, true>(&mlp.wh[l - 1][0][0], H + 4, H, dl, a, lane);
-            else rows_product<T, H / 4, false, true, true>(&mlp.wh[l - 1][0][0], H + 4, H, a, dl, lane);
-            wave_sync_lds();
+                for (int mb = 0; mb < T; ++mb) {
+                    const f32x4 a = ops.f0[mb][lane];
+                    f32x4 acc = ops.bias[0][mb][g];
 #pragma unroll
-            for (int i = 0; i < H; ++i) act[l][i] = l & 1 ? a[lane][i] : dl[lane][i];
-            wave_sync_lds();
-        }
-        float delta[kTrainMaxHidden];
+                    for (int k = 0; k < 3; ++k) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a[k], zb[k], acc, 0, 0, 0);
 #pragma unroll
-        for (int j = 0; j < kTrainMaxHidden; ++j)
-            delta[j] = (live && j < kMaxOut && (uint32_t)j < c) ? grad_out[(size_t)q * c + j] : 0.0f;
-
-        // output layer: W[c][H]
-#pragma unroll
-        for (int i = 0; i < H; ++i) a[lane][i] = act[NH - 1][i];
-        a[lane][H] = 1.0f;
-#pragma unroll
-        for (int j = 0; j < kMaxOut; ++j) dl[lane][j] = delta[j];
-        wave_sync_lds();
-        accumulate(gl, a, dl, lane);
-        wave_sync_lds();
-        // back through the hidden layers: delta of hidden layer l's pre-activation
-#pragma unroll
-        for (int l = NH - 1; l >= 0; --l) {
-            // g = W_{l+1}^T delta, summed over the rows j in order; the rows
-            // of W_{l+1} are read whole (the output layer's past c are zero,
-            // and so are the deltas there)
-            // (on the matrix cores: the deltas are dl's rows, the products
-            // land in a's rows, which the parameter sums above have read)
-            if (l == NH - 1) rows_product<T, kMaxOut / 4, true, false, false>(&mlp.wl[0][0], H + 4, 0, dl, a, lane);
-            else rows_product<T, H / 4, true, false, false>(&mlp.wh[l][0][0], H + 4, 0, dl, a, lane);
-            wave_sync_lds();
-            float g[H];
-#pragma unroll
-            for (int i = 0; i < H; ++i) g[i] = act[l][i] > 0.0f ? a[lane][i] : 0.0f;
-            wave_sync_lds();
-#pragma unroll
-            for (int i = 0; i < H; ++i) delta[i] = g[i];
-            // parameters of layer l: inputs are act[l - 1] (or z), outputs delta
-            const uint32_t n_in = l == 0 ? n0 : H;
-            if (l == 0) {
-#pragma unroll
-                for (int i = 0; i < 12; ++i) a[lane][i] = z[i];
-            } else {
-#pragma unroll
-                for (int i = 0; i < H; ++i) a[lane][i] = act[l > 0 ? l - 1 : 0][i];
+                    for (int r = 0; r < 4; ++r) act[0][mb][r] = fmaxf(acc[r], 0.0f);
+                }
             }
-            a[lane][n_in] = 1.0f;
 #pragma unroll
-            for (int j = 0; j < H; ++j) dl[lane][j] = delta[j];
-            wave_sync_lds();
-            if (l == 0) accumulate(g0, a, dl, lane);
-            else accumulate(gh[l > 0 ? l - 1 : 0], a, dl, lane);
-            wave_sync_lds();
-        }
-        // dL/dz = W_0^T delta (rows 12 .. 15 of the product, from the bias
-        // column and the padding, are not used)
-        rows_product<1, H / 4, true, false, false>(&mlp.w0[0][0], 16, 0, dl, a, lane);
-        wave_sync_lds();
-        float dz[12];
+            for (int l = 1; l < NH; ++l) {
+                f32x4 acc[T];
 #pragma unroll
-        for (int i = 0; i < 12; ++i) dz[i] = a[lane][i];
-        wave_sync_lds();
-        // dL/dz in the sorted order, for the scatter
-        if (live) {
-            float4 *dst = reinterpret_cast<float4 *>(d.bin_dz + 12u * (size_t)slot);
-            dst[0] = make_float4(dz[0], dz[1], dz[2], dz[3]);
-            dst[1] = make_float4(dz[4], dz[5], dz[6], dz[7]);
-            dst[2] = make_float4(dz[8], dz[9], dz[10], dz[11]);
+                for (int mb = 0; mb < T; ++mb) acc[mb] = ops.bias[l][mb][g];
+#pragma unroll
+                for (int kq = 0; kq < T; ++kq) {
+                    const float x[4] = {act[l - 1][kq][0], act[l - 1][kq][1], act[l - 1][kq][2], act[l - 1][kq][3]};
+#pragma unroll
+                    for (int mb = 0; mb < T; ++mb) acc[mb] = mma4(ops.fh[l - 1][mb][kq][lane], x, acc[mb]);
+                }
+#pragma unroll
+                for (int mb = 0; mb < T; ++mb)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) act[l][mb][r] = fmaxf(acc[mb][r], 0.0f);
+            }
+            // back through them: del = delta of hidden layer l's pre-activation
+            f32x4 del[T];
+            {
+                float x[4];
+#pragma unroll
+                for (int k = 0; k < 4; ++k) x[k] = w.go[row][4 * k + g];
+#pragma unroll
+                for (int mb = 0; mb < T; ++mb) {
+                    const f32x4 zero = {0.0f, 0.0f, 0.0f, 0.0f};
+                    const f32x4 p = mma4(ops.bo[mb][lane], x, zero);
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) del[mb][r] = act[NH - 1][mb][r] > 0.0f ? p[r] : 0.0f;
+                }
+            }
+#pragma unroll
+            for (int mb = 0; mb < T; ++mb) {
+                *reinterpret_cast<f32x4 *>(&w.act[mb][i16][4 * g]) = act[NH - 1][mb];
+                *reinterpret_cast<f32x4 *>(&w.del[mb][i16][4 * g]) = del[mb];
+            }
+            wave_sync_lds();
+            accumulate<1, T, kRowPad, 16>(gl, &w.go[16 * grp + g][i16], &w.act[0][g][i16]);
+#pragma unroll
+            for (int l = NH - 1; l >= 1; --l) {
+                // the inputs of layer l, then its delta goes one layer down
+                wave_sync_lds();
+#pragma unroll
+                for (int mb = 0; mb < T; ++mb) *reinterpret_cast<f32x4 *>(&w.act[mb][i16][4 * g]) = act[l - 1][mb];
+                wave_sync_lds();
+                accumulate<T, T, 16, 16>(gh[l - 1], &w.del[0][g][i16], &w.act[0][g][i16]);
+                f32x4 p[T];
+#pragma unroll
+                for (int mb = 0; mb < T; ++mb) p[mb] = (f32x4){0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+                for (int kq = 0; kq < T; ++kq) {
+                    const float x[4] = {del[kq][0], del[kq][1], del[kq][2], del[kq][3]};
+#pragma unroll
+                    for (int mb = 0; mb < T; ++mb) p[mb] = mma4(ops.bh[l - 1][mb][kq][lane], x, p[mb]);
+                }
+#pragma unroll
+                for (int mb = 0; mb < T; ++mb)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) del[mb][r] = act[l - 1][mb][r] > 0.0f ? p[mb][r] : 0.0f;
+                wave_sync_lds();
+#pragma unroll
+                for (int mb = 0; mb < T; ++mb) *reinterpret_cast<f32x4 *>(&w.del[mb][i16][4 * g]) = del[mb];
+                wave_sync_lds();
+            }
+            accumulate<T, 1, 16, kRowPad>(g0, &w.del[0][g][i16], &w.z[16 * grp + g][i16]);
+            // dL/dz = W_0^T delta: lane (g, i) receives inputs 4 g .. 4 g + 3
+            // of sample i; stored in the sorted order, for the scatter
+            f32x4 dz = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+            for (int kq = 0; kq < T; ++kq) {
+                const float x[4] = {del[kq][0], del[kq][1], del[kq][2], del[kq][3]};
+                dz = mma4(ops.b0[kq][lane], x, dz);
+            }
+            const uint32_t to = ch * 64u + row;
+            if (g < 3 && to < n) *reinterpret_cast<f32x4 *>(d.bin_dz + 12u * (size_t)to + 4u * g) = dz;
+            wave_sync_lds();
         }
     }
-    flush(g0, d.g_params + d.w_off[0], d.g_params + d.b_off[0], n0, H, lane);
+    float *red = &waves[0].z[0][0];
+    static_assert(sizeof(waves[0].z) >= 1024 * sizeof(float), "the flush's sums fit a wave's rows");
+    flush<true, false>(g0, red, d.g_params + d.w_off[0], d.g_params + d.b_off[0], n0, H, lane, wv);
 #pragma unroll
-    for (int l = 1; l < NH; ++l) flush(gh[l - 1], d.g_params + d.w_off[l], d.g_params + d.b_off[l], H, H, lane);
-    flush(gl, d.g_params + d.w_off[NH], d.g_params + d.b_off[NH], H, c, lane);
+    for (int l = 1; l < NH; ++l)
+        flush<true, true>(gh[l - 1], red, d.g_params + d.w_off[l], d.g_params + d.b_off[l], H, H, lane, wv);
+    flush<false, true>(gl, red, d.g_params + d.w_off[NH], d.g_params + d.b_off[NH], H, c, lane, wv);
 }
 
 // ---------------------------------------------------------------------------
@@ -956,11 +1014,9 @@ hipError_t forward_hn(const TrainDesc &d, const float *queries, uint32_t n, floa
 template <int H, int NH>
 hipError_t backward_hn(const TrainDesc &d, const float *queries, uint32_t n, const float *grad_out, hipStream_t s)
 {
-    // a few workgroups per CU (each flushes its parameter and small-level
-    // sums once), a multiple of the 8 XCDs
-    constexpr int waves = bwd_waves<H, NH>();
-    const unsigned grid = (grid_for((n + 63u) / 64u, waves, 768) + 7u) & ~7u;
-    k_train_backward<H, NH><<<grid, 64 * waves, 0, s>>>(d, queries, n, grad_out, d.bin_perm);
+    // the workgroups resident at once (two per CU), a multiple of the 8 XCDs
+    const unsigned grid = (grid_for((n + 63u) / 64u, kBwdWaves, 512) + 7u) & ~7u;
+    k_train_backward<H, NH><<<grid, 64 * kBwdWaves, 0, s>>>(d, queries, n, grad_out, d.bin_perm);
     return hipGetLastError();
 }
 

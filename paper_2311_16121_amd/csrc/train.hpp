@@ -11,7 +11,6 @@
 
 namespace bcf {
 
-constexpr int kTrainMaxHidden = 32;
 // The backward takes its samples in spatial order: per call of at most
 // kTrainBinBatch samples, a counting sort by cell of a kTrainBinSide^2 grid
 // over the wrapped (u, v), the cells numbered along a Z-order curve.

@@ -53,3 +53,31 @@ def test_fp32_decode_and_calibration_share_a_workspace(bcf, sizes, dims):
     assert np.abs(want - oracle.decode(host, q)).max() <= 1e-5
     # z0's largest magnitude: one binary32 filter against binary64, so a few ulp
     assert abs(float(absmax[0]) - np.abs(oracle.sample(host, q)).max()) <= 1e-6
+
+
+@pytest.mark.parametrize("n,dims", [(1, (12, 32, 32, 10)), (15, (12, 16, 1)), (17, (9, 32, 16)), (63, (12, 16, 16, 8)),
+                                    (65, (12, 32, 32, 32, 16)), (130, (3, 16, 16, 16, 3))])
+def test_training_backward_over_ragged_groups(bcf, n, dims):
+    """The backward's groups of 16 samples and chunks of 64, partly filled, at
+    every depth and width of its tiles, against the binary64 oracle. The bar is
+    the training tests' (2e-4 of a tensor's largest gradient: binary32 sums)."""
+    from oracle import train as T
+    g = synth.rng(700 + n)
+    texs = []
+    for _ in range(dims[0] // 3):
+        nb = synth.chain_blocks(32, 32, 6)
+        texs.append(T.TrainTexture(32, 32, 6, endpoints=g.uniform(0.0, 31.0, (nb, 4, 3)).astype(np.float32),
+                                   indices=g.uniform(0.0, 1.0, (nb, 16)).astype(np.float32),
+                                   partitions=g.integers(0, 32, nb).astype(np.uint8), lod_bias=0.0))
+    params = synth.mlp_params(dims, g).astype(np.float32)
+    q = synth.uniform_queries(n, g, 5.0)
+    go = g.standard_normal((n, dims[-1])).astype(np.float32)
+    geo = bcf.TrainGeometry([32] * len(texs), [6] * len(texs), [dev(t.partitions) for t in texs], dims,
+                            straight_through=True)
+    g_end, g_idx, g_par = bcf.train_backward(geo, [dev(t.endpoints) for t in texs], [dev(t.indices) for t in texs],
+                                             dev(params), dev(q), dev(go))
+    _, r_end, r_idx, r_par = T.gradients(texs, dims, params, q, go, True)
+    for got, ref in list(zip(g_end, r_end)) + list(zip(g_idx, r_idx)) + [(g_par, r_par)]:
+        ref = np.asarray(ref)
+        err = np.abs(got.cpu().numpy().reshape(ref.shape) - ref).max()
+        assert err <= 2e-4 * max(np.abs(ref).max(), 1e-30)
