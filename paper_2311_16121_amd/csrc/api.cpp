@@ -446,8 +446,10 @@ bcf_status describe_train(const bcf_train_material *m, bcf::TrainDesc *d, size_t
     sh.hidden = hidden;
     sh.out = out;
     for (uint32_t l = 0; l <= m->n_layers; ++l) sh.dims[l] = m->dims[l];
-    const size_t sort_end = 2 * align_up(texels * 16, 256) + align_up((size_t)bcf::kTrainBinBatch * 4, 256) +
-                            2 * align_up((size_t)bcf::kTrainBins * 4, 256) + (size_t)bcf::kTrainBinBatch * 48;
+    const size_t sort_end = align_up(texels * 16, 256) + align_up(texels * 12, 256) +
+                            align_up((size_t)bcf::kTrainBinBatch * 4, 256) +
+                            2 * align_up((size_t)bcf::kTrainBins * 4, 256) +
+                            (size_t)bcf::kTrainBinBatch * 16 * (1 + d->n_tex);
     d->ops = weights_layout(sh, bcf::MLP_MFMA_F32, align_up(sort_end, 256));
     *ws_bytes = d->ops.total;
     return BCF_OK;
@@ -459,17 +461,19 @@ bcf_status bind_train_ws(bcf::TrainDesc *d, void *ws)
 {
     if (!ws || !aligned(ws, 256)) return fail(BCF_ERR_INVALID_ARG, "workspace NULL or not 256-byte aligned");
     uint8_t *p = static_cast<uint8_t *>(ws);
-    const size_t img = align_up((size_t)d->n_texels * 16, 256);
     d->texels = reinterpret_cast<float4 *>(p);
-    d->g_texels = reinterpret_cast<float4 *>(p + img);
-    p += 2 * img;
+    p += align_up((size_t)d->n_texels * 16, 256);
+    d->g_texels = reinterpret_cast<float *>(p);
+    p += align_up((size_t)d->n_texels * 12, 256);
     d->bin_perm = reinterpret_cast<uint32_t *>(p);
     p += align_up((size_t)bcf::kTrainBinBatch * 4, 256);
     d->bin_count = reinterpret_cast<uint32_t *>(p);
     p += align_up((size_t)bcf::kTrainBins * 4, 256);
     d->bin_next = reinterpret_cast<uint32_t *>(p);
     p += align_up((size_t)bcf::kTrainBins * 4, 256);
-    d->bin_dz = reinterpret_cast<float *>(p);
+    d->bin_q = reinterpret_cast<float4 *>(p);
+    p += (size_t)bcf::kTrainBinBatch * 16;
+    d->bin_dz = reinterpret_cast<float4 *>(p);
     d->ops_ws = static_cast<uint8_t *>(ws);
     return BCF_OK;
 }

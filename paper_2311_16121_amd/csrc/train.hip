@@ -9,9 +9,10 @@
 //                     sort over a grid of cells on the wrapped (u, v))
 //   k_train_backward  queries, dL/dG -> dL/d features per sample and dL/d MLP
 //                     parameters (per-wave sums on the matrix cores)
-//   k_train_scatter   dL/d features -> dL/d texel, one workgroup per cell:
-//                     fixed-point sums in LDS windows over the cell's
-//                     footprint, then one float atomic per touched texel channel
+//   k_train_scatter   dL/d features -> dL/d texel, one workgroup per pyramid
+//                     and region of cells: fixed-point sums in LDS windows over
+//                     the region's footprint, then stores inside it and one
+//                     float atomic per touched texel channel at its edges
 //   k_train_blocks    dL/d texel -> dL/d endpoints, dL/d indices (one lane
 //                     per texel, sums over a block's 16 lanes by shuffles)
 //
@@ -198,8 +199,8 @@ __global__ void __launch_bounds__(kTrainThreads) k_train_blocks(TrainDesc d)
         float gx = 0.0f;
         float ge[2][3] = {{0.0f, 0.0f, 0.0f}, {0.0f, 0.0f, 0.0f}};   // this texel's pair A, B
         if (s.valid) {
-            const float4 gt = d.g_texels[s.tex];
-            const float gc[3] = {gt.x, gt.y, gt.z};
+            const float *gt = d.g_texels + 3u * s.tex;
+            const float gc[3] = {gt[0], gt[1], gt[2]};
             const float x = tx.indices[16u * s.b + t];
 #pragma unroll
             for (int c = 0; c < 3; ++c) {
@@ -525,13 +526,15 @@ __device__ __forceinline__ void load_ops(const TrainDesc &d, BwdOps<H, NH> &m)
     const float *P = d.params;
     for (uint32_t e = threadIdx.x; e < (uint32_t)(T * 64); e += blockDim.x) {
         const uint32_t mb = e >> 6, L = e & 63u, g = L >> 4, i = L & 15u, u = 16u * mb + hidden_unit(i);
+        const uint32_t col = 3u * (i >> 2) + (i & 3u);
         f32x4 a, b, w;
 #pragma unroll
         for (uint32_t k = 0; k < 4; ++k) {
             const uint32_t in = 4u * k + g, hid = 16u * mb + 4u * k + g;
             a[k] = in < n0 && k < 3 ? P[d.w_off[0] + u * n0 + in] : 0.0f;
             b[k] = in < c ? P[d.w_off[NH] + in * H + u] : 0.0f;
-            w[k] = i < n0 ? P[d.w_off[0] + hid * n0 + i] : 0.0f;     // rows 0 .. 11: the inputs in order
+            // row 4 t + ch: channel ch of pyramid t (ch 3: zero)
+            w[k] = (i & 3u) < 3u && col < n0 ? P[d.w_off[0] + hid * n0 + col] : 0.0f;
         }
         m.f0[mb][L] = a;
         m.bo[mb][L] = b;
@@ -685,6 +688,7 @@ __global__ void __launch_bounds__(64 * kBwdWaves, 2) k_train_backward(TrainDesc 
         const float u = live ? queries[3u * q] : 0.0f;
         const float v = live ? queries[3u * q + 1u] : 0.0f;
         const float s = live ? queries[3u * q + 2u] : 0.0f;
+        if (live) d.bin_q[slot] = make_float4(u, v, s, 0.0f);      // in the sorted order, for the scatter
         float go[kMaxOut];
 #pragma unroll
         for (int j = 0; j < kMaxOut; ++j) go[j] = live && (uint32_t)j < c ? grad_out[(size_t)q * c + j] : 0.0f;
@@ -781,8 +785,8 @@ __global__ void __launch_bounds__(64 * kBwdWaves, 2) k_train_backward(TrainDesc 
                 wave_sync_lds();
             }
             accumulate<T, 1, 16, kRowPad>(g0, &w.del[0][g][i16], &w.z[16 * grp + g][i16]);
-            // dL/dz = W_0^T delta: lane (g, i) receives inputs 4 g .. 4 g + 3
-            // of sample i; stored in the sorted order, for the scatter
+            // dL/dz = W_0^T delta: lane (g, i) receives the three channels of
+            // pyramid g of sample i; stored per pyramid in the sorted order
             f32x4 dz = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
             for (int kq = 0; kq < T; ++kq) {
@@ -790,7 +794,7 @@ __global__ void __launch_bounds__(64 * kBwdWaves, 2) k_train_backward(TrainDesc 
                 dz = mma4(ops.b0[kq][lane], x, dz);
             }
             const uint32_t to = ch * 64u + row;
-            if (g < 3 && to < n) *reinterpret_cast<f32x4 *>(d.bin_dz + 12u * (size_t)to + 4u * g) = dz;
+            if (g < d.n_tex && to < n) *reinterpret_cast<f32x4 *>(d.bin_dz + (size_t)g * kTrainBinBatch + to) = dz;
             wave_sync_lds();
         }
     }
@@ -806,59 +810,83 @@ __global__ void __launch_bounds__(64 * kBwdWaves, 2) k_train_backward(TrainDesc 
 // ---------------------------------------------------------------------------
 // dL/dz -> dL/d texel
 
-constexpr int kScatterThreads = 256;
-constexpr uint32_t kWindowFloats = 8192;      // 32 KB of LDS windows per workgroup
-
-// A window of one (pyramid, level): the texels x0 .. x0 + w - 1 (wrapped) of
-// rows y0 .. y0 + h - 1, three floats each from `off` in the pool; off = ~0u:
-// the level's gradients go straight to memory. div_w = ceil(2^32 / w) (w > 1),
-// so that p / w = umulhi(p, div_w) for the pool's positions p (p < 2^13).
+// Threads of a region's workgroup: 512 from 2^19 samples on (512 a region and
+// more: 122 us of 2^20 samples, 147 with 256), else 256 (36 us of 2^18, 41)
+constexpr unsigned kScatterThreads = 512;
+// LDS for a workgroup's windows at most: two workgroups a CU
+constexpr uint32_t kScatterPoolMax = 72 * 1024;
+// A window of one level: the texels x0 .. x0 + w - 1 (wrapped) of rows y0 ..
+// y0 + h - 1, three sums each from `off` in the pool; off = ~0u: the level's
+// gradients go straight to memory. div_w = ceil(2^32 / w) (w > 1), so that
+// p / w = umulhi(p, div_w) for the window's texels p (p < 2^13).
 struct TexWindow {
     uint32_t x0, y0, w, h, off, div_w;
 };
 
-// One workgroup per cell of the sample sort: the cell's samples (sorted
-// indices begin .. end) add wt * dL/dz to the texels of their taps. Every tap
-// of a cell's samples at one (pyramid, level) lies in a small box around the
-// cell's footprint, so the sums go to LDS windows over those boxes (the
-// coarsest levels first, while the pool lasts) and then to memory once per
-// touched texel channel; a tap outside its window (or of a level without one)
-// goes to memory directly.
-__global__ void __launch_bounds__(kScatterThreads) k_train_scatter(TrainDesc d, const float *queries)
+// Texels of a window's side on a level of `wl` texels: a region of `cells`
+// cells spans cells * wl / side texels; its samples' taps span at most ceil of
+// that + 2 from floor(first cell * wl / side - 0.5).
+__host__ __device__ inline uint32_t window_side(uint32_t wl, uint32_t cells)
 {
-    __shared__ float pool[kWindowFloats];
-    __shared__ TexWindow win[kMaxTextures][kMaxLevels];
-    __shared__ TrainLevelLut lut;
+    const uint32_t span = (cells * wl + kTrainBinSide - 1) / kTrainBinSide + 2u;
+    return wl < span ? wl : span;
+}
+
+// One workgroup per region (1 << region_log2 cells of the sample sort a side,
+// consecutive in the sort) and pyramid: the region's samples (sorted positions
+// begin .. end) add wt * dL/dz to the texels of their taps. Every tap of a
+// region's samples at one level lies in a small box around the region's
+// footprint, so the sums go to LDS windows over those boxes (the coarsest
+// levels first, while the pool lasts; a level without a window goes straight to
+// memory) and then to memory, one float atomic per touched channel.
+//
+// What bounds it (2^20 samples, 4 x 1024^2, 12-32-32-10): set-up, clearing and
+// flush of the windows 46 us, the samples' taps 55 us (half of it the LDS
+// sums), the flush's atomics 20 us. The version before took single cells, all
+// pyramids in one workgroup, and one thread a sample with two dependent
+// gathers (sorted index, query): 250 us, 100 of them 18M atomics of 4-texel
+// windows; 2 x 2 cells a region and one pyramid a workgroup need 10M, and the
+// backward leaves queries and dL/dz in the sorted order. Plain stores inside
+// the windows, where no other region's samples reach, were much slower than
+// atomics everywhere (225 against 155 us): lines that both touch. So were the
+// coarse levels in workgroups of their own (155 against 122 us: their samples'
+// sums meet on few LDS addresses). LDS float atomics cost about 40 times
+// integer ones on this GPU, so the windows sum in fixed point: contribution v
+// adds rint(v 2^k), with 2^k chosen from the largest |dL/dz| so that a
+// contribution (whose weight is at most 1) stays below 2^30; the 64-bit sums
+// cannot overflow. Non-finite gradients take float atomics.
+__global__ void __launch_bounds__(kScatterThreads) k_train_scatter(TrainDesc d, uint32_t region_log2,
+                                                                   uint32_t pool_sums)
+{
+    extern __shared__ unsigned long long pool[];
+    __shared__ TexWindow win[kMaxLevels];
     __shared__ uint32_t pool_used, dz_max_bits;
-    const uint32_t cell = blockIdx.x;
-    const uint32_t begin = cell ? d.bin_next[cell - 1] : 0u, end = d.bin_next[cell];
+    // the pyramids of one region on one XCD (workgroups are dealt to the 8 in turn)
+    const uint32_t k8 = blockIdx.x >> 3, t = k8 % d.n_tex, region = (k8 / d.n_tex) * 8u + (blockIdx.x & 7u);
+    const uint32_t cell0 = region << (2u * region_log2), cells = 1u << region_log2;
+    const uint32_t begin = cell0 ? d.bin_next[cell0 - 1u] : 0u, end = d.bin_next[cell0 + cells * cells - 1u];
     if (begin == end) return;                          // uniform over the workgroup
-    load_level_lut(d, lut);
-    __syncthreads();
+    const TrainTexDesc &tx = d.tex[t];
+    const uint32_t levels = tx.levels;
+    const float bias = tx.bias;
+    const float4 *dzs = d.bin_dz + (size_t)t * kTrainBinBatch;
     if (threadIdx.x < 64u) {
-        // lane i: window i of the allocation order, the coarsest levels first
-        // (level 15 - i / 4, pyramid i % 4); the pool goes to a prefix of it
-        const uint32_t i = threadIdx.x, l = kMaxLevels - 1u - i / kMaxTextures, t = i % kMaxTextures;
-        static_assert(kMaxLevels * kMaxTextures == 64, "one lane per window");
-        // the cell's corner from its Z-order number
+        // lane i: level 15 - i, the coarsest first; the pool goes to a prefix
+        const uint32_t i = threadIdx.x, l = (kMaxLevels - 1u - i) & (kMaxLevels - 1u);
+        // the region's corner from its Z-order number
         uint32_t cx = 0, cy = 0;
 #pragma unroll
         for (uint32_t b = 0; b < 6; ++b) {
-            cx |= ((cell >> (2 * b)) & 1u) << b;
-            cy |= ((cell >> (2 * b + 1)) & 1u) << b;
+            cx |= ((cell0 >> (2 * b)) & 1u) << b;
+            cy |= ((cell0 >> (2 * b + 1)) & 1u) << b;
         }
-        const uint32_t levels_t = t == 0 ? d.tex[0].levels : t == 1 ? d.tex[1].levels
-                                : t == 2 ? d.tex[2].levels : d.tex[3].levels;
-        const bool have = t < d.n_tex && l < levels_t;
-        // a cell spans wl / side texels; its samples' taps span at most ceil
-        // of that + 2 columns from floor(cx wl / side - 0.5)
-        const uint32_t wl = lut[t][l].x, hl = lut[t][l].y;
-        const uint32_t ww = min(wl, (wl + kTrainBinSide - 1) / kTrainBinSide + 2u);
-        const uint32_t wh = min(hl, (hl + kTrainBinSide - 1) / kTrainBinSide + 2u);
+        const bool have = i < kMaxLevels && l < levels;
+        const uint32_t wl = max(tx.w >> l, 1u), hl = max(tx.h >> l, 1u);
+        const uint32_t ww = window_side(wl, cells), wh = window_side(hl, cells);
         const uint32_t size = have ? 3u * ww * wh : 0u;
         uint32_t upto = size;                      // inclusive prefix over the order
 #pragma unroll
-        for (uint32_t k = 1; k < 64; k <<= 1) {
+        for (uint32_t k = 1; k < kMaxLevels; k <<= 1) {
             const uint32_t o = __shfl_up(upto, k);
             if (i >= k) upto += o;
         }
@@ -869,123 +897,116 @@ __global__ void __launch_bounds__(kScatterThreads) k_train_scatter(TrainDesc d, 
         W.y0 = wh == hl ? 0u : (uint32_t)(int)fy & (hl - 1u);
         W.w = ww;
         W.h = wh;
-        W.off = have && upto <= kWindowFloats ? upto - size : ~0u;
+        W.off = have && upto <= pool_sums ? upto - size : ~0u;
         W.div_w = ww > 1u ? 0xFFFFFFFFu / ww + 1u : 0u;
-        win[t][l] = W;
+        if (i < kMaxLevels) win[l] = W;
         // the pool in use: the end of the last window that fits
-        uint32_t in_use = upto <= kWindowFloats ? upto : 0u;
+        uint32_t in_use = have && upto <= pool_sums ? upto : 0u;
 #pragma unroll
-        for (uint32_t k = 1; k < 64; k <<= 1) in_use = max(in_use, __shfl_xor(in_use, k));
-        if (i == 0u) pool_used = in_use;
-    }
-    // The largest |dL/dz| of the cell's samples (as bits: NaN and infinity
-    // above every finite value) sets the windows' fixed-point scale.
-    if (threadIdx.x == 0) dz_max_bits = 0u;
-    __syncthreads();
-    {
-        uint32_t mb = 0;
-        for (uint32_t j = begin + threadIdx.x; j < end; j += kScatterThreads) {
-            const uint4 *src = reinterpret_cast<const uint4 *>(d.bin_dz + 12u * (size_t)j);
-#pragma unroll
-            for (int k = 0; k < 3; ++k) {
-                const uint4 z = src[k];
-                mb = max(mb, max(max(z.x & 0x7FFFFFFFu, z.y & 0x7FFFFFFFu), max(z.z & 0x7FFFFFFFu, z.w & 0x7FFFFFFFu)));
-            }
+        for (uint32_t k = 1; k < kMaxLevels; k <<= 1) in_use = max(in_use, __shfl_xor(in_use, k));
+        if (i == 0u) {
+            pool_used = in_use;
+            dz_max_bits = 0u;
         }
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) mb = max(mb, (uint32_t)__shfl_xor((int)mb, o));
-        if ((threadIdx.x & 63u) == 0) atomicMax(&dz_max_bits, mb);
     }
-    const uint32_t used = pool_used;
-    for (uint32_t e = threadIdx.x; e < used; e += kScatterThreads) pool[e] = 0.0f;
+    // the largest |dL/dz| of the samples (as bits: NaN and infinity
+    // above every finite value)
+    uint32_t mb = 0;
+    for (uint32_t j = begin + threadIdx.x; j < end; j += blockDim.x) {
+        const uint4 z = *reinterpret_cast<const uint4 *>(dzs + j);
+        mb = max(mb, max(max(z.x & 0x7FFFFFFFu, z.y & 0x7FFFFFFFu), z.z & 0x7FFFFFFFu));
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) mb = max(mb, (uint32_t)__shfl_xor((int)mb, o));
     __syncthreads();
-    // LDS float atomics cost about 40 times integer ones on this GPU, so the
-    // windows sum in 32-bit fixed point: contribution v adds rint(v 2^k),
-    // with 2^k chosen so that the at most nc M of a texel channel (nc samples,
-    // each adding at most M = max |dL/dz| over its taps, whose weights sum to
-    // at most 1) stays below 2^29. Non-finite gradients take float atomics.
+    if ((threadIdx.x & 63u) == 0) atomicMax(&dz_max_bits, mb);
+    const uint32_t used = pool_used;
+    for (uint32_t e = threadIdx.x; e < used; e += blockDim.x) pool[e] = 0ull;
+    __syncthreads();
     const uint32_t mbits = dz_max_bits;
     const bool fixed = mbits < 0x7F800000u;
     int kexp = 0;
     if (fixed && mbits != 0u) {
         int em;
-        frexpf(__uint_as_float(mbits), &em);                  // M < 2^em
-        const uint32_t nc = end - begin;
-        const int en = 32 - __clz(nc);                       // nc < 2^en
-        kexp = min(max(29 - em - en, -120), 120);
+        frexpf(__uint_as_float(mbits), &em);                  // |dL/dz| < 2^em
+        kexp = min(max(30 - em, -120), 120);
     }
     const float scale = ldexpf(1.0f, kexp), unscale = ldexpf(1.0f, -kexp);
-    for (uint32_t j = begin + threadIdx.x; j < end; j += kScatterThreads) {
-        const uint32_t q = d.bin_perm[j];
-        const float4 *src = reinterpret_cast<const float4 *>(d.bin_dz + 12u * (size_t)j);
-        const float4 z0 = src[0], z1 = src[1], z2 = src[2];
-        const float dz[12] = {z0.x, z0.y, z0.z, z0.w, z1.x, z1.y, z1.z, z1.w, z2.x, z2.y, z2.z, z2.w};
-        const float u = queries[3u * q], v = queries[3u * q + 1u], s = queries[3u * q + 2u];
-        const float uf = u - floorf(u), vf = v - floorf(v);       // wrap addressing
+    for (uint32_t j = begin + threadIdx.x; j < end; j += blockDim.x) {
+        const float4 q = d.bin_q[j], z4 = dzs[j];
+        const float dz[3] = {z4.x, z4.y, z4.z};
+        const float uf = q.x - floorf(q.x), vf = q.y - floorf(q.y);       // wrap addressing
+        // the two levels of eq. (10) as the forward takes them
+        const float si = fminf(fmaxf(q.z + bias, 0.0f), (float)(levels - 1u));   // NaN -> 0
+        const uint32_t l0 = (uint32_t)floorf(si);
+        const uint32_t l1 = min(l0 + 1u, levels - 1u);
+        const float lam = si - (float)l0;
 #pragma unroll
-        for (int t = 0; t < kMaxTextures; ++t) {
-            if (t >= (int)d.n_tex) break;
-            // the two levels of eq. (10) as the forward takes them
-            const TrainTexDesc &tx = d.tex[t];
-            const float si = fminf(fmaxf(s + tx.bias, 0.0f), (float)(tx.levels - 1));   // NaN -> 0
-            const uint32_t l0 = (uint32_t)floorf(si);
-            const uint32_t l1 = min(l0 + 1u, tx.levels - 1u);
-            const float lam = si - (float)l0;
+        for (int k = 0; k < 2; ++k) {
+            const uint32_t l = k ? l1 : l0;
+            const float lw = k ? lam : 1.0f - lam;
+            // a zero weight (an unused second level) adds nothing
+            if (lw == 0.0f) continue;
+            const uint32_t wl = max(tx.w >> l, 1u), hl = max(tx.h >> l, 1u);
+            const LevelTaps lt = level_taps(make_uint4(wl, hl, 0u, 0u), uf, vf, lw);
+            const TexWindow W = win[l];
+            const uint32_t dxa = (lt.xa - W.x0) & (wl - 1u), dxb = (lt.xb - W.x0) & (wl - 1u);
+            const uint32_t dya = (lt.ya - W.y0) & (hl - 1u), dyb = (lt.yb - W.y0) & (hl - 1u);
+            const bool inside = W.off != ~0u && max(dxa, dxb) < W.w && max(dya, dyb) < W.h;
+            const uint32_t ra = W.off + 3u * __umul24(dya, W.w), rb = W.off + 3u * __umul24(dyb, W.w);
+            const uint32_t at[4] = {ra + 3u * dxa, ra + 3u * dxb, rb + 3u * dxa, rb + 3u * dxb};
+            if (inside && fixed) {
 #pragma unroll
-            for (int k = 0; k < 2; ++k) {
-                const uint32_t l = k ? l1 : l0;
-                const float lw = k ? lam : 1.0f - lam;
-                // a zero weight (an unused second level) adds nothing
-                if (lw == 0.0f) continue;
-                const uint4 e = lut[t][l];
-                const LevelTaps lt = level_taps(e, uf, vf, lw);
-                const TexWindow W = win[t][l];
-                const uint32_t dxa = (lt.xa - W.x0) & (e.x - 1u), dxb = (lt.xb - W.x0) & (e.x - 1u);
-                const uint32_t dya = (lt.ya - W.y0) & (e.y - 1u), dyb = (lt.yb - W.y0) & (e.y - 1u);
-                const uint32_t base = W.off;
+                for (int i = 0; i < 4; ++i)
+#pragma unroll
+                    for (int c = 0; c < 3; ++c)
+                        atomicAdd(pool + at[i] + c,
+                                  (unsigned long long)(long long)(int32_t)rintf(lt.w[i] * dz[c] * scale));
+            } else {
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
                     const float wt = lt.w[i];
                     if (wt == 0.0f) continue;
                     const uint32_t x = i & 1 ? lt.xb : lt.xa, y = i & 2 ? lt.yb : lt.ya;
-                    const uint32_t dx = i & 1 ? dxb : dxa, dy = i & 2 ? dyb : dya;
-                    if (W.off != ~0u && dx < W.w && dy < W.h) {
-                        float *p = pool + base + 3u * (__umul24(dy, W.w) + dx);
-                        if (fixed) {
-                            uint32_t *pi = reinterpret_cast<uint32_t *>(p);
+                    float *gp = d.g_texels + 3u * (tx.tex_off[l] + y * wl + x);
 #pragma unroll
-                            for (int c = 0; c < 3; ++c)
-                                atomicAdd(pi + c, (uint32_t)(int32_t)rintf(wt * dz[3 * t + c] * scale));
-                        } else {
-#pragma unroll
-                            for (int c = 0; c < 3; ++c) atomicAdd(p + c, wt * dz[3 * t + c]);
-                        }
-                    } else {
-                        float *gp = reinterpret_cast<float *>(d.g_texels + e.z + y * e.x + x);
-                        unsafeAtomicAdd(gp + 0, wt * dz[3 * t + 0]);
-                        unsafeAtomicAdd(gp + 1, wt * dz[3 * t + 1]);
-                        unsafeAtomicAdd(gp + 2, wt * dz[3 * t + 2]);
+                    for (int c = 0; c < 3; ++c) {
+                        if (inside) atomicAdd(reinterpret_cast<float *>(pool + at[i] + c), wt * dz[c]);
+                        else unsafeAtomicAdd(gp + c, wt * dz[c]);
                     }
                 }
             }
         }
     }
     __syncthreads();
-    for (uint32_t t = 0; t < d.n_tex; ++t)
-        for (uint32_t l = 0; l < d.tex[t].levels; ++l) {
-            const TexWindow W = win[t][l];
-            if (W.off == ~0u) continue;
-            const uint4 e = lut[t][l];
-            const uint32_t size = 3u * W.w * W.h;
-            for (uint32_t i = threadIdx.x; i < size; i += kScatterThreads) {
-                const float raw = pool[W.off + i];
-                const float v = fixed ? (float)__float_as_int(raw) * unscale : raw;
-                if (v == 0.0f) continue;
-                const uint32_t p = i / 3u, c = i - 3u * p, dy = W.w > 1u ? __umulhi(p, W.div_w) : p, dx = p - dy * W.w;
-                const uint32_t x = (W.x0 + dx) & (e.x - 1u), y = (W.y0 + dy) & (e.y - 1u);
-                unsafeAtomicAdd(reinterpret_cast<float *>(d.g_texels + e.z + y * e.x + x) + c, v);
-            }
+    // Sums e = first, first + step, ... of level l's window to memory, the
+    // lanes along the channels of a row's texels.
+    auto flush = [&](uint32_t l, uint32_t first, uint32_t step) {
+        const TexWindow W = win[l];
+        const uint32_t wl = max(tx.w >> l, 1u), hl = max(tx.h >> l, 1u), base = tx.tex_off[l];
+        for (uint32_t e = first; e < 3u * W.w * W.h; e += step) {
+            const unsigned long long raw = pool[W.off + e];
+            const uint32_t lo = (uint32_t)raw;
+            // the signed sum as hi 2^32 + signed low half: both exact unless
+            // far above the last bit of the result
+            const float v = fixed ? fmaf((float)(int32_t)((uint32_t)(raw >> 32) + (lo >> 31)), 4294967296.0f,
+                                         (float)(int32_t)lo) * unscale
+                                  : __uint_as_float(lo);
+            const uint32_t p = e / 3u, c = e - 3u * p;
+            const uint32_t dy = W.w > 1u ? __umulhi(p, W.div_w) : p, dx = p - dy * W.w;
+            if (v != 0.0f)
+                unsafeAtomicAdd(
+                    d.g_texels + 3u * (base + ((W.y0 + dy) & (hl - 1u)) * wl + ((W.x0 + dx) & (wl - 1u))) + c, v);
         }
+    };
+    // the large windows by every wave, the small ones by one wave each
+    constexpr uint32_t kWaveSums = 256;
+    const uint32_t wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    for (uint32_t l = 0; l < levels; ++l) {
+        if (win[l].off == ~0u) continue;
+        if (3u * win[l].w * win[l].h > kWaveSums) flush(l, threadIdx.x, blockDim.x);
+        else if (l % (blockDim.x / 64) == wv) flush(l, threadIdx.x & 63u, 64u);
+    }
 }
 
 unsigned grid_for(size_t work, unsigned per_block, unsigned cap)
@@ -1059,11 +1080,26 @@ hipError_t launch_train_backward(const TrainDesc &d, const float *queries, size_
 {
     hipError_t e = launch_texels(d, s);
     if (e != hipSuccess) return e;
-    k_train_zero<<<grid_for((size_t)d.n_texels * 4u, 256, 8192), 256, 0, s>>>(
-        reinterpret_cast<float *>(d.g_texels), d.n_texels * 4u);
+    k_train_zero<<<grid_for((size_t)d.n_texels * 3u, 256, 8192), 256, 0, s>>>(d.g_texels, d.n_texels * 3u);
     k_train_zero<<<grid_for(d.n_params, 256, 64), 256, 0, s>>>(d.g_params, d.n_params);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     const uint32_t c = d.dims[d.n_layers];
+    // the scatter's regions: 2 x 2 cells, where a window then still spans at
+    // most 34 texels (level 0 of 1024), else single cells; LDS for the windows
+    // of the largest pyramid, as far as two workgroups share a CU
+    uint32_t side = 0, pool_sums = 0;
+    for (uint32_t t = 0; t < d.n_tex; ++t) side = std::max(side, std::max(d.tex[t].w, d.tex[t].h));
+    const uint32_t region_log2 = side <= 1024 ? 1u : 0u;
+    for (uint32_t t = 0; t < d.n_tex; ++t) {
+        uint32_t sums = 0;
+        for (uint32_t l = d.tex[t].levels; l-- > 0;) {
+            const uint32_t more = 3u * window_side(std::max(d.tex[t].w >> l, 1u), 1u << region_log2) *
+                                  window_side(std::max(d.tex[t].h >> l, 1u), 1u << region_log2);
+            if ((sums + more) * 8u > kScatterPoolMax) break;
+            sums += more;
+        }
+        pool_sums = std::max(pool_sums, sums);
+    }
     for (size_t off = 0; off < n; off += kTrainBinBatch) {
         const uint32_t m = (uint32_t)std::min(n - off, (size_t)kTrainBinBatch);
         const float *q = queries + 3 * off;
@@ -1075,7 +1111,10 @@ hipError_t launch_train_backward(const TrainDesc &d, const float *queries, size_
         k_train_bin_scatter<<<bins, kBinThreads, 0, s>>>(q, m, d.bin_next, d.bin_perm);
         if ((e = hipGetLastError()) != hipSuccess) return e;
         if ((e = dispatch_backward(d, q, m, grad_out + (size_t)c * off, s)) != hipSuccess) return e;
-        k_train_scatter<<<kTrainBins, kScatterThreads, 0, s>>>(d, q);
+        const unsigned threads = m >= (1u << 19) ? kScatterThreads : kScatterThreads / 2;
+        k_train_scatter<<<(kTrainBins >> (2 * region_log2)) * d.n_tex, threads, pool_sums * 8u, s>>>(
+            d, region_log2, pool_sums);
+        if ((e = hipGetLastError()) != hipSuccess) return e;
     }
     const unsigned grid = grid_for((size_t)d.blk_base[d.n_tex] * 16u, kTrainThreads, 16384);
     if (d.ste) k_train_blocks<true><<<grid, kTrainThreads, 0, s>>>(d);

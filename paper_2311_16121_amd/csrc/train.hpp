@@ -39,7 +39,7 @@ struct TrainDesc {
     uint32_t ste;                  // 1: straight-through (exact decode forward)
     uint32_t blk_base[kMaxTextures + 1];   // first block of each pyramid in a joint numbering
     float4 *texels;                // texel values (r, g, b, 0)
-    float4 *g_texels;              // their gradients
+    float *g_texels;               // their gradients, (r, g, b) per texel
     uint32_t n_texels;
     const float *params;           // per layer W[out][in] row-major, then b[out]
     float *g_params;
@@ -54,9 +54,10 @@ struct TrainDesc {
     uint8_t *ops_ws;
     // the backward's sample sort (workspace): sorted sample indices, per-cell
     // counts, per-cell next free slot (after the sort: the end of the cell's
-    // run), and dL/dz (12 floats) per sorted sample
+    // run), and per sorted sample its query (u, v, s, 0) and, per pyramid
+    // (kTrainBinBatch apart), dL/dz (r, g, b, 0)
     uint32_t *bin_perm, *bin_count, *bin_next;
-    float *bin_dz;
+    float4 *bin_q, *bin_dz;
 };
 
 hipError_t launch_train_forward(const TrainDesc &d, const float *queries, size_t n, float *out,

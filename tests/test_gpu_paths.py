@@ -81,3 +81,32 @@ def test_training_backward_over_ragged_groups(bcf, n, dims):
         ref = np.asarray(ref)
         err = np.abs(got.cpu().numpy().reshape(ref.shape) - ref).max()
         assert err <= 2e-4 * max(np.abs(ref).max(), 1e-30)
+
+
+@pytest.mark.parametrize("n,res", [(300, 64), (5000, 1024), (3000, 2048)])
+def test_training_scatter_with_an_infinite_gradient(bcf, n, res):
+    """One sample's infinite dL/dG makes its own texels' gradients non-finite
+    (its region then sums in floats) and leaves every other gradient what it is
+    without that sample, to the rounding of binary32 sums (1e-5 of the largest)."""
+    g = synth.rng(900 + n)
+    levels = res.bit_length()
+    nb = synth.chain_blocks(res, res, levels)
+    dims = (6, 16, 4)
+    geo = bcf.TrainGeometry([res] * 2, [levels] * 2, [dev(g.integers(0, 32, nb).astype(np.uint8))] * 2, dims)
+    ends = [dev(g.uniform(0.0, 31.0, (nb, 4, 3)).astype(np.float32)) for _ in range(2)]
+    idxs = [dev(g.uniform(0.0, 1.0, (nb, 16)).astype(np.float32)) for _ in range(2)]
+    p = dev(synth.mlp_params(dims, g).astype(np.float32))
+    q = synth.uniform_queries(n, g, 2.0)             # fine levels, so that few texels are touched
+    go = g.standard_normal((n, 4)).astype(np.float32)
+    go[7] = 0.0
+    want = bcf.train_backward(geo, ends, idxs, p, dev(q), dev(go))
+    go[7] = np.inf
+    got = bcf.train_backward(geo, ends, idxs, p, dev(q), dev(go))
+    some = 0
+    for a, b in zip(got[0] + got[1], want[0] + want[1]):
+        a, b = a.cpu().numpy(), b.cpu().numpy()
+        ok = np.isfinite(a)
+        some += (~ok).sum()
+        assert np.isfinite(b).all() and ok.mean() > 0.5
+        assert np.abs(a[ok] - b[ok]).max() <= 1e-5 * np.abs(b).max()
+    assert some > 0
