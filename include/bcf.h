@@ -327,7 +327,7 @@ typedef struct {
 } bcf_train_material;
 
 /* Device workspace bytes (256-byte aligned start) for the training calls
- * on this material: 28 bytes per texel (values and gradients), then 20 MiB +
+ * on this material: at most 28 bytes per texel (values and gradients), then 20 MiB +
  * 32 KiB and 16 MiB per pyramid in which the backward sorts its samples by
  * position and keeps dL/d feature per sample (2^20 samples at a time), then
  * the forward's MLP operands in the matrix-core layout (a few KiB). */

@@ -14,7 +14,7 @@
 //                     the region's footprint, then stores inside it and one
 //                     float atomic per touched texel channel at its edges
 //   k_train_blocks    dL/d texel -> dL/d endpoints, dL/d indices (one lane
-//                     per texel, sums over a block's 16 lanes by shuffles)
+//                     per block row, sums over a block's four lanes)
 //
 // A texel of subset sigma blends the endpoint pair (e_{2 sigma}, e_{2 sigma+1})
 // with index x. Continuous mode: y = a ((2^16 e_A + 2^15)/2^6 + x (2^16 (e_B -
@@ -29,6 +29,7 @@
 #include "bc6h_device.hpp"
 #include "frame_kernels.hpp"
 #include "train.hpp"
+#include "unpack_device.hpp"
 
 namespace bcf {
 namespace {
@@ -130,12 +131,6 @@ __device__ __forceinline__ TexelSite texel_site(const TrainDesc &d, uint32_t gb,
     return s;
 }
 
-__device__ __forceinline__ uint32_t subset_of(const TrainTexDesc &tx, uint32_t b, uint32_t t)
-{
-    // partition ids are taken modulo 32
-    return (kTable[kModes * kModeWords + (tx.partitions[b] & 31u)] >> t) & 1u;
-}
-
 // One lane per block row: its four texels (a level narrower than 4 texels
 // keeps the left ones), the block's endpoints and partition read once.
 template <bool STE>
@@ -165,75 +160,241 @@ __global__ void __launch_bounds__(kTrainThreads) k_train_texels(TrainDesc d)
     }
 }
 
-// Sum over the 16 lanes of a DPP row (a block's texels), in every lane of the
-// row: lanes paired by XOR 1, then 2, then the row's two quads of each half,
-// then its two halves -- the order of a shuffle butterfly over XOR 1, 2, 4, 8,
-// with DPP moves instead of LDS permutes.
+// The straight-through texels of pyramids of one geometry, which are halves, to
+// the decode's packed scratch (filter_device.hpp): lane = 4 * block position +
+// pyramid, the block's palette and slots through LDS as in the unpack, so that
+// whole block rows are stored and a footprint row of all pyramids is three
+// 16-byte loads. Pyramids past n_tex leave zeros. ALIGNED: every pyramid's
+// endpoints and indices start 16-byte aligned.
+// Bound by the parameters' reads and the texels' writes (39 and 34 MB at
+// 4 x 1024^2); the float images it replaces took 90 MB and a lane per block row.
+template <bool ALIGNED>
+__global__ void __launch_bounds__(kTrainThreads) k_train_texels_packed(TrainDesc d)
+{
+    __shared__ uint2 palette[16][256];
+    __shared__ uint2 slots[256];
+    const TrainTexDesc &t0 = d.tex[0];
+    // this workgroup's level and chunk of 64 block positions
+    uint32_t l = 0, chunk = blockIdx.x;
+    uint32_t n_blk;
+    for (;; ++l) {
+        n_blk = ((max(t0.w >> l, 1u) + 3u) >> 2) * ((max(t0.h >> l, 1u) + 3u) >> 2);
+        const uint32_t chunks = (n_blk + 63u) >> 6;
+        if (chunk < chunks) break;
+        chunk -= chunks;
+    }
+    const uint32_t pyr = threadIdx.x & 3u, bi = chunk * 64u + (threadIdx.x >> 2);
+    uint32_t pal[16][2];
+    uint32_t s0 = 0, s1 = 0;
+    if (bi < n_blk && pyr < d.n_tex) {
+        const float *ep = pyr == 0 ? d.tex[0].endpoints : pyr == 1 ? d.tex[1].endpoints : pyr == 2 ? d.tex[2].endpoints : d.tex[3].endpoints;
+        const float *xp = pyr == 0 ? d.tex[0].indices : pyr == 1 ? d.tex[1].indices : pyr == 2 ? d.tex[2].indices : d.tex[3].indices;
+        const uint8_t *pp = pyr == 0 ? d.tex[0].partitions : pyr == 1 ? d.tex[1].partitions : pyr == 2 ? d.tex[2].partitions : d.tex[3].partitions;
+        const size_t b = (size_t)t0.blk_off[l] + bi;
+        float e[12], x[16];
+        if (ALIGNED) {
+#pragma unroll
+            for (int k = 0; k < 3; ++k) {
+                const float4 v = reinterpret_cast<const float4 *>(ep + 12u * b)[k];
+                e[4 * k] = v.x, e[4 * k + 1] = v.y, e[4 * k + 2] = v.z, e[4 * k + 3] = v.w;
+            }
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const float4 v = reinterpret_cast<const float4 *>(xp + 16u * b)[k];
+                x[4 * k] = v.x, x[4 * k + 1] = v.y, x[4 * k + 2] = v.z, x[4 * k + 3] = v.w;
+            }
+        } else {
+#pragma unroll
+            for (int k = 0; k < 12; ++k) e[k] = ep[12u * b + k];
+#pragma unroll
+            for (int k = 0; k < 16; ++k) x[k] = xp[16u * b + k];
+        }
+        // the exported block: texel_chan's rounding of endpoints and indices
+        // (fmaxf before fminf maps NaN to 0), one 8-entry palette per subset
+        Bc6hHeader h;
+#pragma unroll
+        for (int sub = 0; sub < 2; ++sub)
+#pragma unroll
+            for (int c = 0; c < 3; ++c) {
+                const float qa = fminf(fmaxf(rintf(e[6 * sub + c]), 0.0f), 63.0f);
+                const float qb = fminf(fmaxf(rintf(e[6 * sub + 3 + c]), 0.0f), 63.0f);
+                const int32_t A = unquantize<false>((int32_t)qa, 6), B = unquantize<false>((int32_t)qb, 6);
+                h.base[sub][c] = 64 * A + 32;
+                h.diff[sub][c] = B - A;
+            }
+        h.ib = 3;
+        h.valid = 1;
+        bc6h_palette<false>(h, pal);
+        const uint32_t mask = kTable[kModes * kModeWords + (pp[b] & 31u)] & 0xFFFFu;   // ids are taken modulo 32
+#pragma unroll
+        for (int t = 0; t < 8; ++t) {
+            s0 |= (uint32_t)fminf(fmaxf(rintf(7.0f * x[t]), 0.0f), 7.0f) << (4 * t);
+            s1 |= (uint32_t)fminf(fmaxf(rintf(7.0f * x[8 + t]), 0.0f), 7.0f) << (4 * t);
+        }
+        s0 |= spread1to4(mask & 0xFFu) << 3;
+        s1 |= spread1to4(mask >> 8) << 3;
+    } else {
+#pragma unroll
+        for (int j = 0; j < 16; ++j) pal[j][0] = pal[j][1] = 0u;
+    }
+#pragma unroll
+    for (int j = 0; j < 16; ++j) palette[j][threadIdx.x] = make_uint2(pal[j][0], pal[j][1]);
+    slots[threadIdx.x] = make_uint2(s0, s1);
+    __syncthreads();
+    store_positions<false>(d.packed + 6 * (size_t)d.pos_off[l], max(t0.w >> l, 1u), max(t0.h >> l, 1u),
+                           chunk * 64u + ((threadIdx.x & ~63u) >> 2), n_blk, palette, slots);
+}
+
+// The continuous texels of pyramids of one geometry, in floats: positions of 48
+// bytes. Lane = 4 * block row + pyramid, so that a quad fills a position and the
+// four stores of a row fill its lines; pyramids past n_tex leave zeros.
+__global__ void __launch_bounds__(kTrainThreads) k_train_texels_floats(TrainDesc d)
+{
+    const uint32_t total = (d.tex[0].n_blocks + 15u) / 16u * 256u;
+    for (uint32_t g = blockIdx.x * blockDim.x + threadIdx.x; g < total; g += gridDim.x * blockDim.x) {
+        // a wave's 16 positions of one block row of 16 blocks (rows outermost,
+        // so that consecutive quads are consecutive blocks)
+        const uint32_t pyr = g & 3u, r = (g >> 6) & 3u, b = (g >> 8) * 16u + ((g >> 2) & 15u);
+        if (b >= d.tex[0].n_blocks) continue;
+        const TexelSite s = texel_site(d, b, 4u * r);          // pyramid 0's site serves all
+        if (!s.valid) continue;
+        uint32_t l = 0;
+        while (l + 1 < d.tex[0].levels && b >= d.tex[0].blk_off[l + 1]) ++l;
+        float w[4][3];
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int c = 0; c < 3; ++c) w[i][c] = 0.0f;
+        if (pyr < d.n_tex) {
+            const float *ep = pyr == 0 ? d.tex[0].endpoints : pyr == 1 ? d.tex[1].endpoints : pyr == 2 ? d.tex[2].endpoints : d.tex[3].endpoints;
+            const float *xp = pyr == 0 ? d.tex[0].indices : pyr == 1 ? d.tex[1].indices : pyr == 2 ? d.tex[2].indices : d.tex[3].indices;
+            const uint8_t *pp = pyr == 0 ? d.tex[0].partitions : pyr == 1 ? d.tex[1].partitions : pyr == 2 ? d.tex[2].partitions : d.tex[3].partitions;
+            const uint32_t pmask = kTable[kModes * kModeWords + (pp[b] & 31u)] >> (4u * r);   // ids are taken modulo 32
+            float e[12];
+#pragma unroll
+            for (int k = 0; k < 12; ++k) e[k] = ep[12u * (size_t)b + k];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const bool sub = (pmask >> i) & 1u;
+                const float x = xp[16u * (size_t)b + 4u * r + i];
+#pragma unroll
+                for (int c = 0; c < 3; ++c) w[i][c] = texel_chan<false>(sub ? e[6 + c] : e[c], sub ? e[9 + c] : e[3 + c], x).w;
+            }
+        }
+        float *row = reinterpret_cast<float *>(d.packed) +
+                     12u * ((size_t)d.pos_off[l] + (size_t)s.y * row_pitch(s.wl)) + 3u * pyr;
+#pragma unroll
+        for (uint32_t i = 0; i < 4; ++i) {
+            if (s.x + i >= s.wl) break;
+#pragma unroll
+            for (int c = 0; c < 3; ++c) row[12u * (s.x + i) + c] = w[i][c];
+        }
+        if (s.x == 0) {                          // position w repeats position 0
+#pragma unroll
+            for (int c = 0; c < 3; ++c) row[12u * s.wl + c] = w[0][c];
+        }
+    }
+}
+
+// Sum over the four lanes of a quad, in each of them. (bound_ctrl lets the move
+// fold into the add; every source lane exists.)
 template <int CTRL>
 __device__ __forceinline__ float dpp_move(float x)
 {
-    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), CTRL, 0xF, 0xF, false));
+    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), CTRL, 0xF, 0xF, true));
 }
 
-__device__ __forceinline__ float row16_sum(float v)
+__device__ __forceinline__ float quad_sum(float v)
 {
     v += dpp_move<0xB1>(v);       // quad_perm [1, 0, 3, 2]
-    v += dpp_move<0x4E>(v);       // quad_perm [2, 3, 0, 1]
-    v += dpp_move<0x141>(v);      // row_half_mirror: lane i of a half row takes lane 7 - i
-    v += dpp_move<0x140>(v);      // row_mirror: lane i takes lane 15 - i
-    return v;
+    return v + dpp_move<0x4E>(v);   // quad_perm [2, 3, 0, 1]
 }
 
-template <bool STE>
+// dL/d texel -> dL/d endpoints and indices: one lane per block row, a block's
+// four rows in a quad. ALIGNED: the parameters and their gradients start
+// 16-byte aligned (the texel gradients' rows of four always do), so a lane's
+// four indices and their gradients are one access each.
+// Bound by VALU instructions (rounding, slopes and the sums) over 145 MB at
+// 4 x 1024^2; one lane per texel (endpoints rounded 16 times a block, twelve
+// 16-lane sums a texel) took 66 us.
+template <bool STE, bool ALIGNED>
 __global__ void __launch_bounds__(kTrainThreads) k_train_blocks(TrainDesc d)
 {
-    // every 16-lane group is one block: total is a multiple of 16, so a group's
-    // lanes enter and leave the loop together
-    const uint32_t total = d.blk_base[d.n_tex] * 16u;
+    // total is a multiple of 4: a quad enters and leaves the loop together
+    const uint32_t total = d.blk_base[d.n_tex] * 4u;
     for (uint32_t g = blockIdx.x * blockDim.x + threadIdx.x; g < total; g += gridDim.x * blockDim.x) {
-        const uint32_t t = g & 15u;
-        const TexelSite s = texel_site(d, g >> 4, t);
+        const uint32_t r = g & 3u;
+        const TexelSite s = texel_site(d, g >> 2, 4u * r);
         const TrainTexDesc &tx = d.tex[s.ti];
-        const uint32_t sub = subset_of(tx, s.b, t);
-        const float *e = tx.endpoints + 12u * s.b;
-        float gx = 0.0f;
-        float ge[2][3] = {{0.0f, 0.0f, 0.0f}, {0.0f, 0.0f, 0.0f}};   // this texel's pair A, B
-        if (s.valid) {
-            const float *gt = d.g_texels + 3u * s.tex;
-            const float gc[3] = {gt[0], gt[1], gt[2]};
-            const float x = tx.indices[16u * s.b + t];
+        // partition ids are taken modulo 32
+        const uint32_t pmask = kTable[kModes * kModeWords + (tx.partitions[s.b] & 31u)] >> (4u * r);
+        const float *ep = tx.endpoints + 12u * s.b, *xp = tx.indices + 16u * s.b + 4u * r;
+        float e[12], x[4], gt[12];
+        if (ALIGNED) {
 #pragma unroll
-            for (int c = 0; c < 3; ++c) {
-                const TexelChan r = texel_chan<STE>(e[6u * sub + c], e[6u * sub + 3u + c], x);
-                const float gy = gc[c] * r.slope;
-                gx = fmaf(gy, r.dy_dx, gx);
-                ge[0][c] = gy * r.dy_da;
-                ge[1][c] = gy * r.dy_db;
+            for (int k = 0; k < 3; ++k) {
+                const float4 v = reinterpret_cast<const float4 *>(ep)[k];
+                e[4 * k] = v.x, e[4 * k + 1] = v.y, e[4 * k + 2] = v.z, e[4 * k + 3] = v.w;
             }
-        }
-        tx.g_indices[16u * s.b + t] = gx;
-        // sum over the block's texels, per subset
-        float sum[4][3];
+            const float4 v = *reinterpret_cast<const float4 *>(xp);
+            x[0] = v.x, x[1] = v.y, x[2] = v.z, x[3] = v.w;
+        } else {
 #pragma unroll
-        for (int c = 0; c < 3; ++c) {
-            sum[0][c] = sub ? 0.0f : ge[0][c];
-            sum[1][c] = sub ? 0.0f : ge[1][c];
-            sum[2][c] = sub ? ge[0][c] : 0.0f;
-            sum[3][c] = sub ? ge[1][c] : 0.0f;
+            for (int k = 0; k < 12; ++k) e[k] = ep[k];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) x[k] = xp[k];
         }
+        // texels that a level below 4x4 does not have: zero gradients
+        const float *gp = d.g_texels + 3u * s.tex;
+        if (s.valid && s.wl >= 4u) {
+#pragma unroll
+            for (int k = 0; k < 3; ++k) {
+                const float4 v = reinterpret_cast<const float4 *>(gp)[k];
+                gt[4 * k] = v.x, gt[4 * k + 1] = v.y, gt[4 * k + 2] = v.z, gt[4 * k + 3] = v.w;
+            }
+        } else {
+#pragma unroll
+            for (int k = 0; k < 12; ++k) gt[k] = s.valid && (uint32_t)k < 3u * s.wl ? gp[k] : 0.0f;
+        }
+        float sum[4][3], gx[4];
 #pragma unroll
         for (int j = 0; j < 4; ++j)
 #pragma unroll
-            for (int c = 0; c < 3; ++c)
-                sum[j][c] = row16_sum(sum[j][c]);
-        if (t < 12) {
-            float v = 0.0f;
+            for (int c = 0; c < 3; ++c) sum[j][c] = 0.0f;
 #pragma unroll
-            for (int j = 0; j < 4; ++j)
+        for (int i = 0; i < 4; ++i) {
+            const bool sub = (pmask >> i) & 1u;
+            gx[i] = 0.0f;
 #pragma unroll
-                for (int c = 0; c < 3; ++c) v = (3 * j + c == (int)t) ? sum[j][c] : v;
-            tx.g_endpoints[12u * s.b + t] = v;
+            for (int c = 0; c < 3; ++c) {
+                const TexelChan t = texel_chan<STE>(sub ? e[6 + c] : e[c], sub ? e[9 + c] : e[3 + c], x[i]);
+                const float gy = gt[3 * i + c] * t.slope;
+                gx[i] = fmaf(gy, t.dy_dx, gx[i]);
+                const float ga = gy * t.dy_da, gb = gy * t.dy_db;
+                sum[0][c] += sub ? 0.0f : ga;
+                sum[1][c] += sub ? 0.0f : gb;
+                sum[2][c] += sub ? ga : 0.0f;
+                sum[3][c] += sub ? gb : 0.0f;
+            }
         }
+        float *xo = tx.g_indices + 16u * s.b + 4u * r;
+        if (ALIGNED) {
+            *reinterpret_cast<float4 *>(xo) = make_float4(gx[0], gx[1], gx[2], gx[3]);
+        } else {
+#pragma unroll
+            for (int k = 0; k < 4; ++k) xo[k] = gx[k];
+        }
+        // the quad's lane r writes endpoint r
+        float out[3] = {0.0f, 0.0f, 0.0f};
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+#pragma unroll
+            for (int c = 0; c < 3; ++c) {
+                const float v = quad_sum(sum[j][c]);
+                out[c] = (int)r == j ? v : out[c];
+            }
+#pragma unroll
+        for (int c = 0; c < 3; ++c) tx.g_endpoints[12u * s.b + 3u * r + c] = out[c];
     }
 }
 
@@ -241,7 +402,8 @@ __global__ void __launch_bounds__(kTrainThreads) k_train_blocks(TrainDesc d)
 // queries
 
 // Per pyramid and level, for the query kernels' LDS: x = level width,
-// y = level height, z = first texel of the level in the images. A level picked
+// y = level height, z = first texel of the level in the images, w = first
+// position of the level in the packed scratch. A level picked
 // per query indexes it; indexing the descriptor's arrays instead makes the
 // compiler hold every level's values in registers across the query loop.
 typedef uint4 TrainLevelLut[kMaxTextures][kMaxLevels];
@@ -252,7 +414,7 @@ __device__ __forceinline__ void load_level_lut(const TrainDesc &d, TrainLevelLut
     for (uint32_t e = threadIdx.x; e < (uint32_t)(kMaxTextures * kMaxLevels); e += blockDim.x) {
         const uint32_t ti = e / kMaxLevels, l = e % kMaxLevels;
         const TrainTexDesc &tx = d.tex[ti < d.n_tex ? ti : 0u];
-        lut[ti][l] = l < tx.levels ? make_uint4(max(tx.w >> l, 1u), max(tx.h >> l, 1u), tx.tex_off[l], 0u)
+        lut[ti][l] = l < tx.levels ? make_uint4(max(tx.w >> l, 1u), max(tx.h >> l, 1u), tx.tex_off[l], d.pos_off[l])
                                    : make_uint4(1u, 1u, 0u, 0u);
     }
 }
@@ -317,21 +479,68 @@ __device__ __forceinline__ void taps(const TrainDesc &d, const TrainLevelLut &lu
     }
 }
 
+// z of a query: the filtered pyramids, from their images (PACK 0) or from the
+// packed positions of pyramids of one geometry, halves (1) or floats (2): the
+// same sums in the same order; pyramids past n_tex hold zeros.
+template <int PACK>
 __device__ __forceinline__ void features(const TrainDesc &d, const TrainLevelLut &lut, float u, float v, float s,
                                          float z[12])
 {
-    uint32_t idx[32];
-    float wt[32];
-    taps(d, lut, u, v, s, idx, wt);
+    if constexpr (PACK != 0) {
+        constexpr uint32_t kUnit = PACK == 1 ? 24u : 48u;            // bytes a position
+        constexpr int kLoads = 2 * (int)kUnit / 16;                  // of 16 bytes, per footprint row
+        const float uf = u - floorf(u), vf = v - floorf(v);          // wrap addressing
+        const uint32_t levels = d.tex[0].levels;
+        const float si = fminf(fmaxf(s + d.tex[0].bias, 0.0f), (float)(levels - 1));   // NaN -> 0
+        const uint32_t l0 = (uint32_t)floorf(si);
+        const float lam = si - (float)l0;
+        const __amdgpu_buffer_rsrc_t rs = make_rsrc(d.packed, d.packed_bytes);
+        texel_pair q[2][2][kLoads];
+        LevelTaps lt[2];
 #pragma unroll
-    for (int i = 0; i < 12; ++i) z[i] = 0.0f;
+        for (int k = 0; k < 2; ++k) {
+            const uint4 e = lut[0][k ? min(l0 + 1u, levels - 1u) : l0];
+            lt[k] = level_taps(e, uf, vf, k ? lam : 1.0f - lam);
+            // columns xa and xa + 1 (column w repeats column 0)
+            const uint32_t pitch = row_pitch(e.x);
+            const uint32_t o[2] = {kUnit * (e.w + lt[k].ya * pitch + lt[k].xa),
+                                   kUnit * (e.w + lt[k].yb * pitch + lt[k].xa)};
 #pragma unroll
-    for (int k = 0; k < 32; ++k) {
-        const float4 tv = d.texels[idx[k]];
-        const int t = k / 8;
-        z[3 * t + 0] = fmaf(wt[k], tv.x, z[3 * t + 0]);
-        z[3 * t + 1] = fmaf(wt[k], tv.y, z[3 * t + 1]);
-        z[3 * t + 2] = fmaf(wt[k], tv.z, z[3 * t + 2]);
+            for (int r = 0; r < 2; ++r)
+#pragma unroll
+                for (int j = 0; j < kLoads; ++j)
+                    q[k][r][j] = __builtin_amdgcn_raw_buffer_load_b128(rs, (int)(o[r] + 16u * j), 0, 0);
+        }
+#pragma unroll
+        for (int i = 0; i < 12; ++i) z[i] = 0.0f;
+#pragma unroll
+        for (int k = 0; k < 2; ++k)
+#pragma unroll
+            for (int i = 0; i < 12; ++i) {       // i = 3 t + c: values i (xa) and 12 + i (xa + 1)
+                auto value = [&](int row, int j) -> float {
+                    if constexpr (PACK == 1) return packed_half(q[k][row], j);
+                    const uint32_t bits = q[k][row][j >> 2][j & 3];
+                    return __uint_as_float(bits);
+                };
+                z[i] = fmaf(lt[k].w[0], value(0, i), z[i]);
+                z[i] = fmaf(lt[k].w[1], value(0, 12 + i), z[i]);
+                z[i] = fmaf(lt[k].w[2], value(1, i), z[i]);
+                z[i] = fmaf(lt[k].w[3], value(1, 12 + i), z[i]);
+            }
+    } else {
+        uint32_t idx[32];
+        float wt[32];
+        taps(d, lut, u, v, s, idx, wt);
+#pragma unroll
+        for (int i = 0; i < 12; ++i) z[i] = 0.0f;
+#pragma unroll
+        for (int k = 0; k < 32; ++k) {
+            const float4 tv = d.texels[idx[k]];
+            const int t = k / 8;
+            z[3 * t + 0] = fmaf(wt[k], tv.x, z[3 * t + 0]);
+            z[3 * t + 1] = fmaf(wt[k], tv.y, z[3 * t + 1]);
+            z[3 * t + 2] = fmaf(wt[k], tv.z, z[3 * t + 2]);
+        }
     }
 }
 
@@ -341,8 +550,20 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 // decode kernels' operand layout, prepared from the parameters per call): a
 // wave's 64 queries' features pass through LDS into the MFMA B layout, the
 // outputs come back through LDS to each query's lane.
-template <int H, int NH>
-__global__ void __launch_bounds__(kTrainThreads) k_train_forward_mfma(TrainDesc d, const float *queries, uint32_t n,
+// Waves per SIMD the forward's registers are laid out for (the filter's loads
+// in flight against the waves beside it; 0: the compiler's choice). Measured,
+// 2^20 samples, default -> chosen: halves 12-32-32-10 82 -> 65 us and
+// 12-32-32-32-10 76 (4: 98); floats 130 -> 96 and 100 (3: 111); images of four
+// sizes 98 (3: 123) and 157 -> 129.
+constexpr int forward_waves(int NH, int PACK)
+{
+    return PACK == 1 ? (NH < 3 ? 4 : 0) : PACK == 2 ? (NH < 3 ? 3 : 0) : NH < 3 ? 0 : 3;
+}
+
+template <int H, int NH, int PACK>
+__global__ void __attribute__((amdgpu_waves_per_eu(forward_waves(NH, PACK) ? forward_waves(NH, PACK) : 1,
+                                                   forward_waves(NH, PACK) ? forward_waves(NH, PACK) : 8)))
+__launch_bounds__(kTrainThreads) k_train_forward_mfma(TrainDesc d, const float *queries, uint32_t n,
                                                                       float *out)
 {
     constexpr int kWaves = kTrainThreads / 64;
@@ -357,15 +578,23 @@ __global__ void __launch_bounds__(kTrainThreads) k_train_forward_mfma(TrainDesc 
     float *st = reinterpret_cast<float *>(&stage[wv][0]);
     float4_t (*feats)[4] = reinterpret_cast<float4_t (*)[4]>(&stage[wv][0]);
     const uint32_t n_chunks = (n + 63u) / 64u;
+    const bool wide = ((uintptr_t)out & 15u) == 0;
     for (uint32_t ch = blockIdx.x * kWaves + wv; ch < n_chunks; ch += gridDim.x * kWaves) {
         const uint32_t q = ch * 64u + lane;
         const bool live = q < n;
         float z[12];
-        features(d, lut, live ? queries[3u * q] : 0.0f, live ? queries[3u * q + 1u] : 0.0f,
+        features<PACK>(d, lut, live ? queries[3u * q] : 0.0f, live ? queries[3u * q + 1u] : 0.0f,
                  live ? queries[3u * q + 2u] : 0.0f, z);
         mlp_stage<MLP_MFMA_F32, H, NH>(z, mlp, feats, st, c, lane);
-        if (live)
-            for (uint32_t j = 0; j < c; ++j) out[(size_t)q * c + j] = st[lane * c + j];
+        // the chunk's rows are contiguous: 16-byte stores where they may be
+        const uint32_t floats = min(64u, n - ch * 64u) * c;
+        float *dst = out + (size_t)ch * 64u * c;
+        if (wide && floats == 64u * c) {
+            for (uint32_t k = lane; k < 16u * c; k += 64u)
+                reinterpret_cast<float4_t *>(dst)[k] = reinterpret_cast<const float4_t *>(st)[k];
+        } else {
+            for (uint32_t k = lane; k < floats; k += 64u) dst[k] = st[k];
+        }
         wave_lds_sync();                              // the stage is rewritten by the next chunk
     }
 }
@@ -379,11 +608,13 @@ __global__ void __launch_bounds__(kTrainThreads) k_train_forward_mfma(TrainDesc 
 // gradient lines update them while the lines sit in one L2.
 
 constexpr int kBinThreads = 1024;
-// samples a thread of the count and placement kernels takes: a workgroup's
-// histogram then covers 16K samples, so that fewer cells of it reach memory
-// (one atomic per touched cell and workgroup)
-constexpr int kBinPerThread = 16;
-constexpr uint32_t kBinPerGroup = kBinThreads * kBinPerThread;
+// Samples a thread of the count and placement kernels takes. Eight from 3 * 2^17
+// samples on: a workgroup's histogram covers 8K of them, so that fewer cells of
+// it reach memory (one atomic per touched cell and workgroup). Below, one: the
+// workgroups would be too few. (2^20 samples, count + placement: 24 + 35 us with
+// one, 10 + 17 with eight, 14 + 21 with sixteen; 2^18: 3 + 4, 6 + 7, 10 + 10.)
+constexpr uint32_t kBinMany = 3u << 17;
+constexpr uint32_t bin_per_thread(uint32_t n) { return n >= kBinMany ? 8u : 1u; }
 
 // A query's cell: its wrapped (u, v) on the kTrainBinSide grid (NaN and
 // infinities land in cell 0), numbered along a Z-order curve.
@@ -399,16 +630,17 @@ __device__ __forceinline__ uint32_t bin_of(float u, float v)
     return z;
 }
 
-// count[cell] += samples of the cell; kBinPerGroup samples per workgroup
-// (sample blockIdx * kBinPerGroup + k * kBinThreads + threadIdx), a histogram in LDS
+// count[cell] += samples of the cell; PER * kBinThreads samples per workgroup
+// (sample (blockIdx * PER + k) * kBinThreads + threadIdx), a histogram in LDS
+template <uint32_t PER>
 __global__ void __launch_bounds__(kBinThreads) k_train_bin_count(const float *queries, uint32_t n, uint32_t *count)
 {
     __shared__ uint32_t hist[kTrainBins];
     for (uint32_t b = threadIdx.x; b < kTrainBins; b += kBinThreads) hist[b] = 0u;
     __syncthreads();
-#pragma unroll 4
-    for (uint32_t k = 0; k < (uint32_t)kBinPerThread; ++k) {
-        const uint32_t i = blockIdx.x * kBinPerGroup + k * kBinThreads + threadIdx.x;
+#pragma unroll
+    for (uint32_t k = 0; k < PER; ++k) {
+        const uint32_t i = (blockIdx.x * PER + k) * kBinThreads + threadIdx.x;
         if (i < n) atomicAdd(&hist[bin_of(queries[3u * i], queries[3u * i + 1u])], 1u);
     }
     __syncthreads();
@@ -446,19 +678,20 @@ __global__ void __launch_bounds__(kBinThreads) k_train_bin_scan(const uint32_t *
     }
 }
 
-// perm[next[cell]++] = sample: each workgroup ranks its kBinPerGroup samples
-// (as k_train_bin_count takes them) per cell in LDS, then reserves one run per
+// perm[next[cell]++] = sample: each workgroup ranks its samples (as
+// k_train_bin_count takes them) per cell in LDS, then reserves one run per
 // cell it holds
+template <uint32_t PER>
 __global__ void __launch_bounds__(kBinThreads) k_train_bin_scatter(const float *queries, uint32_t n, uint32_t *next,
                                                                    uint32_t *perm)
 {
     __shared__ uint32_t hist[kTrainBins];
     for (uint32_t b = threadIdx.x; b < kTrainBins; b += kBinThreads) hist[b] = 0u;
     __syncthreads();
-    uint32_t bin[kBinPerThread], rank[kBinPerThread];
+    uint32_t bin[PER], rank[PER];
 #pragma unroll
-    for (uint32_t k = 0; k < (uint32_t)kBinPerThread; ++k) {
-        const uint32_t i = blockIdx.x * kBinPerGroup + k * kBinThreads + threadIdx.x;
+    for (uint32_t k = 0; k < PER; ++k) {
+        const uint32_t i = (blockIdx.x * PER + k) * kBinThreads + threadIdx.x;
         bin[k] = i < n ? bin_of(queries[3u * i], queries[3u * i + 1u]) : 0u;
         rank[k] = i < n ? atomicAdd(&hist[bin[k]], 1u) : 0u;
     }
@@ -467,8 +700,8 @@ __global__ void __launch_bounds__(kBinThreads) k_train_bin_scatter(const float *
         if (hist[b]) hist[b] = atomicAdd(&next[b], hist[b]);
     __syncthreads();
 #pragma unroll
-    for (uint32_t k = 0; k < (uint32_t)kBinPerThread; ++k) {
-        const uint32_t i = blockIdx.x * kBinPerGroup + k * kBinThreads + threadIdx.x;
+    for (uint32_t k = 0; k < PER; ++k) {
+        const uint32_t i = (blockIdx.x * PER + k) * kBinThreads + threadIdx.x;
         if (i < n) perm[hist[bin[k]] + rank[k]] = i;
     }
 }
@@ -650,7 +883,7 @@ __device__ __forceinline__ void flush(const LayerGrad<MT, NT> &gr, float *red, f
     }
 }
 
-template <int H, int NH>
+template <int H, int NH, int PACK>
 __global__ void __launch_bounds__(64 * kBwdWaves, 2) k_train_backward(TrainDesc d, const float *queries, uint32_t n,
                                                                       const float *grad_out, const uint32_t *perm)
 {
@@ -693,7 +926,7 @@ __global__ void __launch_bounds__(64 * kBwdWaves, 2) k_train_backward(TrainDesc 
 #pragma unroll
         for (int j = 0; j < kMaxOut; ++j) go[j] = live && (uint32_t)j < c ? grad_out[(size_t)q * c + j] : 0.0f;
         float z[12];
-        features(d, lut, u, v, s, z);
+        features<PACK>(d, lut, u, v, s, z);
 #pragma unroll
         for (int k = 0; k < 3; ++k)
             *reinterpret_cast<f32x4 *>(&w.z[lane][4 * k]) = (f32x4){z[4 * k], z[4 * k + 1], z[4 * k + 2], z[4 * k + 3]};
@@ -1017,6 +1250,22 @@ unsigned grid_for(size_t work, unsigned per_block, unsigned cap)
 
 hipError_t launch_texels(const TrainDesc &d, hipStream_t s)
 {
+    if (d.packed && !d.ste) {
+        const unsigned grid = grid_for(((size_t)d.tex[0].n_blocks + 15u) / 16u * 256u, kTrainThreads, 16384);
+        k_train_texels_floats<<<grid, kTrainThreads, 0, s>>>(d);
+        return hipGetLastError();
+    }
+    if (d.packed) {
+        unsigned chunks = 0;
+        bool al = true;
+        for (uint32_t l = 0; l < d.tex[0].levels; ++l)
+            chunks += (((std::max(d.tex[0].w >> l, 1u) + 3u) / 4u) * ((std::max(d.tex[0].h >> l, 1u) + 3u) / 4u) + 63u) / 64u;
+        for (uint32_t t = 0; t < d.n_tex; ++t)
+            al = al && ((uintptr_t)d.tex[t].endpoints & 15u) == 0 && ((uintptr_t)d.tex[t].indices & 15u) == 0;
+        if (al) k_train_texels_packed<true><<<chunks, kTrainThreads, 0, s>>>(d);
+        else k_train_texels_packed<false><<<chunks, kTrainThreads, 0, s>>>(d);
+        return hipGetLastError();
+    }
     const unsigned grid = grid_for((size_t)d.blk_base[d.n_tex] * 4u, kTrainThreads, 16384);
     if (d.ste) k_train_texels<true><<<grid, kTrainThreads, 0, s>>>(d);
     else k_train_texels<false><<<grid, kTrainThreads, 0, s>>>(d);
@@ -1028,7 +1277,10 @@ hipError_t forward_hn(const TrainDesc &d, const float *queries, uint32_t n, floa
 {
     hipError_t e = launch_prepare_weights(d.params, nullptr, d.ops_shape, MLP_MFMA_F32, d.ops, d.ops_ws, nullptr, s);
     if (e != hipSuccess) return e;
-    k_train_forward_mfma<H, NH><<<grid_for(n, kTrainThreads, 8192), kTrainThreads, 0, s>>>(d, queries, n, out);
+    const unsigned grid = grid_for(n, kTrainThreads, 8192);
+    auto *forward = !d.packed ? k_train_forward_mfma<H, NH, 0>
+                  : d.ste ? k_train_forward_mfma<H, NH, 1> : k_train_forward_mfma<H, NH, 2>;
+    forward<<<grid, kTrainThreads, 0, s>>>(d, queries, n, out);
     return hipGetLastError();
 }
 
@@ -1037,7 +1289,9 @@ hipError_t backward_hn(const TrainDesc &d, const float *queries, uint32_t n, con
 {
     // the workgroups resident at once (two per CU), a multiple of the 8 XCDs
     const unsigned grid = (grid_for((n + 63u) / 64u, kBwdWaves, 512) + 7u) & ~7u;
-    k_train_backward<H, NH><<<grid, 64 * kBwdWaves, 0, s>>>(d, queries, n, grad_out, d.bin_perm);
+    auto *backward = !d.packed ? k_train_backward<H, NH, 0>
+                   : d.ste ? k_train_backward<H, NH, 1> : k_train_backward<H, NH, 2>;
+    backward<<<grid, 64 * kBwdWaves, 0, s>>>(d, queries, n, grad_out, d.bin_perm);
     return hipGetLastError();
 }
 
@@ -1103,12 +1357,15 @@ hipError_t launch_train_backward(const TrainDesc &d, const float *queries, size_
     for (size_t off = 0; off < n; off += kTrainBinBatch) {
         const uint32_t m = (uint32_t)std::min(n - off, (size_t)kTrainBinBatch);
         const float *q = queries + 3 * off;
-        const unsigned bins = (m + kBinPerGroup - 1) / kBinPerGroup;
+        const uint32_t per = bin_per_thread(m);
+        const unsigned bins = (m + per * kBinThreads - 1) / (per * kBinThreads);
         // (the counts are cleared as floats: 0.0f is all zero bits)
         k_train_zero<<<8, 256, 0, s>>>(reinterpret_cast<float *>(d.bin_count), kTrainBins);
-        k_train_bin_count<<<bins, kBinThreads, 0, s>>>(q, m, d.bin_count);
+        if (per == 1) k_train_bin_count<1><<<bins, kBinThreads, 0, s>>>(q, m, d.bin_count);
+        else k_train_bin_count<8><<<bins, kBinThreads, 0, s>>>(q, m, d.bin_count);
         k_train_bin_scan<<<1, kBinThreads, 0, s>>>(d.bin_count, d.bin_next);
-        k_train_bin_scatter<<<bins, kBinThreads, 0, s>>>(q, m, d.bin_next, d.bin_perm);
+        if (per == 1) k_train_bin_scatter<1><<<bins, kBinThreads, 0, s>>>(q, m, d.bin_next, d.bin_perm);
+        else k_train_bin_scatter<8><<<bins, kBinThreads, 0, s>>>(q, m, d.bin_next, d.bin_perm);
         if ((e = hipGetLastError()) != hipSuccess) return e;
         if ((e = dispatch_backward(d, q, m, grad_out + (size_t)c * off, s)) != hipSuccess) return e;
         const unsigned threads = m >= (1u << 19) ? kScatterThreads : kScatterThreads / 2;
@@ -1116,9 +1373,13 @@ hipError_t launch_train_backward(const TrainDesc &d, const float *queries, size_
             d, region_log2, pool_sums);
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }
-    const unsigned grid = grid_for((size_t)d.blk_base[d.n_tex] * 16u, kTrainThreads, 16384);
-    if (d.ste) k_train_blocks<true><<<grid, kTrainThreads, 0, s>>>(d);
-    else k_train_blocks<false><<<grid, kTrainThreads, 0, s>>>(d);
+    const unsigned grid = grid_for((size_t)d.blk_base[d.n_tex] * 4u, kTrainThreads, 16384);
+    uintptr_t bits = 0;
+    for (uint32_t t = 0; t < d.n_tex; ++t)
+        bits |= (uintptr_t)d.tex[t].endpoints | (uintptr_t)d.tex[t].indices | (uintptr_t)d.tex[t].g_indices;
+    auto *blocks = (bits & 15u) == 0 ? (d.ste ? k_train_blocks<true, true> : k_train_blocks<false, true>)
+                                     : (d.ste ? k_train_blocks<true, false> : k_train_blocks<false, false>);
+    blocks<<<grid, kTrainThreads, 0, s>>>(d);
     return hipGetLastError();
 }
 

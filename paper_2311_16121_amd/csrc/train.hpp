@@ -38,7 +38,14 @@ struct TrainDesc {
     uint32_t n_tex;
     uint32_t ste;                  // 1: straight-through (exact decode forward)
     uint32_t blk_base[kMaxTextures + 1];   // first block of each pyramid in a joint numbering
-    float4 *texels;                // texel values (r, g, b, 0)
+    float4 *texels;                // texel values (r, g, b, 0), one image per pyramid and level
+    // or, for pyramids of one geometry (packed_bytes > 0), packed positions, rows
+    // of w + 2 whose position w repeats position 0: the decode's 24 bytes of
+    // halves (straight-through texels are halves) or 48 bytes of floats;
+    // pos_off = each level's first position (packed != NULL once bound)
+    uint32_t *packed;
+    uint32_t packed_bytes;
+    uint32_t pos_off[kMaxLevels];
     float *g_texels;               // their gradients, (r, g, b) per texel
     uint32_t n_texels;
     const float *params;           // per layer W[out][in] row-major, then b[out]

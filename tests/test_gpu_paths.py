@@ -110,3 +110,42 @@ def test_training_scatter_with_an_infinite_gradient(bcf, n, res):
         assert np.isfinite(b).all() and ok.mean() > 0.5
         assert np.abs(a[ok] - b[ok]).max() <= 1e-5 * np.abs(b).max()
     assert some > 0
+
+
+@pytest.mark.parametrize("sizes,levels", [([(64, 64)] * 4, 7), ([(32, 64)] * 3, 7), ([(4, 4)] * 3, 3), ([(1, 8)] * 4, 4),
+                                          ([(2, 2)] * 4, 2)])
+@pytest.mark.parametrize("shift,straight", [(0, True), (1, True), (1, False)])
+def test_training_packed_texels_equal_the_images(bcf, sizes, levels, shift, straight):
+    """Pyramids of one geometry go through packed positions: the same outputs,
+    bit for bit, as from float images (which a pyramid with another bias
+    forces). Parameters 16-byte aligned and not (shift)."""
+    g = synth.rng(950)
+    dims = (12, 16, 16, 5) if len(sizes) == 4 else (9, 16, 16, 5)
+    nb = [synth.chain_blocks(w, h, levels) for w, h in sizes]
+
+    def moved(x):
+        flat = torch.zeros(x.size + shift, device="cuda")
+        flat[shift:] = dev(x.reshape(-1))
+        return flat[shift:].view(x.shape)
+
+    ends = [moved(g.uniform(-1.0, 64.0, (n, 4, 3)).astype(np.float32)) for n in nb]
+    idxs = [moved(g.uniform(-0.1, 1.1, (n, 16)).astype(np.float32)) for n in nb]
+    parts = [dev(g.integers(0, 256, n).astype(np.uint8)) for n in nb]
+    p = dev(synth.mlp_params(dims, g).astype(np.float32))
+    q = synth.uniform_queries(1000, g, float(levels))
+    q[:, :2] = q[:, :2] * 3.0 - 1.0
+    q[:, 2] -= 0.5
+    go = dev(g.standard_normal((len(q), 5)).astype(np.float32))
+
+    def geometry(bias):
+        return bcf.TrainGeometry(sizes, [levels] * len(sizes), parts, dims, bias, straight_through=straight)
+
+    # a bias that rounds away (|s| + 1e-30) makes the geometries differ
+    one, other = geometry([0.0] * len(sizes)), geometry([0.0] * (len(sizes) - 1) + [1e-30])
+    assert torch.equal(bcf.train_forward(one, ends, idxs, p, dev(q)), bcf.train_forward(other, ends, idxs, p, dev(q)))
+    # one sample at a time: no sum has an order to differ in
+    for k in range(0, 1000, 125):
+        (ge, gi, gp), (re, ri, rp) = (bcf.train_backward(geo, ends, idxs, p, dev(q[k:k + 1]), go[k:k + 1])
+                                      for geo in (one, other))
+        for a, b in list(zip(ge, re)) + list(zip(gi, ri)) + [(gp, rp)]:
+            assert torch.equal(a, b)
