@@ -31,32 +31,53 @@ __device__ __forceinline__ void load_table(uint32_t *lds)
 // ---------------------------------------------------------------------------
 // blocks -> halves
 
+// One lane per block unpacks its palette and slots into LDS; then the lanes
+// take the workgroup's output, 96 contiguous bytes a block, in 16-byte chunks
+// in turn: chunk 3 h + p of a block holds halves 8 p .. 8 p + 7 of its texels
+// 8 h .. 8 h + 7. The palette's rows are padded so that the chunks of one block
+// read different banks.
+// Bound by the header's VALU work and 112 bytes a block; with every lane
+// blending all 48 halves and storing its own 96 bytes: 36 us for 1,000,003
+// blocks.
 template <bool SIGNED>
 __global__ void __launch_bounds__(256) k_decode_blocks(const uint4 *__restrict__ blocks, size_t n,
                                                        uint16_t *__restrict__ out)
 {
     __shared__ uint32_t table[kTableWords];
+    __shared__ uint2 palette[16][257];
+    __shared__ uint2 slots[256];
     load_table(table);
-    const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    const uint4 b = blocks[i];
-    Bc6hHeader h;
-    bc6h_header<SIGNED>(b.x, b.y, b.z, b.w, table, h);
-    uint32_t packed[24];
+    const size_t first = (size_t)blockIdx.x * 256;
+    const uint32_t nb = (uint32_t)min((size_t)256, n - first);
+    if (threadIdx.x < nb) {
+        const uint4 b = blocks[first + threadIdx.x];
+        Bc6hHeader h;
+        bc6h_header<SIGNED>(b.x, b.y, b.z, b.w, table, h);
+        uint32_t pal[16][2];
+        bc6h_palette<SIGNED>(h, pal);
 #pragma unroll
-    for (int t = 0; t < 16; ++t) {
-#pragma unroll
-        for (int c = 0; c < 3; ++c) {
-            const int k = 3 * t + c;
-            const uint32_t v = bc6h_texel<SIGNED>(h, (uint32_t)t, c);
-            if (k & 1) packed[k >> 1] |= v << 16;
-            else packed[k >> 1] = v;
-        }
+        for (int j = 0; j < 16; ++j) palette[j][threadIdx.x] = make_uint2(pal[j][0], pal[j][1]);
+        uint32_t s0, s1;
+        bc6h_slots(h, s0, s1);
+        slots[threadIdx.x] = make_uint2(s0, s1);
     }
-    uint4 *dst = reinterpret_cast<uint4 *>(out + 48 * i);
+    __syncthreads();
+    uint4 *dst = reinterpret_cast<uint4 *>(out + 48 * first);
+    for (uint32_t k = threadIdx.x; k < 6u * nb; k += 256) {
+        const uint32_t blk = k / 6u, c = k - 6u * blk, p = c % 3u;
+        // texels 8 h + 2 p .. 8 h + 2 p + 3: their 12 halves hold the chunk's
+        // eight from half 2 p on
+        const uint2 sl = slots[blk];
+        const uint32_t w = c < 3u ? sl.x : sl.y, t0 = 2u * p;
+        uint2 e[4];
 #pragma unroll
-    for (int j = 0; j < 6; ++j)
-        dst[j] = make_uint4(packed[4 * j], packed[4 * j + 1], packed[4 * j + 2], packed[4 * j + 3]);
+        for (int i = 0; i < 4; ++i) e[i] = palette[(w >> (4u * (t0 + i))) & 15u][blk];
+        // the four texels' 12 halves as six words, shifted by 0, 2 or 4 halves
+        const uint32_t h[6] = {e[0].x, pack_lo_hi(e[0].y, e[1].x), pack_lo_hi(e[1].x >> 16, e[1].y),
+                               e[2].x, pack_lo_hi(e[2].y, e[3].x), pack_lo_hi(e[3].x >> 16, e[3].y)};
+        dst[k] = p == 0u ? make_uint4(h[0], h[1], h[2], h[3])
+               : p == 1u ? make_uint4(h[1], h[2], h[3], h[4]) : make_uint4(h[2], h[3], h[4], h[5]);
+    }
 }
 
 hipError_t launch_decode_blocks(const uint4 *blocks, size_t n, uint32_t is_signed, uint16_t *out,

@@ -37,9 +37,15 @@ namespace {
 constexpr float kA = 31.0f / 64.0f;      // a of eq. (6) for the unsigned format
 constexpr int kTrainThreads = 256;
 
-__global__ void __launch_bounds__(256) k_train_zero(float *p, uint32_t n)
+// What the backward accumulates into: the texel gradients (n_texels is a
+// multiple of 4), the parameter gradients and the sort's cell counts.
+__global__ void __launch_bounds__(256) k_train_clear(TrainDesc d)
 {
-    for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) p[i] = 0.0f;
+    const uint32_t tid = blockIdx.x * blockDim.x + threadIdx.x, step = gridDim.x * blockDim.x;
+    float4 *g = reinterpret_cast<float4 *>(d.g_texels);
+    for (uint32_t i = tid; i < d.n_texels / 4u * 3u; i += step) g[i] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    for (uint32_t i = tid; i < d.n_params; i += step) d.g_params[i] = 0.0f;
+    for (uint32_t i = tid; i < kTrainBins; i += step) d.bin_count[i] = 0u;
 }
 
 __device__ __forceinline__ void wave_sync_lds()
@@ -648,8 +654,9 @@ __global__ void __launch_bounds__(kBinThreads) k_train_bin_count(const float *qu
         if (hist[b]) atomicAdd(&count[b], hist[b]);
 }
 
-// next[cell] = samples of the cells before it (one workgroup, 4 cells a thread)
-__global__ void __launch_bounds__(kBinThreads) k_train_bin_scan(const uint32_t *count, uint32_t *next)
+// next[cell] = samples of the cells before it (one workgroup, 4 cells a
+// thread); leaves the counts clear for the next batch of samples
+__global__ void __launch_bounds__(kBinThreads) k_train_bin_scan(uint32_t *count, uint32_t *next)
 {
     static_assert(kTrainBins == 4 * kBinThreads, "four cells a thread");
     __shared__ uint32_t wave_sum[kBinThreads / 64];
@@ -658,6 +665,7 @@ __global__ void __launch_bounds__(kBinThreads) k_train_bin_scan(const uint32_t *
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
         c[k] = count[4 * t + k];
+        count[4 * t + k] = 0u;
         own += c[k];
     }
     uint32_t incl = own;                           // inclusive scan within the wave
@@ -1334,8 +1342,7 @@ hipError_t launch_train_backward(const TrainDesc &d, const float *queries, size_
 {
     hipError_t e = launch_texels(d, s);
     if (e != hipSuccess) return e;
-    k_train_zero<<<grid_for((size_t)d.n_texels * 3u, 256, 8192), 256, 0, s>>>(d.g_texels, d.n_texels * 3u);
-    k_train_zero<<<grid_for(d.n_params, 256, 64), 256, 0, s>>>(d.g_params, d.n_params);
+    k_train_clear<<<grid_for(std::max<size_t>((size_t)d.n_texels / 4u * 3u, kTrainBins), 256, 8192), 256, 0, s>>>(d);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     const uint32_t c = d.dims[d.n_layers];
     // the scatter's regions: 2 x 2 cells, where a window then still spans at
@@ -1359,8 +1366,6 @@ hipError_t launch_train_backward(const TrainDesc &d, const float *queries, size_
         const float *q = queries + 3 * off;
         const uint32_t per = bin_per_thread(m);
         const unsigned bins = (m + per * kBinThreads - 1) / (per * kBinThreads);
-        // (the counts are cleared as floats: 0.0f is all zero bits)
-        k_train_zero<<<8, 256, 0, s>>>(reinterpret_cast<float *>(d.bin_count), kTrainBins);
         if (per == 1) k_train_bin_count<1><<<bins, kBinThreads, 0, s>>>(q, m, d.bin_count);
         else k_train_bin_count<8><<<bins, kBinThreads, 0, s>>>(q, m, d.bin_count);
         k_train_bin_scan<<<1, kBinThreads, 0, s>>>(d.bin_count, d.bin_next);
