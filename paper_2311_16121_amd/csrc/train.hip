@@ -149,7 +149,7 @@ __global__ void __launch_bounds__(kTrainThreads) k_train_texels(TrainDesc d)
         if (!s.valid) continue;
         const TrainTexDesc &tx = d.tex[s.ti];
         // partition ids are taken modulo 32
-        const uint32_t pmask = kTable[kModes * kModeWords + (tx.partitions[s.b] & 31u)];
+        const uint32_t pmask = kTable[kPartitionRow + (tx.partitions[s.b] & 31u)];
         float e[12];
 #pragma unroll
         for (int k = 0; k < 12; ++k) e[k] = tx.endpoints[12u * s.b + k];
@@ -231,14 +231,14 @@ __global__ void __launch_bounds__(kTrainThreads) k_train_texels_packed(TrainDesc
         h.ib = 3;
         h.valid = 1;
         bc6h_palette<false>(h, pal);
-        const uint32_t mask = kTable[kModes * kModeWords + (pp[b] & 31u)] & 0xFFFFu;   // ids are taken modulo 32
+        const uint32_t part = pp[b] & 31u;           // ids are taken modulo 32
 #pragma unroll
         for (int t = 0; t < 8; ++t) {
             s0 |= (uint32_t)fminf(fmaxf(rintf(7.0f * x[t]), 0.0f), 7.0f) << (4 * t);
             s1 |= (uint32_t)fminf(fmaxf(rintf(7.0f * x[8 + t]), 0.0f), 7.0f) << (4 * t);
         }
-        s0 |= spread1to4(mask & 0xFFu) << 3;
-        s1 |= spread1to4(mask >> 8) << 3;
+        s0 |= kTable[kSpreadRow + 2 * part];
+        s1 |= kTable[kSpreadRow + 2 * part + 1];
     } else {
 #pragma unroll
         for (int j = 0; j < 16; ++j) pal[j][0] = pal[j][1] = 0u;
@@ -275,7 +275,7 @@ __global__ void __launch_bounds__(kTrainThreads) k_train_texels_floats(TrainDesc
             const float *ep = pyr == 0 ? d.tex[0].endpoints : pyr == 1 ? d.tex[1].endpoints : pyr == 2 ? d.tex[2].endpoints : d.tex[3].endpoints;
             const float *xp = pyr == 0 ? d.tex[0].indices : pyr == 1 ? d.tex[1].indices : pyr == 2 ? d.tex[2].indices : d.tex[3].indices;
             const uint8_t *pp = pyr == 0 ? d.tex[0].partitions : pyr == 1 ? d.tex[1].partitions : pyr == 2 ? d.tex[2].partitions : d.tex[3].partitions;
-            const uint32_t pmask = kTable[kModes * kModeWords + (pp[b] & 31u)] >> (4u * r);   // ids are taken modulo 32
+            const uint32_t pmask = kTable[kPartitionRow + (pp[b] & 31u)] >> (4u * r);   // ids are taken modulo 32
             float e[12];
 #pragma unroll
             for (int k = 0; k < 12; ++k) e[k] = ep[12u * (size_t)b + k];
@@ -333,7 +333,7 @@ __global__ void __launch_bounds__(kTrainThreads) k_train_blocks(TrainDesc d)
         const TexelSite s = texel_site(d, g >> 2, 4u * r);
         const TrainTexDesc &tx = d.tex[s.ti];
         // partition ids are taken modulo 32
-        const uint32_t pmask = kTable[kModes * kModeWords + (tx.partitions[s.b] & 31u)] >> (4u * r);
+        const uint32_t pmask = kTable[kPartitionRow + (tx.partitions[s.b] & 31u)] >> (4u * r);
         const float *ep = tx.endpoints + 12u * s.b, *xp = tx.indices + 16u * s.b + 4u * r;
         float e[12], x[4], gt[12];
         if (ALIGNED) {

@@ -5,6 +5,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "bc6h_device.hpp"
 #include "filter_device.hpp"
 
 namespace bcf {
@@ -42,7 +43,7 @@ typedef __attribute__((address_space(1))) u32x3_t global_u32x3;
 template <bool NT>
 __device__ __forceinline__ void store_packed_pair(uint32_t *dst, uint2 t0, uint2 t1)
 {
-    const u32x3_t v = {t0.x, (t0.y & 0xFFFFu) | (t1.x << 16), (t1.x >> 16) | (t1.y << 16)};
+    const u32x3_t v = {t0.x, pack_lo_hi(t0.y, t1.x), pack_lo_hi(t1.x >> 16, t1.y)};
     if (NT) __builtin_nontemporal_store(v, (global_u32x3 *)dst);
     else *(global_u32x3 *)dst = v;
 }
@@ -71,6 +72,11 @@ __device__ __forceinline__ void store_positions(uint32_t *pdst, uint32_t lw, uin
     const uint32_t bx = (lw + 3) / 4, bxm = bx - 1u, bxs = (uint32_t)__builtin_ctz(bx), pitch = row_pitch(lw);
     const uint32_t lane = threadIdx.x & 63u, wave0 = threadIdx.x & ~63u;
     const uint32_t chunk8 = lane & 7u, pp = 2 * (lane & 1u), cpos = chunk8 >> 1;
+    // a level's scratch is below 2 GB: byte offsets in 32 bits
+    auto store = [&](uint32_t off, uint2 t0, uint2 t1) {
+        store_packed_pair<NT>(reinterpret_cast<uint32_t *>(reinterpret_cast<uint8_t *>(pdst) + off), t0, t1);
+    };
+#pragma unroll
     for (uint32_t h = 0; h < 2; ++h) {
         const uint32_t blw = 8 * h + (lane >> 3);                     // block within the wave
         const uint32_t p = (wave0 >> 2) + blw;                        // within the chunk
@@ -78,6 +84,22 @@ __device__ __forceinline__ void store_positions(uint32_t *pdst, uint32_t lw, uin
         const uint32_t bj = list ? list[p] : first + blw;             // its index in the level
         const uint32_t lb = wave0 + 4 * blw + pp;                     // LDS lane of pyramid pp
         const uint32_t x0 = 4 * (bj & bxm), y0 = 4 * (bj >> bxs);
+        if (lw >= 4 && lh >= 4) {
+            // four whole rows: this lane's column of both blocks' slots, then
+            // a nibble and a palette read per row and pyramid
+            const uint2 sa = slots[lb], sb = slots[lb + 1];
+            const uint32_t sh = 4 * cpos;
+            const uint32_t wa[2] = {sa.x >> sh, sa.y >> sh}, wb[2] = {sb.x >> sh, sb.y >> sh};
+            uint32_t off = 24u * (__umul24(y0, pitch) + x0 + cpos) + 12u * (pp >> 1);
+#pragma unroll
+            for (int r = 0; r < 4; ++r, off += 24u * pitch) {
+                const uint2 p0 = palette[(wa[r >> 1] >> (16 * (r & 1))) & 15u][lb];
+                const uint2 p1 = palette[(wb[r >> 1] >> (16 * (r & 1))) & 15u][lb + 1];
+                store(off, p0, p1);
+                if (x0 == 0 && cpos < 2) store(off + 24u * lw, p0, p1);   // wrap positions w, w + 1
+            }
+            continue;
+        }
         for (uint32_t r = 0; r < 4; ++r) {
             if (y0 + r >= lh) break;
             // position index within the level (below 2^31: levels are at most 32768^2)
@@ -88,9 +110,9 @@ __device__ __forceinline__ void store_positions(uint32_t *pdst, uint32_t lw, uin
             const uint32_t col = lw >= 4 ? cpos : lw == 2 ? (cpos & 1u) : 0u;
             const uint2 p0 = palette_texel(palette, slots, lb, 4 * r + col);
             const uint2 p1 = palette_texel(palette, slots, lb + 1, 4 * r + col);
-            store_packed_pair<NT>(pdst + 6 * (size_t)(prow + x0 + cpos) + 3 * (pp >> 1), p0, p1);
+            store(24u * (prow + x0 + cpos) + 12u * (pp >> 1), p0, p1);
             if (lw >= 4 && x0 == 0 && cpos < 2)                        // wrap positions w, w + 1
-                store_packed_pair<NT>(pdst + 6 * (size_t)(prow + lw + cpos) + 3 * (pp >> 1), p0, p1);
+                store(24u * (prow + lw + cpos) + 12u * (pp >> 1), p0, p1);
         }
     }
 }
