@@ -66,8 +66,8 @@ struct FrameArgs {
 constexpr uint32_t kTileLog2 = 4, kTileW = 1u << kTileLog2, kTileH = 64u >> kTileLog2;
 
 // The grid is a multiple of the 8 XCDs, to which workgroups are dispatched
-// round-robin (workgroup b runs on XCD b % 8), and a small multiple of what
-// is resident at once, so the waves sweep the image nearly together. Tiled
+// round-robin (workgroup b runs on XCD b % 8), and at most what is resident
+// at once, so the waves sweep the image nearly together. Tiled
 // work deals strips of whole tile rows to the XCDs in turn (strip j to XCD
 // j % 8); an XCD's waves walk its strips tile by tile. Texels are shared
 // along a strip -- a textured plane that wraps repeats the same texels
@@ -195,7 +195,12 @@ __device__ __forceinline__ void copy_lut(const LevelLut &src, LevelLut &dst)
 // MLP (eq. 3) of a wave's 64 feature vectors z (one per lane); the outputs
 // land in the wave's LDS stage, lane L's at st[L * out_dim ...]. The feature
 // vectors pass through `feats`, which may be the same LDS as st (both 4 KB).
-template <MlpKind K, int H, int NH>
+// YIELD: the other waves of the SIMD go first while this one feeds the matrix
+// cores, so that their loads and filters run beside its products (k_frame's
+// waves otherwise meet in the MLP one after the other: 1920 x 1080 fp32 91 ->
+// 88 us, 2^22 points fp32 178 -> 173, 2720 x 1530 fp16 76.5 -> 74.9; k_batch and
+// the training forward, which do not load ahead, lost 1 to 4%).
+template <bool YIELD, MlpKind K, int H, int NH>
 __device__ __forceinline__ void mlp_stage(const float z[12], const MfmaMlp<K, H, NH> &mlp, float4_t (*feats)[4],
                                           float *st, uint32_t out_dim, uint32_t lane)
 {
@@ -220,7 +225,9 @@ __device__ __forceinline__ void mlp_stage(const float z[12], const MfmaMlp<K, H,
 #pragma unroll
         for (int i = 0; i < 4; ++i) f[grp][i] = fin[grp][i];
     float4_t o[4];
+    if (YIELD) __builtin_amdgcn_s_setprio(0);
     mlp.template run_groups<4>(f, o);
+    if (YIELD) __builtin_amdgcn_s_setprio(3);
 #pragma unroll
     for (int grp = 0; grp < 4; ++grp) {
         const float4_t o4 = o[grp];
@@ -233,18 +240,18 @@ __device__ __forceinline__ void mlp_stage(const float z[12], const MfmaMlp<K, H,
 }
 
 // One wave's 64 queries: filter (eqs. 9, 10), concatenate, MLP.
-template <MlpKind K, int H, int NH, int LAYOUT>
+template <bool YIELD, MlpKind K, int H, int NH, int LAYOUT>
 __device__ __forceinline__ void decode_wave(const Query &qq, __amdgpu_buffer_rsrc_t rs, const LevelLut &lut,
                                             const float *levels_bias, uint32_t stride,
                                             const MfmaMlp<K, H, NH> &mlp, float4_t (*feats)[4], float *st, uint32_t out_dim, uint32_t lane)
 {
     float z[12];
     filter4<LAYOUT>(rs, lut, levels_bias, stride, qq.u, qq.v, qq.s, z);
-    mlp_stage<K, H, NH>(z, mlp, feats, st, out_dim, lane);
+    mlp_stage<YIELD, K, H, NH>(z, mlp, feats, st, out_dim, lane);
 }
 
 // decode_wave for a material with a position-interleaved scratch
-template <MlpKind K, int H, int NH>
+template <bool YIELD, MlpKind K, int H, int NH>
 __device__ __forceinline__ void decode_wave_interleaved(const Query &qq, __amdgpu_buffer_rsrc_t rs,
                                                         const LevelLut &lut, const float *levels_bias,
                                                         const MfmaMlp<K, H, NH> &mlp, float4_t (*feats)[4],
@@ -254,7 +261,7 @@ __device__ __forceinline__ void decode_wave_interleaved(const Query &qq, __amdgp
     fetch4_packed(rs, lut, levels_bias, qq.u, qq.v, qq.s, taps);
     float z[12];
     filter_pending_packed(taps, z);
-    mlp_stage<K, H, NH>(z, mlp, feats, st, out_dim, lane);
+    mlp_stage<YIELD, K, H, NH>(z, mlp, feats, st, out_dim, lane);
 }
 
 // Item `it` of a run of n consecutive queries: its (up to) 64 staged rows go
@@ -418,7 +425,7 @@ __global__ void __launch_bounds__(kFrameThreads) k_frame(FrameArgs a)
                 float z[12];
                 if constexpr (LAYOUT == kLayoutPacked) filter_pending_packed(taps, z);
                 else filter_pending(taps, z);
-                mlp_stage<K, H, NH>(z, mlp, feats, st, a.out_dim, lane);
+                mlp_stage<true, K, H, NH>(z, mlp, feats, st, a.out_dim, lane);
                 fetch(qnext, taps);
                 qnext = load_query(rq, query_of(clamp_item(k + 2 * items.step), i_, r_, c_));
                 store_item<V>(a, oob, st, ro, it, row0, col0, lane);
@@ -431,7 +438,7 @@ __global__ void __launch_bounds__(kFrameThreads) k_frame(FrameArgs a)
                 query_of(k, it, row0, col0);
                 const Query qq = next;
                 if (k + items.step < items.end) next = load_query(rq, query_of(k + items.step, i_, r_, c_));
-                decode_wave<K, H, NH, kLayoutSplit>(qq, rs, lut, a.levels_bias, a.stride, mlp, feats, st, a.out_dim,
+                decode_wave<true, K, H, NH, kLayoutSplit>(qq, rs, lut, a.levels_bias, a.stride, mlp, feats, st, a.out_dim,
                                                     lane);
                 store_item<V>(a, oob, st, ro, it, row0, col0, lane);
                 wave_lds_sync();
@@ -584,11 +591,11 @@ __global__ void __launch_bounds__(64 * W) k_batch(BatchArgs a)
         const uint32_t j = it - first_item;
         const Query qq = load_query(rq, j * 64 + lane);   // past n_k: zeros, not stored
         if (interleaved)
-            decode_wave_interleaved<K, H, NH>(qq, rs, lut[wv], lb, mlp, feats, st, a.out_dim, lane);
+            decode_wave_interleaved<false, K, H, NH>(qq, rs, lut[wv], lb, mlp, feats, st, a.out_dim, lane);
         else if (shared)
-            decode_wave<K, H, NH, kLayoutShared>(qq, rs, lut[wv], lb, stride, mlp, feats, st, a.out_dim, lane);
+            decode_wave<false, K, H, NH, kLayoutShared>(qq, rs, lut[wv], lb, stride, mlp, feats, st, a.out_dim, lane);
         else
-            decode_wave<K, H, NH, kLayoutSplit>(qq, rs, lut[wv], lb, stride, mlp, feats, st, a.out_dim, lane);
+            decode_wave<false, K, H, NH, kLayoutSplit>(qq, rs, lut[wv], lb, stride, mlp, feats, st, a.out_dim, lane);
         store_run(stage[wv], ro, j, n_k, a.out_dim, lane);
         wave_lds_sync();
     }
@@ -633,9 +640,12 @@ unsigned resident_workgroups()
 }
 
 // One workgroup per kFrameWaves items, at most `cap`, a multiple of the XCDs.
-// The cap is twice the workgroups resident at once (measured on the frame
-// benchmark: the kernels run fastest when their waves sweep the image nearly
-// together).
+// The cap is the workgroups resident at once: every wave then loads its weights
+// and fills its pipeline once and takes the same share of the items. With twice
+// as many, the later half of the workgroups paid both again, which a 4K frame
+// does not show (158 against 161 us with fp16) and smaller work does: 1920 x
+// 1080 fp16 37 against 47 us, 960 x 540 15 / 18, 2^20 points 33 / 36, the same
+// points with fp32 55 / 60.
 inline unsigned frame_launch_grid(uint32_t n_items, unsigned cap)
 {
     const unsigned want = (n_items + kFrameWaves - 1) / kFrameWaves;
@@ -646,12 +656,11 @@ inline unsigned frame_launch_grid(uint32_t n_items, unsigned cap)
 template <MlpKind K, int SH>
 hipError_t launch_frame_kind(const FrameArgs &a, const MlpShape &sh, hipStream_t s)
 {
-    constexpr unsigned kOversub = 2;
 #define BCF_CASE(H, NH)                                                                       \
     if (sh.hidden == H && sh.n_hidden == NH) {                                               \
         const unsigned res = resident_workgroups<k_frame<K, H, NH, SH>>();                \
         k_frame<K, H, NH, SH>                                                                 \
-            <<<frame_launch_grid(a.n_items, res ? kOversub * res : 4096u), kFrameThreads, 0, s>>>(a); \
+            <<<frame_launch_grid(a.n_items, res ? res : 1024u), kFrameThreads, 0, s>>>(a); \
         return hipGetLastError();                                                             \
     }
     BCF_CASE(16, 1) BCF_CASE(16, 2) BCF_CASE(16, 3)

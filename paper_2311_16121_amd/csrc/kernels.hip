@@ -554,8 +554,23 @@ static FrameArgs frame_args(const MaterialDesc &m, const WsLayout &lay, const vo
     return a;
 }
 
-// tile rows per strip of a tiled frame (16 x 4 tiles: 16 image rows)
+// Tile rows per strip of a tiled frame: four (16 x 4 tiles: 16 image rows),
+// fewer when whole strips would leave the XCDs with shares that differ by more
+// than 1/32 (a 1080-row image: 68 strips of four rows give nine to some XCDs
+// and eight to others, 135 strips of two rows 17 and 16), and 0 (round-robin)
+// when the image has too few tile rows to give every XCD one. A 4K frame: 192,
+// 195, 187 and 199 us a step with 1, 2, 4 and 8 rows.
 constexpr uint32_t kStripRows = 4;
+
+static uint32_t strip_rows(uint32_t tiles_y)
+{
+    uint32_t r = kStripRows;
+    for (; r > 1; r /= 2) {
+        const uint32_t strips = (tiles_y + r - 1) / r, most = (strips + kXcds - 1) / kXcds * r;   // of one XCD
+        if (strips >= kXcds && (uint64_t)most * kXcds * 32 <= (uint64_t)tiles_y * 33) break;
+    }
+    return tiles_y >= r * kXcds ? r : 0;
+}
 
 hipError_t launch_filter_mlp(const MaterialDesc &m, const MlpShape &sh, MlpKind kind,
                              const WsLayout &lay, const void *ws, const float *queries, size_t n,
@@ -583,11 +598,7 @@ hipError_t launch_filter_mlp(const MaterialDesc &m, const MlpShape &sh, MlpKind 
         a.tiles_x = (grid_width + kTileW - 1) / kTileW;
         a.tiles_y = (rows + kTileH - 1) / kTileH;
         a.n_items = a.tiles_x * a.tiles_y;
-        // strips of kStripRows tile rows, fewer when the image has too few
-        // tile rows to give every XCD a strip
-        a.strip_rows = 0;
-        for (uint32_t r = kStripRows; r >= 1 && !a.strip_rows; r /= 2)
-            if (a.tiles_y >= r * kXcds) a.strip_rows = r;
+        a.strip_rows = strip_rows(a.tiles_y);
         a.wide = (grid_width * sh.out) % 4 == 0 && (a.n * sh.out) % 4 == 0 && ((uintptr_t)out & 15) == 0;
         return launch();
     }

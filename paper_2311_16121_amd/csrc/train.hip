@@ -591,7 +591,7 @@ __launch_bounds__(kTrainThreads) k_train_forward_mfma(TrainDesc d, const float *
         float z[12];
         features<PACK>(d, lut, live ? queries[3u * q] : 0.0f, live ? queries[3u * q + 1u] : 0.0f,
                  live ? queries[3u * q + 2u] : 0.0f, z);
-        mlp_stage<MLP_MFMA_F32, H, NH>(z, mlp, feats, st, c, lane);
+        mlp_stage<false, MLP_MFMA_F32, H, NH>(z, mlp, feats, st, c, lane);
         // the chunk's rows are contiguous: 16-byte stores where they may be
         const uint32_t floats = min(64u, n - ch * 64u) * c;
         float *dst = out + (size_t)ch * 64u * c;
