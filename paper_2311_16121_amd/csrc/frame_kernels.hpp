@@ -54,7 +54,9 @@ struct FrameArgs {
     // a wave takes a tile of kTileW columns by kTileH rows (lane = row *
     // kTileW + column); with 0, 64 consecutive queries.
     // wide: every output row this launch writes starts on a 16-byte boundary
-    // and n * out_dim is a multiple of 4, so items store 16-byte chunks
+    // (linear items: the output does), so items store 16-byte chunks; an
+    // image's n * out_dim is then a multiple of 4, and a linear launch's last
+    // n * out_dim % 4 floats follow on their own (store_rest)
     uint32_t grid_w, tiles_x, n_items, wide;
     // tiled work: tiles_y rows of tiles; strip_rows > 0: the tile rows form
     // strips of that many, dealt to the XCDs in turn (0: items round-robin).
@@ -93,8 +95,10 @@ __device__ __forceinline__ WaveWork wave_work(const FrameArgs &a, uint32_t wv)
         const uint32_t n_strips = (a.tiles_y + a.strip_rows - 1) / a.strip_rows;
         const uint32_t mine = n_strips > x ? (n_strips - x + kXcds - 1) / kXcds : 0;   // strips x, x + 8, ...
         const uint32_t per = a.strip_rows * a.tiles_x;
-        return WaveWork{(blockIdx.x / kXcds) * kFrameWaves + wv, mine * per, (gridDim.x / kXcds) * kFrameWaves, x,
-                        per};
+        // the last strip ends with the last item
+        const uint32_t past = (n_strips - 1) % kXcds == x ? n_strips * per - a.n_items : 0;
+        return WaveWork{(blockIdx.x / kXcds) * kFrameWaves + wv, mine * per - past, (gridDim.x / kXcds) * kFrameWaves,
+                        x, per};
     }
     return WaveWork{blockIdx.x * kFrameWaves + wv, a.n_items, gridDim.x * kFrameWaves, 0, 0};
 }
@@ -320,12 +324,26 @@ __device__ __forceinline__ void store_item(const FrameArgs &a, uint32_t oob, con
     for (int m = 0; m < 16 / V; ++m) {
         const uint32_t e = e0 + step * m;
         const vec_t v = *reinterpret_cast<const vec_t *>(st + k0 + e);
-        const int off = (int)(e < lim ? (base + e) * 4u : oob);
+        const int off = (int)(e + (V - 1) < lim ? (base + e) * 4u : oob);
         if constexpr (V == 4)
             __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(uint4_t, v), ro, off, 0, kStoreNT);
         else
             __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, v), ro, off, 0, kStoreNT);
     }
+}
+
+// The last n * out_dim % 4 floats of a linear launch, which its 16-byte chunks
+// leave out, from the stage of the wave that took the last item (an item that
+// no other follows in its wave).
+__device__ __forceinline__ void store_rest(const FrameArgs &a, const float *st, __amdgpu_buffer_rsrc_t ro, uint32_t it,
+                                           uint32_t lane)
+{
+    const uint32_t n_out = a.n * a.out_dim, rest = n_out & 3u;
+    if (a.grid_w || !rest || it != a.n_items - 1) return;
+    const uint32_t at = n_out - rest;
+    if (lane < rest)
+        __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, st[at + lane - it * 64u * a.out_dim]), ro,
+                                              (int)((at + lane) * 4u), 0, 0);
 }
 
 // 16 / V stores past the output's end: the loop's entry then has the same
@@ -400,7 +418,7 @@ __global__ void __launch_bounds__(kFrameThreads) k_frame(FrameArgs a)
     const ItemRange items{w.first, w.end, w.step};
     auto run = [&](auto width) {
         constexpr int V = decltype(width)::value;
-        uint32_t it, row0, col0, i_, r_, c_;
+        uint32_t it = 0, row0, col0, i_, r_, c_;
         if (LAYOUT != kLayoutSplit) {
             // Per item: blend its texels, run the MLP, issue the next item's
             // texel loads and the query after that, then store -- so the
@@ -444,6 +462,7 @@ __global__ void __launch_bounds__(kFrameThreads) k_frame(FrameArgs a)
                 wave_lds_sync();
             }
         }
+        if (V == 4) store_rest(a, st, ro, it, lane);
     };
     if (a.wide)
         run(Width<4>());
