@@ -599,7 +599,7 @@ hipError_t launch_filter_mlp(const MaterialDesc &m, const MlpShape &sh, MlpKind 
         a.tiles_y = (rows + kTileH - 1) / kTileH;
         a.n_items = a.tiles_x * a.tiles_y;
         a.strip_rows = strip_rows(a.tiles_y);
-        a.wide = (grid_width * sh.out) % 4 == 0 && (a.n * sh.out) % 4 == 0 && ((uintptr_t)out & 15) == 0;
+        a.row_rest = (grid_width * sh.out) % 4 != 0 || (a.n * sh.out) % 4 != 0;
         return launch();
     }
     // one launch covers at most kMaxQueriesPerLaunch queries (32-bit buffer offsets)
@@ -612,7 +612,7 @@ hipError_t launch_filter_mlp(const MaterialDesc &m, const MlpShape &sh, MlpKind 
         a.tiles_x = kLinearRun;
         a.tiles_y = (a.n_items + kLinearRun - 1) / kLinearRun;
         a.strip_rows = a.tiles_y >= kXcds ? 1 : 0;
-        a.wide = ((uintptr_t)a.out & 15) == 0;
+        a.row_rest = 0;
         const hipError_t e = launch();
         if (e != hipSuccess) return e;
     }

@@ -149,3 +149,24 @@ def test_training_packed_texels_equal_the_images(bcf, sizes, levels, shift, stra
                                       for geo in (one, other))
         for a, b in list(zip(ge, re)) + list(zip(gi, ri)) + [(gp, rp)]:
             assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("n,grid,out_dim", [
+    (1, 0, 1), (5, 0, 3), (63, 0, 9), (64, 0, 16), (65, 0, 7), (129, 0, 10), (4097, 0, 3),      # linear items
+    (32768, 0, 1), (32769, 0, 1), (33001, 0, 5),                                               # linear strips
+    (1, 1, 1), (7, 3, 1), (70, 7, 3), (81, 9, 9), (15 * 8 + 4, 15, 16), (33 * 17, 33, 10), (201 * 173 - 5, 201, 7)])
+def test_decode_stores_every_row_and_nothing_else(bcf, n, grid, out_dim):
+    """Linear launches and images whose rows leave 1..3 floats over, in outputs
+    at every four-byte alignment, with the bytes around them kept."""
+    mat, host = material(bcf, [(64, 64)] * 4, [7] * 4, (12, 16, out_dim), seed=130)
+    q = synth.uniform_queries(n, synth.rng(131), 6.0)
+    want = oracle.decode(host, q)
+    ws = bcf.prepare(mat, bcf.Precision.FP32)
+    for shift in range(4):
+        buf = torch.full((64 + n * out_dim + 64,), -77.0, device="cuda")
+        out = buf[64 + shift - 4:][:n * out_dim].view(n, out_dim)
+        bcf.decode(mat, ws, dev(q), grid_width=grid, out=out)
+        got = buf.cpu().numpy()
+        lo = 64 + shift - 4
+        assert np.abs(got[lo:lo + n * out_dim].reshape(n, out_dim) - want).max() <= 1e-5
+        assert (got[:lo] == -77.0).all() and (got[lo + n * out_dim:] == -77.0).all()
