@@ -241,10 +241,10 @@ bcf_status bcf_prepare_batch(const bcf_material *mats, uint32_t n_mats, bcf_prec
 /* bcf_unpack for every material of the batch, in one launch (each workgroup
  * unpacks one 256-lane chunk of a table of every material's (pyramid, level)
  * segments that bcf_prepare_batch wrote into the workspace).
- * A material whose four pyramids share size, level count and bias keeps its
- * texels position-interleaved in the batch workspace (the four pyramids'
+ * A material whose three or four pyramids share size, level count and bias
+ * keeps its texels position-interleaved in the batch workspace (the pyramids'
  * texels of one position together), so a decode reads one footprint row of
- * all four from one span; results do not depend on the layout. */
+ * all of them from one span; results do not depend on the layout. */
 bcf_status bcf_unpack_batch(const bcf_material *mats, uint32_t n_mats, void *ws, void *stream);
 
 /* bcf_unpack_batch restricted to the blocks that these queries' trilinear

@@ -28,11 +28,11 @@ struct MaterialDesc {
     TexDesc tex[kMaxTextures];
     uint32_t n_tex;
     uint32_t is_signed;
-    // 1: the four pyramids share one geometry and their texel scratch is
-    // position-packed -- texel (x, y) of level l of all four pyramids in one
-    // 24-byte position of (r, g, b) halves (pyramid t at byte 6t), tex_off
-    // counting positions and equal for every pyramid -- so a footprint row of
-    // all four pyramids is one 48-byte span. 0: each pyramid's levels back to
+    // 1: the three or four pyramids share one geometry and their texel scratch
+    // is position-packed -- texel (x, y) of level l of all pyramids in one
+    // 24-byte position of (r, g, b) halves (pyramid t at byte 6t; of three, the
+    // last slot repeats pyramid 0), tex_off counting positions and equal for
+    // every pyramid -- so a footprint row of all pyramids is one 48-byte span. 0: each pyramid's levels back to
     // back (8-byte texels (r | g << 16, b)).
     uint32_t interleaved;
 };

@@ -513,8 +513,8 @@ __global__ void k_fill(float *p, uint32_t n, float v)
 }
 
 // Frame arguments common to the decode and the calibration.
-// *layout: kLayoutPacked for a packed scratch, kLayoutShared for pyramids of
-// one geometry a constant stride apart, else kLayoutSplit.
+// *layout: kLayoutPacked for a packed scratch, kLayoutShared for one or two
+// pyramids of one geometry, else kLayoutSplit.
 static FrameArgs frame_args(const MaterialDesc &m, const WsLayout &lay, const void *ws, uint32_t out_dim,
                             int *layout)
 {
@@ -538,7 +538,7 @@ static FrameArgs frame_args(const MaterialDesc &m, const WsLayout &lay, const vo
         a.levels_bias[2 * t + 1] = T.bias;
     }
     // shared geometry: identical w, h, levels and bias, scratch a constant stride apart
-    bool shared = true;
+    bool shared = m.n_tex <= (uint32_t)kSharedTextures;
     const uint32_t stride_texels = m.n_tex > 1 ? m.tex[1].tex_off[0] - m.tex[0].tex_off[0] : 0;
     for (uint32_t t = 1; t < m.n_tex; ++t) {
         const TexDesc &A = m.tex[0], &B = m.tex[t];

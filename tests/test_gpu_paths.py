@@ -170,3 +170,30 @@ def test_decode_stores_every_row_and_nothing_else(bcf, n, grid, out_dim):
         lo = 64 + shift - 4
         assert np.abs(got[lo:lo + n * out_dim].reshape(n, out_dim) - want).max() <= 1e-5
         assert (got[:lo] == -77.0).all() and (got[lo + n * out_dim:] == -77.0).all()
+
+
+@pytest.mark.parametrize("n_tex,size,levels", [(3, (64, 64), 7), (3, (8, 2), 4), (3, (1, 32), 6), (3, (256, 4), 1),
+                                               (2, (64, 64), 7), (2, (2, 16), 3), (1, (64, 64), 7), (1, (1, 1), 1)])
+def test_pyramids_of_one_geometry_in_each_count(bcf, n_tex, size, levels):
+    """One to three pyramids of one geometry: the packed scratch of three, the
+    two-slot filter of one and two, single and batched, whole and touched."""
+    dims = (3 * n_tex, 16, 10)
+    mats, hosts = zip(*(material(bcf, [size] * n_tex, [levels] * n_tex, dims, seed=140 + k, bias=[-0.5] * n_tex)
+                        for k in range(2)))
+    q = synth.uniform_queries(1500, synth.rng(143), float(levels))
+    offsets = np.array([0, 1000, 1500], np.int32)
+    wants = [oracle.decode(hosts[0], q[:1000]), oracle.decode(hosts[1], q[1000:])]
+    for prec, tol in (("FP32", 1e-5), ("FP16", 2e-3)):
+        p = bcf.Precision[prec]
+        batch = bcf.Batch(list(mats), p, ws_fill=0xFF)
+        batch.unpack_touched(dev(q), dev(offsets))
+        touched = batch.decode(dev(q), dev(offsets)).cpu().numpy()
+        batch.unpack()
+        assert np.array_equal(batch.decode(dev(q), dev(offsets)).cpu().numpy(), touched)
+        for k, part in enumerate((slice(0, 1000), slice(1000, 1500))):
+            single = bcf.decode(mats[k], bcf.prepare(mats[k], p), dev(q[part]), p).cpu().numpy()
+            assert np.array_equal(single, touched[part])
+            assert np.abs(single - wants[k]).max() <= tol
+    # z0's largest magnitude: one binary32 filter against binary64, so a few ulp
+    absmax = bcf.calibrate(mats[0], dev(q)).cpu().numpy()
+    assert abs(float(absmax[0]) - np.abs(oracle.sample(hosts[0], q)).max()) <= 1e-6
