@@ -17,7 +17,7 @@ namespace bcf {
 __host__ __device__ inline uint32_t row_pitch(uint32_t w) { return w + 2u; }
 
 // Per pyramid slot and level, as the kernels read it from LDS:
-//   x = float(w_l), y = float(h_l), z = (w_l - 1) | (h_l - 1) << 16, w = first texel
+//   x = float(w_l), y = float(h_l), z = (w_l - 1) | (h_l - 1) << 16, w = byte offset of the first texel
 struct LevelLut {
     uint4 e[kMaxTextures][kMaxLevels];
 };
@@ -90,8 +90,11 @@ __device__ __forceinline__ TapCoords tap_coords(uint4 e, float uf, float vf)
     return t;
 }
 
-// UNIT: bytes per texel slot of the scratch (8; 24 for a packed one, whose
-// LUT offsets count 24-byte positions)
+// UNIT: bytes per texel slot of the scratch (8; 24 for a packed one). Row y
+// starts y * UNIT (w + 2) bytes after the level, two 24-bit factors (levels
+// are at most 32768 x 32768) and a product below 2^31: one 24-bit
+// multiply-add per row, where shifts and a 32-bit product by UNIT took four
+// instructions and a quarter-rate one.
 template <uint32_t UNIT = 8>
 __device__ __forceinline__ Footprint footprint(uint4 e, float uf, float vf, float lw)
 {
@@ -102,11 +105,10 @@ __device__ __forceinline__ Footprint footprint(uint4 e, float uf, float vf, floa
     const TapCoords t = tap_coords(e, uf, vf);
     const float fx = t.fx, fy = t.fy;
     const uint32_t x0 = t.x0, y0 = t.y0, y1 = t.y1;
-    const uint32_t lw2 = __builtin_popcount(t.wm);              // log2 w
-    // row y starts at y * (w + 2) = (y << log2 w) + 2 y
+    const uint32_t pitch = __umul24(t.wm, UNIT) + 3u * UNIT, at = __umul24(x0, UNIT) + first;
     Footprint f;
-    f.o0 = ((y0 << lw2) + 2u * y0 + x0 + first) * UNIT;
-    f.o1 = ((y1 << lw2) + 2u * y1 + x0 + first) * UNIT;
+    f.o0 = __umul24(y0, pitch) + at;
+    f.o1 = __umul24(y1, pitch) + at;
     const float wx1 = fx * lw, wx0 = fmaf(-fx, lw, lw);
     f.w01 = wx0 * fy;
     f.w11 = wx1 * fy;
@@ -251,8 +253,14 @@ constexpr int kLayoutSplit = 0, kLayoutShared = 1, kLayoutPacked = 2;
 // z[3t + c] = T_t(u, v, s) channel c for the four pyramid slots (slots past
 // the material's pyramids repeat slot 0, or are zero; their MLP weights are zero).
 // kLayoutShared / kLayoutPacked: every slot has the same w, h, levels and
-// bias, so one footprint serves all four.
-template <int LAYOUT>
+// bias, so one footprint serves all four. IN_TURN (kLayoutSplit): a
+// footprint's two loads are blended before the next footprint's are issued;
+// otherwise they are issued as registers allow. An image's footprints share
+// lines, and the loads in flight hide the latency (1366 x 768 bf16 in turn
+// 24.9 us, free 23.1); scattered points share none, and more of them in flight
+// only evict each other (300,000 points of 2048 to 256 texels 29.4 us in turn,
+// 31.4 free), so launches that declare no image take them in turn.
+template <int LAYOUT, bool IN_TURN = true>
 __device__ __forceinline__ void filter4(__amdgpu_buffer_rsrc_t rs, const LevelLut &lut,
                                         const float *levels_bias, uint32_t stride, float u, float v,
                                         float s, float z[12])
@@ -283,7 +291,9 @@ __device__ __forceinline__ void filter4(__amdgpu_buffer_rsrc_t rs, const LevelLu
             const Footprint f0 = footprint(lut.e[t][ls.l0], uf, vf, 1.0f - ls.lam);
             const Footprint f1 = footprint(lut.e[t][ls.l1], uf, vf, ls.lam);
             gather(rs, f0, 0, z + 3 * t);
+            if (IN_TURN) __builtin_amdgcn_sched_barrier(0);
             gather(rs, f1, 0, z + 3 * t);
+            if (IN_TURN) __builtin_amdgcn_sched_barrier(0);
         }
     }
 }

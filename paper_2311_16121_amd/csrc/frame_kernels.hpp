@@ -52,10 +52,11 @@ struct FrameArgs {
     float *absmax;                         // k_calibrate: per-layer largest |input|
     // 2D work items: with grid_w > 0 the queries are image rows of grid_w and
     // a wave takes a tile of kTileW columns by kTileH rows (lane = row *
-    // kTileW + column); with 0, 64 consecutive queries.
+    // kTileW + column) of the image's `rows`; with 0, 64 consecutive queries.
     // row_rest: tile rows of this image can end in 1..3 floats that no 16-byte
     // chunk takes (its rows or its n * out_dim are no multiple of 4 floats)
-    uint32_t grid_w, tiles_x, n_items, row_rest;
+    uint32_t grid_w, rows, tiles_x, n_items, row_rest;
+    uint32_t tiles_x_inv, per_inv;    // divide_by's for tiles_x and strip_rows * tiles_x
     // tiled work: tiles_y rows of tiles; strip_rows > 0: the tile rows form
     // strips of that many, dealt to the XCDs in turn (0: items round-robin).
     // Linear work is laid out the same way, as rows of tiles_x items.
@@ -104,6 +105,20 @@ __device__ __forceinline__ WaveWork wave_work(const FrameArgs &a, uint32_t wv)
 struct ItemRange {
     uint32_t first, end, step;
 };
+
+// k / d and k % d from inv = (2^32 - 1) / d: the high product is the quotient
+// or one less. For scalars that is six scalar instructions, and a division's
+// float reciprocal is some fifteen vector ones and three moves between the files.
+__device__ __forceinline__ uint32_t divide_by(uint32_t k, uint32_t d, uint32_t inv, uint32_t &rem)
+{
+    uint32_t q = __umulhi(k, inv);
+    rem = k - q * d;
+    if (rem >= d) {
+        ++q;
+        rem -= d;
+    }
+    return q;
+}
 
 struct Query {
     float u, v, s;
@@ -217,10 +232,6 @@ __device__ __forceinline__ void mlp_stage(const float z[12], const MfmaMlp<K, H,
 #pragma unroll
     for (int grp = 0; grp < 4; ++grp) fin[grp] = feats[16 * grp + qi][g];
     wave_lds_sync();                      // feats and st share the wave's LDS
-    // lane (g, qi) holds outputs 4g .. 4g + 3 of its query; those past
-    // out_dim go to the stage's last float, which 64 rows of fewer than
-    // kMaxOut outputs never use (a select, not a branch per output)
-    constexpr uint32_t kSpare = 64 * kMaxOut - 1;
     float f[4][4];
 #pragma unroll
     for (int grp = 0; grp < 4; ++grp)
@@ -230,25 +241,27 @@ __device__ __forceinline__ void mlp_stage(const float z[12], const MfmaMlp<K, H,
     if (YIELD) __builtin_amdgcn_s_setprio(0);
     mlp.template run_groups<4>(f, o);
     if (YIELD) __builtin_amdgcn_s_setprio(3);
+    // lane (g, qi) holds outputs 4g .. 4g + 3 of its query in each group: the
+    // lanes that have output 4g + j write the four groups' under one mask (an
+    // address select per output and group was forty instructions per item)
+    float *row = st + qi * out_dim + 4 * g;
 #pragma unroll
-    for (int grp = 0; grp < 4; ++grp) {
-        const float4_t o4 = o[grp];
-        const uint32_t row = (16 * grp + qi) * out_dim;
+    for (int j = 0; j < 4; ++j)
+        if (4 * g + j < out_dim) {
 #pragma unroll
-        for (int j = 0; j < 4; ++j)
-            st[4 * g + j < out_dim ? row + 4 * g + j : kSpare] = o4[j];
-    }
+            for (int grp = 0; grp < 4; ++grp) row[16 * grp * out_dim + j] = o[grp][j];
+        }
     wave_lds_sync();
 }
 
 // One wave's 64 queries: filter (eqs. 9, 10), concatenate, MLP.
-template <bool YIELD, MlpKind K, int H, int NH, int LAYOUT>
+template <bool YIELD, MlpKind K, int H, int NH, int LAYOUT, bool IN_TURN = true>
 __device__ __forceinline__ void decode_wave(const Query &qq, __amdgpu_buffer_rsrc_t rs, const LevelLut &lut,
                                             const float *levels_bias, uint32_t stride,
                                             const MfmaMlp<K, H, NH> &mlp, float4_t (*feats)[4], float *st, uint32_t out_dim, uint32_t lane)
 {
     float z[12];
-    filter4<LAYOUT>(rs, lut, levels_bias, stride, qq.u, qq.v, qq.s, z);
+    filter4<LAYOUT, IN_TURN>(rs, lut, levels_bias, stride, qq.u, qq.v, qq.s, z);
     mlp_stage<YIELD, K, H, NH>(z, mlp, feats, st, out_dim, lane);
 }
 
@@ -285,77 +298,113 @@ __device__ __forceinline__ void store_run(const float4_t *stage, __amdgpu_buffer
     }
 }
 
-// Stores of one work item: always 4 buffer stores of 4 floats per lane, with
-// REST one more of 1, and no branches around them. Buffer stores ask for
-// dword alignment only, so neither the output nor its rows need a 16-byte
-// boundary: 1366 x 768 of 9 channels (fp16) 25.5 us with the 16 four-byte
-// stores per lane that such rows once took, 22.0 with these. An item's
-// output is a set of runs of contiguous floats: one run of 64 * out_dim for
-// linear items, one of kTileW * out_dim per tile row for tiled items. The
-// lanes of a run take its 4-float chunks in turn, and with REST its last
-// lim % 4 floats; a chunk with nowhere to go (past the run, the image's right
-// edge or the output's end) is sent to `oob`, the first byte past the output
-// buffer, which the buffer range check drops. Stores count in the same
+// How the items of a launch map to queries and outputs, known to the loop
+// when it is compiled: 64 consecutive queries, a tile of an image, or a tile
+// of an image with FrameArgs::row_rest.
+enum ItemKind { kItemLinear, kItemTile, kItemTileRest };
+
+// A wave's current item: its first query; tiles: the columns and rows that
+// the image has from there.
+struct Item {
+    uint32_t q0, cols, rows;
+};
+
+// What a lane adds to every item, so that an item costs its lanes a few
+// instructions and the rest scalar ones: its query's byte offset from the
+// item's first, and of the item's output its first float in the stage, the
+// same float's index in its run (below) and its byte offset from the first.
+struct LaneItem {
+    uint32_t query, stage, run, out;
+};
+
+template <ItemKind KIND>
+__device__ __forceinline__ LaneItem lane_item(const FrameArgs &a, uint32_t lane)
+{
+    if (KIND == kItemLinear) return LaneItem{12u * lane, 4u * lane, 4u * lane, 16u * lane};
+    const uint32_t r = lane >> kTileLog2, c = lane & (kTileW - 1u);
+    return LaneItem{12u * (r * a.grid_w + c), r * kTileW * a.out_dim + 4u * c, 4u * c,
+                    4u * (r * a.grid_w * a.out_dim + 4u * c)};
+}
+
+// The query of this lane in an item; past the image's right edge and past n
+// (below it) zeros, by the buffer range check.
+template <ItemKind KIND>
+__device__ __forceinline__ Query item_query(const FrameArgs &a, __amdgpu_buffer_rsrc_t rq, const Item &item,
+                                            const LaneItem &li, uint32_t lane)
+{
+    uint32_t at = 12u * item.q0 + li.query;
+    if (KIND != kItemLinear) at = (lane & (kTileW - 1u)) < item.cols ? at : 12u * a.n;
+    const auto qv = __builtin_amdgcn_raw_buffer_load_b96(rq, (int)at, 0, 0);
+    const uint32_t u = qv[0], v = qv[1], s = qv[2];
+    return Query{__builtin_bit_cast(float, u), __builtin_bit_cast(float, v), __builtin_bit_cast(float, s)};
+}
+
+// Stores of one work item: always 4 buffer stores of 4 floats per lane (tiles
+// with row_rest one more of 1), and no branches around them. Buffer stores
+// ask for dword alignment only, so neither the output nor its rows need a
+// 16-byte boundary: 1366 x 768 of 9 channels (fp16) 25.5 us with the 16
+// four-byte stores per lane that such rows once took, 22.0 with these. An
+// item's output is a set of runs of contiguous floats: one run of 64 *
+// out_dim for linear items, one of kTileW * out_dim per tile row for tiles.
+// The lanes of a run take its 4-float chunks in turn, and with row_rest its
+// last lim % 4 floats; a chunk with nowhere to go (past the run, the image's
+// right edge or the output's end) is sent to `oob`, the first byte past the
+// output buffer, which the buffer range check drops. Stores count in the same
 // in-order counter as loads; a fixed count lets the compiler wait for a load
 // issued before these stores without waiting for the stores themselves.
-template <bool REST>
+template <ItemKind KIND>
 __device__ __forceinline__ void store_item(const FrameArgs &a, uint32_t oob, const float *st,
-                                           __amdgpu_buffer_rsrc_t ro, uint32_t it, uint32_t row0, uint32_t col0,
+                                           __amdgpu_buffer_rsrc_t ro, const Item &item, const LaneItem &li,
                                            uint32_t lane)
 {
-    const uint32_t n_out = a.n * a.out_dim;
-    uint32_t e0, step, k0, base, lim;
-    if (!a.grid_w) {
-        base = it * 64u * a.out_dim;
-        lim = min(64u * a.out_dim, n_out - min(base, n_out));
-        e0 = 4u * lane;
-        step = 64u * 4u;
-        k0 = 0;
+    const uint32_t n_out = a.n * a.out_dim, base = item.q0 * a.out_dim, r = lane >> kTileLog2;
+    constexpr uint32_t step = KIND == kItemLinear ? 64u * 4u : kTileW * 4u;
+    uint32_t lim;                         // floats of the lane's run
+    if (KIND == kItemLinear) {
+        lim = min(64u * a.out_dim, n_out - base);
     } else {
-        const uint32_t r = lane >> kTileLog2;
-        base = ((row0 + r) * a.grid_w + col0) * a.out_dim;
-        lim = min(kTileW, a.grid_w - col0) * a.out_dim;
-        lim = min(lim, n_out - min(base, n_out));
-        e0 = 4u * (lane & (kTileW - 1u));
-        step = kTileW * 4u;
-        k0 = r * kTileW * a.out_dim;
+        lim = r < item.rows ? min(kTileW, item.cols) * a.out_dim : 0u;
+        // the last row may end early: its chunks past the output's end are
+        // dropped whole, and only with row_rest can one straddle it
+        if (KIND == kItemTileRest) {
+            const uint32_t first = base + r * a.grid_w * a.out_dim;
+            lim = min(lim, n_out - min(first, n_out));
+        }
     }
+    const uint32_t out = 4u * base + li.out;
 #pragma unroll
-    for (int m = 0; m < 4; ++m) {
-        const uint32_t e = e0 + step * m;
-        const float4_t v = *reinterpret_cast<const float4_t *>(st + k0 + e);
-        const int off = (int)(e + 3u < lim ? (base + e) * 4u : oob);
-        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(uint4_t, v), ro, off, 0, kStoreNT);
+    for (uint32_t m = 0; m < 4; ++m) {
+        const float4_t v = *reinterpret_cast<const float4_t *>(st + li.stage + step * m);
+        const uint32_t off = (li.run + step * m + 3u < lim ? out : oob) + 4u * step * m;
+        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(uint4_t, v), ro, (int)off, 0, kStoreNT);
     }
-    if constexpr (REST) {
-        const uint32_t e = (lim & ~3u) + (lane & (kTileW - 1u));
-        const int off = (int)(e < lim ? (base + e) * 4u : oob);
-        const float v = st[min(k0 + e, 64u * kMaxOut - 1u)];
-        __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, v), ro, off, 0, kStoreNT);
+    if (KIND == kItemTileRest) {
+        const uint32_t e = (lim & ~3u) + (lane & (kTileW - 1u)), k = li.stage - li.run + e;
+        const uint32_t off = e < lim ? out - 4u * li.run + 4u * e : oob;
+        const float v = st[min(k, 64u * kMaxOut - 1u)];
+        __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, v), ro, (int)off, 0, kStoreNT);
     }
 }
 
 // The last n * out_dim % 4 floats of a linear launch, which its 16-byte chunks
 // leave out, from the stage of the wave that took the last item (an item that
 // no other follows in its wave).
-__device__ __forceinline__ void store_rest(const FrameArgs &a, const float *st, __amdgpu_buffer_rsrc_t ro, uint32_t it,
-                                           uint32_t lane)
+__device__ __forceinline__ void store_rest(const FrameArgs &a, const float *st, __amdgpu_buffer_rsrc_t ro,
+                                           const Item &last, uint32_t lane)
 {
-    const uint32_t n_out = a.n * a.out_dim, rest = n_out & 3u;
-    if (a.grid_w || !rest || it != a.n_items - 1) return;
-    const uint32_t at = n_out - rest;
-    if (lane < rest)
-        __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, st[at + lane - it * 64u * a.out_dim]), ro,
-                                              (int)((at + lane) * 4u), 0, 0);
+    const uint32_t n_out = a.n * a.out_dim, rest = n_out & 3u, at = n_out - rest;
+    if (last.q0 + 64u < a.n || lane >= rest) return;
+    __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, st[at + lane - last.q0 * a.out_dim]), ro,
+                                          (int)((at + lane) * 4u), 0, 0);
 }
 
 // As many stores past the output's end: the loop's entry then has the same
 // stores outstanding as its back edge.
-template <bool REST>
+template <ItemKind KIND>
 __device__ __forceinline__ void store_dummies(__amdgpu_buffer_rsrc_t ro, uint32_t oob)
 {
 #pragma unroll
-    for (int m = 0; m < (REST ? 5 : 4); ++m) {
+    for (int m = 0; m < (KIND == kItemTileRest ? 5 : 4); ++m) {
         uint32_t o = oob;
         asm volatile("" : "+v"(o));           // separate stores, not merged into wider ones
         if (m < 4)
@@ -387,36 +436,25 @@ __global__ void __launch_bounds__(kFrameThreads) k_frame(FrameArgs a)
     const uint32_t oob = a.n * a.out_dim * 4u;
     const WaveWork w = wave_work(a, wv);
     if (w.first >= w.end) return;
-    // Item k of this wave's share: sets `it` (the linear item, or the tile
-    // row) and the tile's origin, and returns this lane's query; lanes outside
-    // the image or past n (also whole tiles of a strip below the image) read
-    // zeros (buffer range check) and their rows are not stored.
-    auto query_of = [&](uint32_t k, uint32_t &it, uint32_t &row0, uint32_t &col0) -> uint32_t {
-        uint32_t tr, tc;
-        if (w.per) {
-            const uint32_t j = k / w.per, rem = k - j * w.per;
-            tr = (j * kXcds + w.xcd) * a.strip_rows + rem / a.tiles_x;
-            tc = rem % a.tiles_x;
-        } else {
-            tr = k / a.tiles_x;
-            tc = k - tr * a.tiles_x;
-        }
-        if (!a.grid_w) {                  // linear work: rows of tiles_x items
-            it = tr * a.tiles_x + tc;
-            row0 = col0 = 0;
-            return it * 64 + lane;
-        }
-        it = tr;
-        row0 = tr * kTileH;
-        col0 = tc * kTileW;
-        const uint32_t col = col0 + (lane & (kTileW - 1u));
-        const uint32_t q = (row0 + (lane >> kTileLog2)) * a.grid_w + col;
-        return col < a.grid_w && q < a.n ? q : a.n;
-    };
     const ItemRange items{w.first, w.end, w.step};
-    auto run = [&](auto rest) {
-        constexpr bool REST = decltype(rest)::value;
-        uint32_t it = 0, row0, col0, i_, r_, c_;
+    auto run = [&](auto kind) {
+        constexpr ItemKind KIND = decltype(kind)::value;
+        const LaneItem li = lane_item<KIND>(a, lane);
+        // item k of this wave's share, all scalar
+        auto locate = [&](uint32_t k) -> Item {
+            uint32_t tr, tc;
+            if (w.per) {
+                uint32_t rem;
+                const uint32_t j = divide_by(k, w.per, a.per_inv, rem);
+                tr = (j * kXcds + w.xcd) * a.strip_rows + divide_by(rem, a.tiles_x, a.tiles_x_inv, tc);
+            } else {
+                tr = divide_by(k, a.tiles_x, a.tiles_x_inv, tc);
+            }
+            if (KIND == kItemLinear) return Item{64u * (tr * a.tiles_x + tc), 0, 0};   // rows of tiles_x items
+            return Item{tr * kTileH * a.grid_w + tc * kTileW, a.grid_w - tc * kTileW, a.rows - tr * kTileH};
+        };
+        auto query = [&](uint32_t k) { return item_query<KIND>(a, rq, locate(k), li, lane); };
+        Item item{0, 0, 0};
         if (LAYOUT != kLayoutSplit) {
             // Per item: blend its texels, run the MLP, issue the next item's
             // texel loads and the query after that, then store -- so the
@@ -431,41 +469,45 @@ __global__ void __launch_bounds__(kFrameThreads) k_frame(FrameArgs a)
                 else fetch4_shared(rs, lut, a.levels_bias, a.stride, q.u, q.v, q.s, t);
             };
             auto clamp_item = [&](uint32_t k) { return k < items.end ? k : items.first; };
-            const Query q0 = load_query(rq, query_of(items.first, i_, r_, c_));
+            const Query q0 = query(items.first);
             Taps taps;
             fetch(q0, taps);
-            Query qnext = load_query(rq, query_of(clamp_item(items.first + items.step), i_, r_, c_));
-            store_dummies<REST>(ro, oob);
+            Query qnext = query(clamp_item(items.first + items.step));
+            store_dummies<KIND>(ro, oob);
             for (uint32_t k = items.first; k < items.end; k += items.step) {
-                query_of(k, it, row0, col0);
+                item = locate(k);
                 float z[12];
                 if constexpr (LAYOUT == kLayoutPacked) filter_pending_packed(taps, z);
                 else filter_pending(taps, z);
                 mlp_stage<true, K, H, NH>(z, mlp, feats, st, a.out_dim, lane);
                 fetch(qnext, taps);
-                qnext = load_query(rq, query_of(clamp_item(k + 2 * items.step), i_, r_, c_));
-                store_item<REST>(a, oob, st, ro, it, row0, col0, lane);
+                qnext = query(clamp_item(k + 2 * items.step));
+                store_item<KIND>(a, oob, st, ro, item, li, lane);
                 wave_lds_sync();
             }
         } else {
-            // the next item's query is loaded while this item's texels are fetched
-            Query next = load_query(rq, query_of(items.first, i_, r_, c_));
+            // the next item's query is loaded while this item's texels are
+            // fetched; fetching texels ahead too costs registers and so waves:
+            // 1366 x 768 bf16 27.9 -> 28.0 us, 300,000 points 29.6 -> 42.5
+            Query next = query(items.first);
             for (uint32_t k = items.first; k < items.end; k += items.step) {
-                query_of(k, it, row0, col0);
+                item = locate(k);
                 const Query qq = next;
-                if (k + items.step < items.end) next = load_query(rq, query_of(k + items.step, i_, r_, c_));
-                decode_wave<true, K, H, NH, kLayoutSplit>(qq, rs, lut, a.levels_bias, a.stride, mlp, feats, st, a.out_dim,
-                                                    lane);
-                store_item<REST>(a, oob, st, ro, it, row0, col0, lane);
+                if (k + items.step < items.end) next = query(k + items.step);
+                decode_wave<true, K, H, NH, kLayoutSplit, KIND == kItemLinear>(
+                    qq, rs, lut, a.levels_bias, a.stride, mlp, feats, st, a.out_dim, lane);
+                store_item<KIND>(a, oob, st, ro, item, li, lane);
                 wave_lds_sync();
             }
         }
-        if constexpr (!REST) store_rest(a, st, ro, it, lane);
+        if constexpr (KIND == kItemLinear) store_rest(a, st, ro, item, lane);
     };
-    if (a.row_rest)
-        run(std::true_type());
+    if (!a.grid_w)
+        run(std::integral_constant<ItemKind, kItemLinear>());
+    else if (a.row_rest)
+        run(std::integral_constant<ItemKind, kItemTileRest>());
     else
-        run(std::false_type());
+        run(std::integral_constant<ItemKind, kItemTile>());
 }
 
 // The plain fp32 decode that records each layer's largest input magnitude

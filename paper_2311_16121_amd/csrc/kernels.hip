@@ -530,7 +530,7 @@ static FrameArgs frame_args(const MaterialDesc &m, const WsLayout &lay, const vo
             std::memcpy(&e.x, &fw, 4);
             std::memcpy(&e.y, &fh, 4);
             e.z = (w - 1) | ((h - 1) << 16);
-            e.w = T.tex_off[ll];
+            e.w = T.tex_off[ll] * (m.interleaved ? 24u : 8u);
             a.lut.e[t][l] = e;
         }
         const uint32_t lv = T.levels;
@@ -579,6 +579,9 @@ hipError_t launch_filter_mlp(const MaterialDesc &m, const MlpShape &sh, MlpKind 
     int layout;
     FrameArgs a = frame_args(m, lay, ws, sh.out, &layout);
     auto launch = [&]() -> hipError_t {
+        const uint32_t per = a.strip_rows * a.tiles_x;
+        a.tiles_x_inv = 0xFFFFFFFFu / a.tiles_x;
+        a.per_inv = per ? 0xFFFFFFFFu / per : 0;
         switch (kind) {
         case MLP_MFMA_F16: return launch_frame_f16(a, sh, layout, s);
         case MLP_MFMA_BF16: return launch_frame_bf16(a, sh, layout, s);
@@ -595,6 +598,7 @@ hipError_t launch_filter_mlp(const MaterialDesc &m, const MlpShape &sh, MlpKind 
         a.out = out;
         a.n = (uint32_t)n;
         a.grid_w = grid_width;
+        a.rows = rows;
         a.tiles_x = (grid_width + kTileW - 1) / kTileW;
         a.tiles_y = (rows + kTileH - 1) / kTileH;
         a.n_items = a.tiles_x * a.tiles_y;

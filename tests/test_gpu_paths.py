@@ -197,3 +197,18 @@ def test_pyramids_of_one_geometry_in_each_count(bcf, n_tex, size, levels):
     # z0's largest magnitude: one binary32 filter against binary64, so a few ulp
     absmax = bcf.calibrate(mats[0], dev(q)).cpu().numpy()
     assert abs(float(absmax[0]) - np.abs(oracle.sample(hosts[0], q)).max()) <= 1e-6
+
+
+@pytest.mark.parametrize("sizes", [[(64, 64), (32, 32), (16, 16), (8, 8)], [(64, 32)] * 2, [(32768, 4)], [(4, 32768)],
+                                   [(16384, 4)] * 3, [(4, 16384)] * 4])
+@pytest.mark.parametrize("n,grid,out_dim", [(1, 0, 2), (321, 0, 7), (40 * 21, 40, 8), (33 * 17 - 2, 33, 5),
+                                            (150 * 140, 150, 10)])
+def test_every_layout_under_every_item_kind(bcf, sizes, n, grid, out_dim):
+    """Runs of 64 queries, tiles and tiles with ragged rows over each texel
+    layout, up to the longest rows and columns a level may have."""
+    levels = [3] * len(sizes)
+    mat, host = material(bcf, sizes, levels, (3 * len(sizes), 16, out_dim), seed=150)
+    q = synth.uniform_queries(n, synth.rng(151), 2.0)
+    got = bcf.decode(mat, bcf.prepare(mat, bcf.Precision.FP32), dev(q), grid_width=grid).cpu().numpy()
+    pick = np.unique(np.linspace(0, n - 1, 1500).astype(int))
+    assert np.abs(got[pick] - oracle.decode(host, q[pick])).max() <= 1e-5
