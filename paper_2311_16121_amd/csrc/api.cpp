@@ -745,10 +745,10 @@ bcf_status bcf_decode_noalloc(const bcf_material *m, bcf_precision p, const floa
     hipStream_t s = static_cast<hipStream_t>(stream);
     const bcf::WsHeader header = ws_header(p, 1, material_hash(kFnvOffset, m, p), lay.scratch_off,
                                            lay.scratch_bytes, lay.total);
-    st = device_status(bcf::launch_prepare_weights(m->params, m->act_absmax, sh, kind, lay, ws, &header, s),
-                       "prepare launch");
+    st = device_status(bcf::launch_prepare_unpack(m->params, m->act_absmax, sh, kind, lay, ws, header, d,
+                                                  predecode_plan(d), scratch_of(ws, lay), s),
+                       "prepare and unpack launch");
     if (st != BCF_OK) return st;
-    if ((st = unpack(d, lay, ws, s)) != BCF_OK) return st;
     return device_status(bcf::launch_filter_mlp(d, sh, kind, lay, ws, queries, n, grid_width, out, s),
                          "decode launch");
 }

@@ -255,11 +255,13 @@ constexpr int kLayoutSplit = 0, kLayoutShared = 1, kLayoutPacked = 2;
 // kLayoutShared / kLayoutPacked: every slot has the same w, h, levels and
 // bias, so one footprint serves all four. IN_TURN (kLayoutSplit): a
 // footprint's two loads are blended before the next footprint's are issued;
-// otherwise they are issued as registers allow. An image's footprints share
-// lines, and the loads in flight hide the latency (1366 x 768 bf16 in turn
-// 24.9 us, free 23.1); scattered points share none, and more of them in flight
-// only evict each other (300,000 points of 2048 to 256 texels 29.4 us in turn,
-// 31.4 free), so launches that declare no image take them in turn.
+// otherwise they are loaded four footprints ahead. An image's footprints share
+// lines, and the loads in flight hide the latency (1366 x 768 bf16 24.9 us in
+// turn, 23.5 ahead; two ahead and the compiler's own order are within the noise
+// of that, but that order changed with code around it and then took 26.3);
+// scattered points share none, and more of them in flight only evict each
+// other (300,000 points of 2048 to 256 texels 29.4 us in turn, 31.4 ahead), so
+// launches that declare no image take them in turn.
 template <int LAYOUT, bool IN_TURN = true>
 __device__ __forceinline__ void filter4(__amdgpu_buffer_rsrc_t rs, const LevelLut &lut,
                                         const float *levels_bias, uint32_t stride, float u, float v,
@@ -284,16 +286,27 @@ __device__ __forceinline__ void filter4(__amdgpu_buffer_rsrc_t rs, const LevelLu
             gather(rs, f1, (uint32_t)t * stride, z + 3 * t);
         }
     } else {
+        // footprint k: level k % 2 of pyramid k / 2, loaded kAhead before it is blended
+        constexpr int kAhead = IN_TURN ? 0 : 4;
+        LevelSel ls;
+        Footprint f[kAhead + 1];
+        texel_pair r[kAhead + 1][2];
 #pragma unroll
-        for (int t = 0; t < kMaxTextures; ++t) {
-            const LevelSel ls = select_levels(s, levels_bias[2 * t + 1],
-                                              __builtin_bit_cast(uint32_t, levels_bias[2 * t]));
-            const Footprint f0 = footprint(lut.e[t][ls.l0], uf, vf, 1.0f - ls.lam);
-            const Footprint f1 = footprint(lut.e[t][ls.l1], uf, vf, ls.lam);
-            gather(rs, f0, 0, z + 3 * t);
-            if (IN_TURN) __builtin_amdgcn_sched_barrier(0);
-            gather(rs, f1, 0, z + 3 * t);
-            if (IN_TURN) __builtin_amdgcn_sched_barrier(0);
+        for (int k = -kAhead; k < 2 * kMaxTextures; ++k) {
+            const int n = k + kAhead;
+            if (n < 2 * kMaxTextures) {
+                const int t = n >> 1, b = n % (kAhead + 1);
+                if (!(n & 1))
+                    ls = select_levels(s, levels_bias[2 * t + 1], __builtin_bit_cast(uint32_t, levels_bias[2 * t]));
+                f[b] = footprint(lut.e[t][n & 1 ? ls.l1 : ls.l0], uf, vf, n & 1 ? ls.lam : 1.0f - ls.lam);
+                r[b][0] = __builtin_amdgcn_raw_buffer_load_b128(rs, (int)f[b].o0, 0, 0);
+                r[b][1] = __builtin_amdgcn_raw_buffer_load_b128(rs, (int)f[b].o1, 0, 0);
+            }
+            if (k < 0) continue;
+            const int b = k % (kAhead + 1);
+            if (!IN_TURN) __builtin_amdgcn_sched_barrier(0);
+            blend(f[b], r[b][0], r[b][1], z + 3 * (k >> 1));
+            __builtin_amdgcn_sched_barrier(0);
         }
     }
 }

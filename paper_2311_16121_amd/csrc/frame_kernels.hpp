@@ -420,7 +420,11 @@ __global__ void __launch_bounds__(kFrameThreads) k_frame(FrameArgs a)
     __shared__ LevelLut lut;
     // per wave 4 KB: the feature vectors, then the staged output rows
     __shared__ float4_t stage[kFrameWaves][64 * kMaxOut / 4];
-    copy_lut(a.lut, lut);
+    // A small launch is a chain of memory latencies: the table's entries, the
+    // weights and the first queries are all on their way before the first wait.
+    static_assert(kMaxTextures * kMaxLevels <= kFrameThreads, "one table entry per thread");
+    uint4 entry;
+    if (threadIdx.x < kMaxTextures * kMaxLevels) entry = (&a.lut.e[0][0])[threadIdx.x];
 
     // the wave index is uniform across the wave: say so, so that everything
     // derived from it (work items, materials, offsets) lives in SGPRs
@@ -435,7 +439,12 @@ __global__ void __launch_bounds__(kFrameThreads) k_frame(FrameArgs a)
 
     const uint32_t oob = a.n * a.out_dim * 4u;
     const WaveWork w = wave_work(a, wv);
-    if (w.first >= w.end) return;
+    // the table to LDS; a wave without items only helps with that
+    auto have_items = [&]() {
+        if (threadIdx.x < kMaxTextures * kMaxLevels) (&lut.e[0][0])[threadIdx.x] = entry;
+        __syncthreads();
+        return w.first < w.end;
+    };
     const ItemRange items{w.first, w.end, w.step};
     auto run = [&](auto kind) {
         constexpr ItemKind KIND = decltype(kind)::value;
@@ -455,6 +464,8 @@ __global__ void __launch_bounds__(kFrameThreads) k_frame(FrameArgs a)
         };
         auto query = [&](uint32_t k) { return item_query<KIND>(a, rq, locate(k), li, lane); };
         Item item{0, 0, 0};
+        const Query q0 = query(w.first < w.end ? w.first : 0);
+        if (!have_items()) return;
         if (LAYOUT != kLayoutSplit) {
             // Per item: blend its texels, run the MLP, issue the next item's
             // texel loads and the query after that, then store -- so the
@@ -469,7 +480,6 @@ __global__ void __launch_bounds__(kFrameThreads) k_frame(FrameArgs a)
                 else fetch4_shared(rs, lut, a.levels_bias, a.stride, q.u, q.v, q.s, t);
             };
             auto clamp_item = [&](uint32_t k) { return k < items.end ? k : items.first; };
-            const Query q0 = query(items.first);
             Taps taps;
             fetch(q0, taps);
             Query qnext = query(clamp_item(items.first + items.step));
@@ -489,7 +499,7 @@ __global__ void __launch_bounds__(kFrameThreads) k_frame(FrameArgs a)
             // the next item's query is loaded while this item's texels are
             // fetched; fetching texels ahead too costs registers and so waves:
             // 1366 x 768 bf16 27.9 -> 28.0 us, 300,000 points 29.6 -> 42.5
-            Query next = query(items.first);
+            Query next = q0;
             for (uint32_t k = items.first; k < items.end; k += items.step) {
                 item = locate(k);
                 const Query qq = next;

@@ -130,6 +130,10 @@ constexpr uint32_t kWsMagic = 0x57464342u;   // "BCFW"
 hipError_t launch_prepare_weights(const float *params, const float *act_absmax, const MlpShape &sh,
                                   MlpKind kind, const WsLayout &lay, void *ws, const WsHeader *header,
                                   hipStream_t s);
+// launch_prepare_weights and launch_predecode, in one launch where the operands allow
+hipError_t launch_prepare_unpack(const float *params, const float *act_absmax, const MlpShape &sh, MlpKind kind,
+                                 const WsLayout &lay, void *ws, const WsHeader &header, const MaterialDesc &m,
+                                 const PredecodePlan &p, uint2 *texels, hipStream_t s);
 
 hipError_t launch_calibrate(const MaterialDesc &m, const MlpShape &sh, const WsLayout &lay, const void *ws,
                             const float *queries, size_t n, float *absmax, hipStream_t s);

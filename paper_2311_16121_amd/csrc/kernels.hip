@@ -93,10 +93,17 @@ hipError_t launch_decode_blocks(const uint4 *blocks, size_t n, uint32_t is_signe
 // ---------------------------------------------------------------------------
 // every block -> texel scratch (layout in filter_device.hpp)
 
+// One segment of a single material's unpack, as its kernel reads it: 16 bytes
+// a lane. geom = log2(lw) | log2(lh) << 8 | pyramid << 16.
+struct MaterialSeg {
+    uint32_t wg0, blk_off, texel_off, geom;      // first workgroup, block and 8-byte unit of the scratch
+};
+
 struct PredecodeArgs {
-    MaterialDesc m;
-    PredecodePlan p;
+    MaterialSeg seg[kMaxTextures * kMaxLevels];  // past n_seg: unused
+    const uint4 *blocks[kMaxTextures];           // of each pyramid slot (slots past the pyramids: slot 0)
     uint2 *texels;
+    uint32_t n_seg, interleaved;
 };
 
 // One chunk (256 lanes) of one unpack segment into the texel scratch. The
@@ -193,23 +200,31 @@ __device__ __forceinline__ void unpack_chunk(const UnpackSeg &sg, uint32_t chunk
     }
 }
 
-// The unpack segment of (pyramid or interleaved slot set, level) of a single
-// material's plan entry `seg`.
-__device__ __forceinline__ UnpackSeg material_seg(const PredecodeArgs &a, uint32_t seg)
+// The unpack segment that workgroup wg of a single material's unpack works on.
+// Lane i holds segment i, so finding the last one that starts at or before wg
+// and reading it are a ballot and four lane reads behind one load: a scan of
+// the arguments by scalar loads, each waiting for the one before, was half the
+// time of a small unpack (four 64 x 64 pyramids 6.3 -> 4.9 us).
+__device__ __forceinline__ UnpackSeg material_seg(const PredecodeArgs &a, uint32_t wg)
 {
-    const uint32_t l = a.p.seg_lvl[seg];
-    const uint32_t il = a.m.interleaved;
+    static_assert(kMaxTextures * kMaxLevels <= 64, "one segment per lane");
+    const uint32_t lane = threadIdx.x & 63u;
+    const MaterialSeg mine = a.seg[lane];
+    const uint32_t k = (uint32_t)__popcll(__ballot(lane < a.n_seg && mine.wg0 <= wg)) - 1u;
+    auto field = [&](uint32_t v) { return (uint32_t)__builtin_amdgcn_readlane((int)v, (int)k); };
+    const uint32_t geom = field(mine.geom), blk = field(mine.blk_off), il = a.interleaved;
+    const uint32_t tex = geom >> 16;
     UnpackSeg sg;
-    for (uint32_t t = 0; t < (uint32_t)kMaxTextures; ++t) {
-        const TexDesc &T = a.m.tex[il ? (t < a.m.n_tex ? t : 0u) : a.p.seg_tex[seg]];
-        sg.blocks[t] = T.blocks + T.blk_off[l];
-    }
-    const TexDesc &T0 = a.m.tex[il ? 0u : a.p.seg_tex[seg]];
-    sg.lw = max(T0.w >> l, 1u);
-    sg.lh = max(T0.h >> l, 1u);
-    // 8-byte units per position: 3 packed, 1 per pyramid
-    sg.texels = a.texels + (il ? 3u : 1u) * (size_t)T0.tex_off[l];
-    sg.wg0 = a.p.seg_wg[seg];
+    const uint4 *first = tex == 0 ? a.blocks[0] : tex == 1 ? a.blocks[1] : tex == 2 ? a.blocks[2] : a.blocks[3];
+    // pyramids of one geometry: their levels start at the same block
+    sg.blocks[0] = first + blk;
+    sg.blocks[1] = a.blocks[1] + blk;
+    sg.blocks[2] = a.blocks[2] + blk;
+    sg.blocks[3] = a.blocks[3] + blk;
+    sg.lw = 1u << (geom & 0xFFu);
+    sg.lh = 1u << ((geom >> 8) & 0xFFu);
+    sg.texels = a.texels + field(mine.texel_off);
+    sg.wg0 = field(mine.wg0);
     sg.flags = il ? kSegInterleaved : 0u;
     return sg;
 }
@@ -222,13 +237,9 @@ __global__ void __launch_bounds__(256) k_predecode(PredecodeArgs a)
     // consecutive 8-byte slots across lanes, and its 16 four-bit slots
     __shared__ uint2 palette[16][256];
     __shared__ uint2 slots[256];
+    const UnpackSeg sg = material_seg(a, blockIdx.x);
     load_table(table);
-    // segment of this workgroup (uniform scan over at most 64 entries)
-    const uint32_t wg = blockIdx.x;
-    uint32_t seg = 0;
-    while (seg + 1 < a.p.n_seg && a.p.seg_wg[seg + 1] <= wg) ++seg;
-    const UnpackSeg sg = material_seg(a, seg);
-    unpack_chunk<SIGNED, false>(sg, wg - sg.wg0, table, palette, slots);
+    unpack_chunk<SIGNED, false>(sg, blockIdx.x - sg.wg0, table, palette, slots);
 }
 
 // Every material of a batch in one launch: workgroup c unpacks chunk c of
@@ -326,11 +337,29 @@ hipError_t launch_predecode_batch(const UnpackSeg *segs, const uint32_t *chunk_s
     return hipGetLastError();
 }
 
+static PredecodeArgs predecode_args(const MaterialDesc &m, const PredecodePlan &p, uint2 *texels)
+{
+    PredecodeArgs a;
+    std::memset(&a, 0, sizeof a);
+    for (uint32_t j = 0; j < p.n_seg; ++j) {
+        const uint32_t t = p.seg_tex[j], l = p.seg_lvl[j];
+        const TexDesc &T = m.tex[t];
+        const uint32_t lw = std::max(T.w >> l, 1u), lh = std::max(T.h >> l, 1u);
+        a.seg[j] = MaterialSeg{p.seg_wg[j], T.blk_off[l], (m.interleaved ? 3u : 1u) * T.tex_off[l],
+                               (uint32_t)__builtin_ctz(lw) | (uint32_t)__builtin_ctz(lh) << 8 | t << 16};
+    }
+    for (uint32_t t = 0; t < (uint32_t)kMaxTextures; ++t) a.blocks[t] = m.tex[t < m.n_tex ? t : 0].blocks;
+    a.texels = texels;
+    a.n_seg = p.n_seg;
+    a.interleaved = m.interleaved;
+    return a;
+}
+
 hipError_t launch_predecode(const MaterialDesc &m, const PredecodePlan &p, uint2 *texels, hipStream_t s)
 {
-    PredecodeArgs a{m, p, texels};
     const unsigned grid = p.seg_wg[p.n_seg];
     if (grid == 0) return hipSuccess;
+    const PredecodeArgs a = predecode_args(m, p, texels);
     if (m.is_signed) k_predecode<true><<<grid, 256, 0, s>>>(a);
     else k_predecode<false><<<grid, 256, 0, s>>>(a);
     return hipGetLastError();
@@ -444,18 +473,23 @@ __global__ void __launch_bounds__(256) k_fp8_scales(PrepareArgs a)
     }
 }
 
-__global__ void k_prepare(PrepareArgs a)
+// Workgroup `block` of kPrepareBlocks: operands and bias of layer block % 4,
+// each layer by workgroups of its own, so that its loads do not wait for the
+// layers before (three layers, first run 6.4 -> 4.0 us).
+constexpr uint32_t kPrepareBlocks = 16 * 4;
+
+__device__ __forceinline__ void prepare_weights(const PrepareArgs &a, uint32_t block)
 {
-    const uint32_t tid = blockIdx.x * blockDim.x + threadIdx.x;
-    const uint32_t stride = gridDim.x * blockDim.x;
-    const uint32_t L = a.sh.n_hidden + 1;
+    const uint32_t tid = (block / 4) * blockDim.x + threadIdx.x;
+    const uint32_t stride = kPrepareBlocks / 4 * blockDim.x;
     const float *sc = reinterpret_cast<const float *>(a.ws + a.lay.scales_off);
-    for (uint32_t l = 0; l < L; ++l) {
-        const size_t ne = layer_elems(a.sh, l, a.kind);
+    const uint32_t l = block % 4;
+    if (l <= a.sh.n_hidden) {
+        const uint32_t ne = (uint32_t)layer_elems(a.sh, l, a.kind);    // at most 64 x 64
         const uint32_t rows = layer_out(a.sh, l, a.kind);
         uint8_t *wdst = a.ws + a.lay.layer_w_off[l];
         float *bdst = reinterpret_cast<float *>(a.ws + a.lay.layer_b_off[l]);
-        for (size_t e = tid; e < ne; e += stride) {
+        for (uint32_t e = tid; e < ne; e += stride) {
             float v;
             if (a.kind == MLP_VALU_F32) {
                 const uint32_t cols = layer_in(a.sh, l);
@@ -466,7 +500,7 @@ __global__ void k_prepare(PrepareArgs a)
                 const uint32_t p = e % P;
                 const uint32_t lane = (e / P) % 64;
                 const uint32_t kc = (e / (P * 64)) % KC;
-                const uint32_t mb = e / ((size_t)P * 64 * KC);
+                const uint32_t mb = e / (P * 64 * KC);
                 const int in = mfma_in_unit(l, a.kind, kc, lane / 16, p);
                 v = param_w(a, l, (int)(16 * mb + lane % 16), in);
             }
@@ -482,7 +516,27 @@ __global__ void k_prepare(PrepareArgs a)
         }
         for (uint32_t o = tid; o < rows; o += stride) bdst[o] = param_b(a, l, o);
     }
-    if (a.write_header && tid == 0) *reinterpret_cast<WsHeader *>(a.ws) = a.header;
+    if (a.write_header && block == 0 && tid == 0) *reinterpret_cast<WsHeader *>(a.ws) = a.header;
+}
+
+__global__ void __launch_bounds__(256) k_prepare(PrepareArgs a) { prepare_weights(a, blockIdx.x); }
+
+// The unpack and the operands of a call that needs both, in one launch: the
+// workgroups past the unpack's convert the weights (501 queries without a
+// caller's workspace, where three launches were the cost: 17.8 -> 13.5 us).
+template <bool SIGNED>
+__global__ void __launch_bounds__(256) k_predecode_prepare(PredecodeArgs a, PrepareArgs w, uint32_t unpack_blocks)
+{
+    __shared__ uint32_t table[kTableWords];
+    __shared__ uint2 palette[16][256];
+    __shared__ uint2 slots[256];
+    if (blockIdx.x >= unpack_blocks) {
+        prepare_weights(w, blockIdx.x - unpack_blocks);
+        return;
+    }
+    const UnpackSeg sg = material_seg(a, blockIdx.x);
+    load_table(table);
+    unpack_chunk<SIGNED, false>(sg, blockIdx.x - sg.wg0, table, palette, slots);
 }
 
 hipError_t launch_prepare_weights(const float *params, const float *act_absmax, const MlpShape &sh,
@@ -499,7 +553,23 @@ hipError_t launch_prepare_weights(const float *params, const float *act_absmax, 
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
-    k_prepare<<<16, 256, 0, s>>>(a);
+    k_prepare<<<kPrepareBlocks, 256, 0, s>>>(a);
+    return hipGetLastError();
+}
+
+hipError_t launch_prepare_unpack(const float *params, const float *act_absmax, const MlpShape &sh, MlpKind kind,
+                                 const WsLayout &lay, void *ws, const WsHeader &header, const MaterialDesc &m,
+                                 const PredecodePlan &p, uint2 *texels, hipStream_t s)
+{
+    if (kind == MLP_MFMA_FP8) {                 // the operands need the scales first
+        const hipError_t e = launch_prepare_weights(params, act_absmax, sh, kind, lay, ws, &header, s);
+        return e == hipSuccess ? launch_predecode(m, p, texels, s) : e;
+    }
+    const PrepareArgs w{params, act_absmax, sh, kind, lay, static_cast<uint8_t *>(ws), header, 1u};
+    const PredecodeArgs a = predecode_args(m, p, texels);
+    const uint32_t unpack = p.seg_wg[p.n_seg];
+    if (m.is_signed) k_predecode_prepare<true><<<unpack + kPrepareBlocks, 256, 0, s>>>(a, w, unpack);
+    else k_predecode_prepare<false><<<unpack + kPrepareBlocks, 256, 0, s>>>(a, w, unpack);
     return hipGetLastError();
 }
 

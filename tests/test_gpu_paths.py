@@ -212,3 +212,18 @@ def test_every_layout_under_every_item_kind(bcf, sizes, n, grid, out_dim):
     got = bcf.decode(mat, bcf.prepare(mat, bcf.Precision.FP32), dev(q), grid_width=grid).cpu().numpy()
     pick = np.unique(np.linspace(0, n - 1, 1500).astype(int))
     assert np.abs(got[pick] - oracle.decode(host, q[pick])).max() <= 1e-5
+
+
+@pytest.mark.parametrize("precision", ["FP32", "FP16", "BF16", "FP8"])
+@pytest.mark.parametrize("sizes,dims,signed", [([(64, 64)] * 4, (12, 16, 1), False), ([(8, 4)], (3, 64, 64, 64, 16), True),
+                                               ([(64, 32), (16, 16)], (6, 33, 24, 7), True)])
+def test_decode_without_a_workspace_equals_one_with(bcf, precision, sizes, dims, signed):
+    """The launch that unpacks and converts the operands together, against
+    bcf_prepare and bcf_decode, bit for bit."""
+    p = bcf.Precision[precision]
+    mat, _ = material(bcf, sizes, [max(s).bit_length() for s in sizes], dims, seed=160, signed=signed)
+    q = dev(synth.uniform_queries(300, synth.rng(161), 4.0))
+    if precision == "FP8":
+        mat.set_act_absmax(bcf.calibrate(mat, q))
+    want = bcf.decode(mat, bcf.prepare(mat, p), q, p)
+    assert torch.equal(bcf.decode_noalloc(mat, q, p).view(torch.int32), want.view(torch.int32))
