@@ -327,10 +327,11 @@ typedef struct {
 } bcf_train_material;
 
 /* Device workspace bytes (256-byte aligned start) for the training calls
- * on this material: at most 28 bytes per texel (values and gradients), then 20 MiB +
- * 32 KiB and 16 MiB per pyramid in which the backward sorts its samples by
- * position and keeps dL/d feature per sample (2^20 samples at a time), then
- * the forward's MLP operands in the matrix-core layout (a few KiB). */
+ * on this material: 32 bytes per texel and 52 MiB + 32 KiB, which hold the
+ * texel values, their gradients, and the samples that the backward sorts by
+ * position with their dL/d feature (as many at a time as there is room for,
+ * 548,000 to 2^20), then the forward's MLP operands in the matrix-core layout
+ * (a few KiB). */
 bcf_status bcf_train_workspace_size(const bcf_train_material *m, size_t *ws_bytes);
 
 /* G(u, v, s) for n queries (device [n][3]) into out (device [n][dims[n_layers]]),

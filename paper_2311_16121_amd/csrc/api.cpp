@@ -478,10 +478,16 @@ bcf_status describe_train(const bcf_train_material *m, bcf::TrainDesc *d, size_t
         pos *= d->ste ? 24 : 48;
         if (pos <= ((size_t)1 << 31)) d->packed_bytes = (uint32_t)pos;
     }
-    const size_t sort_end = train_values_bytes(*d) + align_up(texels * 12, 256) +
-                            align_up((size_t)bcf::kTrainBinBatch * 4, 256) +
-                            2 * align_up((size_t)bcf::kTrainBins * 4, 256) +
-                            (size_t)bcf::kTrainBinBatch * 16 * (1 + d->n_tex);
+    // 32 bytes a texel and 52 a sample of a full batch. The texel values and
+    // gradients take 18 to 28 of the former (more only where levels are at most
+    // 4 texels wide), a sample 20 bytes and 16 per pyramid: four pyramids of 512
+    // or less have room for 650,000 to 880,000 samples a batch, larger ones and
+    // fewer pyramids for a full one.
+    const size_t sort_end = 2 * align_up(unpadded * 16, 256) + (size_t)bcf::kTrainBinBatch * 52 +
+                            2 * align_up((size_t)bcf::kTrainBins * 4, 256);
+    const size_t samples = (sort_end - train_values_bytes(*d) - align_up(texels * 12, 256) -
+                            2 * align_up((size_t)bcf::kTrainBins * 4, 256)) / (4 + 16 * (1 + d->n_tex));
+    d->bin_batch = (uint32_t)std::min<size_t>(samples, bcf::kTrainBinBatch) & ~63u;
     d->ops = weights_layout(sh, bcf::MLP_MFMA_F32, align_up(sort_end, 256));
     *ws_bytes = d->ops.total;
     return BCF_OK;
@@ -499,13 +505,13 @@ bcf_status bind_train_ws(bcf::TrainDesc *d, void *ws)
     d->g_texels = reinterpret_cast<float *>(p);
     p += align_up((size_t)d->n_texels * 12, 256);
     d->bin_perm = reinterpret_cast<uint32_t *>(p);
-    p += align_up((size_t)bcf::kTrainBinBatch * 4, 256);
+    p += (size_t)d->bin_batch * 4;
     d->bin_count = reinterpret_cast<uint32_t *>(p);
     p += align_up((size_t)bcf::kTrainBins * 4, 256);
     d->bin_next = reinterpret_cast<uint32_t *>(p);
     p += align_up((size_t)bcf::kTrainBins * 4, 256);
     d->bin_q = reinterpret_cast<float4 *>(p);
-    p += (size_t)bcf::kTrainBinBatch * 16;
+    p += (size_t)d->bin_batch * 16;
     d->bin_dz = reinterpret_cast<float4 *>(p);
     d->ops_ws = static_cast<uint8_t *>(ws);
     return BCF_OK;

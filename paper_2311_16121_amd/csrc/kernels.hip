@@ -522,7 +522,7 @@ __device__ __forceinline__ void prepare_weights(const PrepareArgs &a, uint32_t b
 __global__ void __launch_bounds__(256) k_prepare(PrepareArgs a) { prepare_weights(a, blockIdx.x); }
 
 // The unpack and the operands of a call that needs both, in one launch: the
-// workgroups past the unpack's convert the weights (501 queries without a
+// workgroups past the unpack's convert the weights (65,536 queries without a
 // caller's workspace, where three launches were the cost: 17.8 -> 13.5 us).
 template <bool SIGNED>
 __global__ void __launch_bounds__(256) k_predecode_prepare(PredecodeArgs a, PrepareArgs w, uint32_t unpack_blocks)

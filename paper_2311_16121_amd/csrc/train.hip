@@ -1035,7 +1035,7 @@ __global__ void __launch_bounds__(64 * kBwdWaves, 2) k_train_backward(TrainDesc 
                 dz = mma4(ops.b0[kq][lane], x, dz);
             }
             const uint32_t to = ch * 64u + row;
-            if (g < d.n_tex && to < n) *reinterpret_cast<f32x4 *>(d.bin_dz + (size_t)g * kTrainBinBatch + to) = dz;
+            if (g < d.n_tex && to < n) *reinterpret_cast<f32x4 *>(d.bin_dz + (size_t)g * d.bin_batch + to) = dz;
             wave_sync_lds();
         }
     }
@@ -1110,7 +1110,7 @@ __global__ void __launch_bounds__(kScatterThreads) k_train_scatter(TrainDesc d, 
     const TrainTexDesc &tx = d.tex[t];
     const uint32_t levels = tx.levels;
     const float bias = tx.bias;
-    const float4 *dzs = d.bin_dz + (size_t)t * kTrainBinBatch;
+    const float4 *dzs = d.bin_dz + (size_t)t * d.bin_batch;
     if (threadIdx.x < 64u) {
         // lane i: level 15 - i, the coarsest first; the pool goes to a prefix
         const uint32_t i = threadIdx.x, l = (kMaxLevels - 1u - i) & (kMaxLevels - 1u);
@@ -1361,8 +1361,11 @@ hipError_t launch_train_backward(const TrainDesc &d, const float *queries, size_
         }
         pool_sums = std::max(pool_sums, sums);
     }
-    for (size_t off = 0; off < n; off += kTrainBinBatch) {
-        const uint32_t m = (uint32_t)std::min(n - off, (size_t)kTrainBinBatch);
+    // batches of one size
+    const size_t batches = (n + d.bin_batch - 1) / d.bin_batch;
+    const size_t batch = batches ? ((n + batches - 1) / batches + 63u) & ~(size_t)63u : 1;
+    for (size_t off = 0; off < n; off += batch) {
+        const uint32_t m = (uint32_t)std::min(n - off, batch);
         const float *q = queries + 3 * off;
         const uint32_t per = bin_per_thread(m);
         const unsigned bins = (m + per * kBinThreads - 1) / (per * kBinThreads);

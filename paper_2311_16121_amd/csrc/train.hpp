@@ -11,8 +11,8 @@
 
 namespace bcf {
 
-// The backward takes its samples in spatial order: per call of at most
-// kTrainBinBatch samples, a counting sort by cell of a kTrainBinSide^2 grid
+// The backward takes its samples in spatial order: per batch of at most
+// kTrainBinBatch samples (TrainDesc::bin_batch), a counting sort by cell of a kTrainBinSide^2 grid
 // over the wrapped (u, v), the cells numbered along a Z-order curve.
 constexpr uint32_t kTrainBinBatch = 1u << 20;
 constexpr uint32_t kTrainBinSide = 64;
@@ -62,9 +62,10 @@ struct TrainDesc {
     // the backward's sample sort (workspace): sorted sample indices, per-cell
     // counts, per-cell next free slot (after the sort: the end of the cell's
     // run), and per sorted sample its query (u, v, s, 0) and, per pyramid
-    // (kTrainBinBatch apart), dL/dz (r, g, b, 0)
+    // (bin_batch apart), dL/dz (r, g, b, 0)
     uint32_t *bin_perm, *bin_count, *bin_next;
     float4 *bin_q, *bin_dz;
+    uint32_t bin_batch;            // samples of a batch that the workspace has room for
 };
 
 hipError_t launch_train_forward(const TrainDesc &d, const float *queries, size_t n, float *out,

@@ -227,3 +227,29 @@ def test_decode_without_a_workspace_equals_one_with(bcf, precision, sizes, dims,
         mat.set_act_absmax(bcf.calibrate(mat, q))
     want = bcf.decode(mat, bcf.prepare(mat, p), q, p)
     assert torch.equal(bcf.decode_noalloc(mat, q, p).view(torch.int32), want.view(torch.int32))
+
+
+def test_training_backward_in_batches_equals_its_parts(bcf):
+    """More samples than the workspace of a small material sorts at once: the
+    gradients are the sums of two calls' that each fit one batch."""
+    sizes, levels, dims, n = [(32, 32)] * 4, [6] * 4, (12, 16, 4), 700_003
+    g = torch.Generator("cuda").manual_seed(170)
+    blocks = [sum(max((s >> l) // 4, 1) ** 2 for l in range(6)) for s, _ in sizes]
+    ends = [60.0 * torch.rand((b, 4, 3), device="cuda", generator=g) for b in blocks]
+    idxs = [torch.rand((b, 16), device="cuda", generator=g) for b in blocks]
+    parts = [torch.randint(0, 32, (b,), device="cuda", generator=g, dtype=torch.uint8) for b in blocks]
+    n_par = sum(a * b + b for a, b in zip(dims[:-1], dims[1:]))
+    params = torch.randn(n_par, device="cuda", generator=g) * 0.3
+    q = torch.rand((n, 3), device="cuda", generator=g) * torch.tensor([1.0, 1.0, 5.0], device="cuda")
+    go = torch.rand((n, 4), device="cuda", generator=g)
+    geo = bcf.TrainGeometry(sizes, levels, parts, dims)
+
+    def flat(r):
+        return [t.double() for t in r[0] + r[1] + [r[2]]]
+
+    whole = flat(bcf.train_backward(geo, ends, idxs, params, q, go))
+    halves = [flat(bcf.train_backward(geo, ends, idxs, params, q[s], go[s]))
+              for s in (slice(0, 350_000), slice(350_000, n))]
+    for w, a, b in zip(whole, *halves):
+        # fp32 sums of some hundred partial sums each way, in any order
+        assert float((w - a - b).abs().max()) <= 1e-3 * float(w.abs().max()) + 1e-12
