@@ -574,7 +574,7 @@ struct BatchArgs {
     const uint8_t *ws;
     const BatchMat *mats;                  // [n_mats], in the workspace
     const uint32_t *offsets;               // caller's [n_mats + 1] first query of each material
-    uint32_t *items;                       // [n_mats + 1] first item of each material (k_batch_items)
+    uint32_t *items;                       // [n_mats + 1] first item of each material (BatchItems: past 64)
     WsLayout lay;                          // weight layout relative to a material's weights_off
     const float *queries;
     float *out;
@@ -592,6 +592,77 @@ __device__ __forceinline__ void batch_range(const BatchArgs &a, uint32_t k, uint
     cnt = min(q1 - q0, (uint32_t)kMaxQueriesPerLaunch);
 }
 
+// The work items of a batch as a wave sees them: which material an item
+// belongs to, and a material's queries and first items. Up to 64 materials,
+// lane k holds material k and every wave adds the prefix up by itself, so
+// there is no launch for it and finding an item's material is a ballot; more
+// are read from BatchArgs::items (k_batch_items), by binary search. Two
+// materials of some thousand queries, with their unpack: 25.2 -> 21.0 us; eight
+// with the touched blocks' 88.7 -> 84.1; 24 of 5.5 million 455.5 -> 454.9.
+constexpr uint32_t kWaveItems = 64;
+
+struct BatchItems {
+    const BatchArgs &a;
+    bool held;                             // in lanes
+    uint32_t start, q0, cnt, total;        // held: of this lane's material; start = total past n_mats
+
+    __device__ __forceinline__ BatchItems(const BatchArgs &args, uint32_t lane)
+        : a(args), held(args.n_mats <= kWaveItems), start(0), q0(0), cnt(0), total(0)
+    {
+        if (!held) {
+            total = uniform(a.items[a.n_mats]);
+            return;
+        }
+        if (lane < a.n_mats) batch_range(a, lane, q0, cnt);
+        const uint32_t n = (cnt + 63u) / 64u;
+        uint32_t v = n;                    // inclusive scan across the wave
+#pragma unroll
+        for (int d = 1; d < 64; d <<= 1) {
+            const uint32_t t = __shfl_up(v, d);
+            if (lane >= (uint32_t)d) v += t;
+        }
+        start = v - n;
+        total = __builtin_amdgcn_readlane(v, 63);
+    }
+
+    static __device__ __forceinline__ uint32_t lane_of(uint32_t v, uint32_t k)
+    {
+        return (uint32_t)__builtin_amdgcn_readlane((int)v, (int)k);
+    }
+
+    // the material of item `it` < total: the last one that starts at or before
+    // it (empty materials share their first item with the next one)
+    __device__ __forceinline__ uint32_t find(uint32_t it) const
+    {
+        if (held) return (uint32_t)__popcll(__ballot(start <= it)) - 1u;
+        uint32_t lo = 0, hi = a.n_mats;
+        while (hi - lo > 1) {
+            const uint32_t mid = (lo + hi) >> 1;
+            if (a.items[mid] <= it) lo = mid;
+            else hi = mid;
+        }
+        return uniform(lo);
+    }
+
+    // material k: its first query and query count, its first item and the next material's
+    __device__ __forceinline__ void range(uint32_t k, uint32_t &first_q, uint32_t &n, uint32_t &first,
+                                          uint32_t &next) const
+    {
+        if (held) {
+            first_q = lane_of(q0, k);
+            n = lane_of(cnt, k);
+            first = lane_of(start, k);
+            next = first + (n + 63u) / 64u;
+            return;
+        }
+        batch_range(a, k, first_q, n);
+        first_q = uniform(first_q);
+        n = uniform(n);
+        first = uniform(a.items[k]);
+        next = uniform(a.items[k + 1]);
+    }
+};
+
 // W waves per workgroup (the autotuner picks 2 or 4).
 template <MlpKind K, int H, int NH, int W>
 __global__ void __launch_bounds__(64 * W) k_batch(BatchArgs a)
@@ -603,7 +674,8 @@ __global__ void __launch_bounds__(64 * W) k_batch(BatchArgs a)
     const uint32_t lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     float *st = reinterpret_cast<float *>(&stage[wv][0]);
     float4_t (*feats)[4] = reinterpret_cast<float4_t (*)[4]>(&stage[wv][0]);
-    const uint32_t total = a.items[a.n_mats];
+    const BatchItems all(a, lane);
+    const uint32_t total = all.total;
 
     // interleaved: wave g takes runs of `run` consecutive items, g-th run of
     // every gridDim.x * W; contiguous: the XCD's band split into one range per wave
@@ -627,17 +699,9 @@ __global__ void __launch_bounds__(64 * W) k_batch(BatchArgs a)
     __amdgpu_buffer_rsrc_t rs = make_rsrc(a.ws, 0), rq = rs, ro = rs;
     for (uint32_t it0 = items.first; it0 < items.end; it0 += items.step)
     for (uint32_t it = it0; it < min(it0 + run, items.end); ++it) {
-        // the material: the last k with items[k] <= it (empty materials share
-        // their first item with the next one, which the search lands on)
-        uint32_t lo = 0, hi = a.n_mats;
-        while (hi - lo > 1) {
-            const uint32_t mid = (lo + hi) >> 1;
-            if (a.items[mid] <= it) lo = mid;
-            else hi = mid;
-        }
-        lo = uniform(lo);
-        if (lo != cur) {
-            cur = lo;
+        const uint32_t k = all.find(it);
+        if (k != cur) {
+            cur = k;
             const BatchMat &M = a.mats[cur];
             lut[wv].e[lane >> 4][lane & 15] = M.lut.e[lane >> 4][lane & 15];
 #pragma unroll
@@ -647,14 +711,11 @@ __global__ void __launch_bounds__(64 * W) k_batch(BatchArgs a)
             interleaved = uniform(M.interleaved);
             stride = uniform(M.stride);
             rs = make_rsrc(a.ws + uniform64(M.scratch_off), uniform(M.scratch_bytes));
-            uint32_t q0;
-            batch_range(a, cur, q0, n_k);
-            q0 = uniform(q0);
-            n_k = uniform(n_k);
+            uint32_t q0, next_item;
+            all.range(cur, q0, n_k, first_item, next_item);
             rq = make_rsrc(a.queries + 3ull * q0, n_k * 12u);
             ro = make_rsrc(a.out + (uint64_t)a.out_dim * q0, n_k * a.out_dim * 4u);
             mlp.load(a.ws + uniform64(M.weights_off), a.lay, lane);
-            first_item = uniform(a.items[cur]);
             wave_lds_sync();
         }
         const uint32_t j = it - first_item;

@@ -724,6 +724,13 @@ __global__ void __launch_bounds__(64) k_batch_items(BatchArgs a)
     if (lane == 0) a.items[a.n_mats] = carry;
 }
 
+static hipError_t launch_batch_items(const BatchArgs &a, hipStream_t s)
+{
+    if (a.n_mats <= kWaveItems) return hipSuccess;       // every wave adds them up (BatchItems)
+    k_batch_items<<<1, 64, 0, s>>>(a);
+    return hipGetLastError();
+}
+
 // Marks, for the position-packed materials of a batch, the block positions
 // the queries' footprints read: the same work items, levels and taps as
 // k_batch (items of 64 queries; a lane past a material's queries reads the
@@ -745,17 +752,11 @@ __global__ void __launch_bounds__(256) k_batch_mark(BatchArgs a, uint8_t *marks)
     const uint32_t lane = threadIdx.x & 63u, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     uint8_t *pm = reinterpret_cast<uint8_t *>(priv[wv]);
     for (uint32_t i = lane; i < kPrivBytes / 4; i += 64) priv[wv][i] = 0u;
-    const uint32_t total = a.items[a.n_mats];
+    const BatchItems all(a, lane);
+    const uint32_t total = all.total;
     const uint32_t waves = gridDim.x * 4, w = blockIdx.x * 4 + wv;
     const uint32_t first = (uint32_t)((uint64_t)total * w / waves), end = (uint32_t)((uint64_t)total * (w + 1) / waves);
     if (first >= end) return;
-    uint32_t lo = 0, hi = a.n_mats;                 // the material of `first`
-    while (hi - lo > 1) {
-        const uint32_t mid = (lo + hi) >> 1;
-        if (a.items[mid] <= first) lo = mid;
-        else hi = mid;
-    }
-    lo = uniform(lo);
     uint32_t base = 0, next = 0, interleaved = 0;
     float lb0 = 0.0f, lb1 = 0.0f;
     __amdgpu_buffer_rsrc_t rq = make_rsrc(a.queries, 0);
@@ -769,10 +770,8 @@ __global__ void __launch_bounds__(256) k_batch_mark(BatchArgs a, uint8_t *marks)
         lb0 = __builtin_bit_cast(float, uniform(__builtin_bit_cast(uint32_t, M.levels_bias[0])));
         lb1 = __builtin_bit_cast(float, uniform(__builtin_bit_cast(uint32_t, M.levels_bias[1])));
         uint32_t q0, n_k;
-        batch_range(a, k, q0, n_k);
-        rq = make_rsrc(a.queries + 3ull * uniform(q0), uniform(n_k) * 12u);
-        base = uniform(a.items[k]);
-        next = uniform(a.items[k + 1]);
+        all.range(k, q0, n_k, base, next);
+        rq = make_rsrc(a.queries + 3ull * q0, n_k * 12u);
         wave_lds_sync();
         if (lane == 0) {                            // the private levels, coarsest first
             const uint32_t levels = __builtin_bit_cast(uint32_t, lb0);
@@ -802,7 +801,7 @@ __global__ void __launch_bounds__(256) k_batch_mark(BatchArgs a, uint8_t *marks)
         }
         wave_lds_sync();
     };
-    enter(lo);
+    enter(all.find(first));
     Query q = load_query(rq, (first - base) * 64 + lane);
     for (uint32_t it = first; it < end; ++it) {
         const uint32_t nx = it + 1;
@@ -836,10 +835,7 @@ __global__ void __launch_bounds__(256) k_batch_mark(BatchArgs a, uint8_t *marks)
         if (nx < end && !same) {                    // the next item starts another material
             wave_lds_sync();                        // this item's LDS reads and marks are done
             flush();
-            uint32_t k = lo + 1;
-            while (k + 1 < a.n_mats && a.items[k + 1] <= nx) ++k;   // past empty materials
-            lo = uniform(k);
-            enter(lo);
+            enter(all.find(nx));
             qn = load_query(rq, (nx - base) * 64 + lane);
         }
         q = qn;
@@ -875,8 +871,7 @@ hipError_t launch_batch_mark(void *ws, size_t table_off, size_t items_off, const
     a.queries = queries;
     a.n_mats = n_mats;
     a.n_total = n_total;
-    k_batch_items<<<1, 64, 0, s>>>(a);
-    hipError_t e = hipGetLastError();
+    hipError_t e = launch_batch_items(a, s);
     if (e != hipSuccess) return e;
     // waves walk contiguous ranges of at least 16 items (1024 queries), at
     // most 8192 waves (what the chip keeps resident)
@@ -944,8 +939,7 @@ hipError_t launch_batch(void *ws, size_t table_off, size_t items_off, const WsLa
     a.out_dim = sh.out;
     a.interleave = shape.interleave;
     a.run = shape.run;
-    k_batch_items<<<1, 64, 0, s>>>(a);
-    hipError_t e = hipGetLastError();
+    hipError_t e = launch_batch_items(a, s);
     if (e != hipSuccess) return e;
     const uint32_t waves = shape.waves == 2 ? 2u : 4u;
     const unsigned cap = 256u * 64u / waves;               // at most 64 waves per CU's worth

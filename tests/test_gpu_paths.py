@@ -253,3 +253,27 @@ def test_training_backward_in_batches_equals_its_parts(bcf):
     for w, a, b in zip(whole, *halves):
         # fp32 sums of some hundred partial sums each way, in any order
         assert float((w - a - b).abs().max()) <= 1e-3 * float(w.abs().max()) + 1e-12
+
+
+@pytest.mark.parametrize("n_mats", [1, 63, 64, 65, 130])
+def test_batches_around_the_materials_a_wave_holds(bcf, n_mats):
+    """Items found from the lanes and from the table, with empty materials at
+    both ends and in between: whole and touched unpacks equal single decodes."""
+    g = synth.rng(180)
+    mats = [material(bcf, [(16, 16), (16, 16), (16, 16)] if k % 2 else [(32, 16), (16, 16), (8, 8)], [3, 3, 3],
+                     (9, 16, 3), seed=181 + k)[0] for k in range(5)]
+    mats = [mats[k % 5] for k in range(n_mats)]
+    counts = g.integers(0, 3, n_mats) * g.integers(1, 150, n_mats)
+    counts[0] = 0 if n_mats > 1 else 100
+    counts[-1] = 0 if n_mats > 1 else 100
+    offsets = np.concatenate([[0], np.cumsum(counts)]).astype(np.int32)
+    q = dev(synth.uniform_queries(int(offsets[-1]), g, 2.0))
+    batch = bcf.Batch(mats, bcf.Precision.FP16, ws_fill=0xFF)
+    batch.unpack_touched(q, dev(offsets))
+    touched = batch.decode(q, dev(offsets))
+    batch.unpack()
+    assert torch.equal(batch.decode(q, dev(offsets)), touched)
+    for k in np.flatnonzero(counts):
+        part = slice(int(offsets[k]), int(offsets[k + 1]))
+        assert torch.equal(bcf.decode(mats[k], bcf.prepare(mats[k], bcf.Precision.FP16), q[part], bcf.Precision.FP16),
+                           touched[part])
