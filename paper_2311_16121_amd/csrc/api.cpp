@@ -273,6 +273,22 @@ void interleave_if_shared(bcf::MaterialDesc &d)
     d.interleaved = 1;
 }
 
+// Whether the unpack before a decode of n queries stores past the caches
+// (packed scratches; others always do). A scratch of a few times the L2s (32
+// MB) and less is best left in them for the decode. A larger one would only
+// write them back under its reads: 134 MB with 1,000 points 53.0 us ordinarily,
+// 38.1 so, 1920 x 1080 93.8 and 85.8, 3840 x 2160 203.7 and 192.5; 34 MB 18.3
+// and 19.4, 50.2 and 53.9 (fp16, four pyramids of 2048 and 1024). Scattered
+// points read it line by line, and once they read about as much as it holds,
+// what the unpack left in the caches counts again: 134 MB with 600,000 80.2
+// and 73.1, with 1,000,000 94.2 and 95.3, with 2,000,000 128.9 and 138.5.
+bool unpack_past_caches(const bcf::WsLayout &lay, size_t n, uint32_t grid_width)
+{
+    constexpr size_t kPointBytes = 160;
+    if (lay.scratch_bytes <= (size_t)64 << 20) return false;
+    return (grid_width >= 16 && grid_width <= n) || n < lay.scratch_bytes / kPointBytes;
+}
+
 // describe() for the single-material calls: three or four pyramids of one
 // geometry get the packed scratch.
 bcf_status describe_single(const bcf_material *m, bcf::MaterialDesc *d, bcf::MlpShape *sh)
@@ -370,9 +386,9 @@ uint2 *scratch_of(void *ws, const bcf::WsLayout &lay)
     return reinterpret_cast<uint2 *>(static_cast<uint8_t *>(ws) + lay.scratch_off);
 }
 
-bcf_status unpack(const bcf::MaterialDesc &d, const bcf::WsLayout &lay, void *ws, hipStream_t s)
+bcf_status unpack(const bcf::MaterialDesc &d, const bcf::WsLayout &lay, void *ws, hipStream_t s, bool nt = false)
 {
-    return device_status(bcf::launch_predecode(d, predecode_plan(d), scratch_of(ws, lay), s), "unpack launch");
+    return device_status(bcf::launch_predecode(d, predecode_plan(d), scratch_of(ws, lay), nt, s), "unpack launch");
 }
 
 
@@ -658,7 +674,7 @@ bcf_status bcf_decode(const bcf_material *m, bcf_precision p, void *ws, const fl
     if (st != BCF_OK || n == 0) return st;
     const bcf::WsLayout lay = layout(d, sh, kind);
     hipStream_t s = static_cast<hipStream_t>(stream);
-    st = unpack(d, lay, ws, s);
+    st = unpack(d, lay, ws, s, unpack_past_caches(lay, n, grid_width));
     if (st != BCF_OK) return st;
     return device_status(bcf::launch_filter_mlp(d, sh, kind, lay, ws, queries, n, grid_width, out, s),
                          "decode launch");

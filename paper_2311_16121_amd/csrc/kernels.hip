@@ -229,7 +229,7 @@ __device__ __forceinline__ UnpackSeg material_seg(const PredecodeArgs &a, uint32
     return sg;
 }
 
-template <bool SIGNED>
+template <bool SIGNED, bool NT>
 __global__ void __launch_bounds__(256) k_predecode(PredecodeArgs a)
 {
     __shared__ uint32_t table[kTableWords];
@@ -239,7 +239,7 @@ __global__ void __launch_bounds__(256) k_predecode(PredecodeArgs a)
     __shared__ uint2 slots[256];
     const UnpackSeg sg = material_seg(a, blockIdx.x);
     load_table(table);
-    unpack_chunk<SIGNED, false>(sg, blockIdx.x - sg.wg0, table, palette, slots);
+    unpack_chunk<SIGNED, NT>(sg, blockIdx.x - sg.wg0, table, palette, slots);
 }
 
 // Every material of a batch in one launch: workgroup c unpacks chunk c of
@@ -355,13 +355,14 @@ static PredecodeArgs predecode_args(const MaterialDesc &m, const PredecodePlan &
     return a;
 }
 
-hipError_t launch_predecode(const MaterialDesc &m, const PredecodePlan &p, uint2 *texels, hipStream_t s)
+hipError_t launch_predecode(const MaterialDesc &m, const PredecodePlan &p, uint2 *texels, bool nt, hipStream_t s)
 {
     const unsigned grid = p.seg_wg[p.n_seg];
     if (grid == 0) return hipSuccess;
     const PredecodeArgs a = predecode_args(m, p, texels);
-    if (m.is_signed) k_predecode<true><<<grid, 256, 0, s>>>(a);
-    else k_predecode<false><<<grid, 256, 0, s>>>(a);
+    auto *kernel = m.is_signed ? (nt ? k_predecode<true, true> : k_predecode<true, false>)
+                               : (nt ? k_predecode<false, true> : k_predecode<false, false>);
+    kernel<<<grid, 256, 0, s>>>(a);
     return hipGetLastError();
 }
 
@@ -563,7 +564,7 @@ hipError_t launch_prepare_unpack(const float *params, const float *act_absmax, c
 {
     if (kind == MLP_MFMA_FP8) {                 // the operands need the scales first
         const hipError_t e = launch_prepare_weights(params, act_absmax, sh, kind, lay, ws, &header, s);
-        return e == hipSuccess ? launch_predecode(m, p, texels, s) : e;
+        return e == hipSuccess ? launch_predecode(m, p, texels, false, s) : e;
     }
     const PrepareArgs w{params, act_absmax, sh, kind, lay, static_cast<uint8_t *>(ws), header, 1u};
     const PredecodeArgs a = predecode_args(m, p, texels);

@@ -34,12 +34,11 @@ typedef uint32_t u32x3_t __attribute__((ext_vector_type(3)));
 typedef __attribute__((address_space(1))) u32x3_t global_u32x3;
 
 // Two pyramids' texels of one position of a packed scratch, (r, g, b) halves
-// each, as one 12-byte store (dst 4-byte aligned). NT: non-temporal. A single
-// material's unpack stores ordinarily: the decode that reads the scratch next
-// runs faster when the unpack's lines went through the caches (frame4k, 134
-// MB of scratch: 161 -> 138 us for the decode, 44 -> 50 us for the unpack).
-// A batch's unpacks, gigabytes of scratch, store non-temporally (batch64: the
-// decode 2.85 -> 2.79 ms, the whole unpack 4.06 -> 3.45 ms).
+// each, as one 12-byte store (dst 4-byte aligned). NT: non-temporal. Small
+// scratches are stored ordinarily, for the decode that reads them next, large
+// ones past the caches (unpack_past_caches in api.cpp), and a batch's unpacks,
+// gigabytes of scratch, too (batch64: the decode 2.85 -> 2.79 ms, the whole
+// unpack 4.06 -> 3.45 ms).
 template <bool NT>
 __device__ __forceinline__ void store_packed_pair(uint32_t *dst, uint2 t0, uint2 t1)
 {

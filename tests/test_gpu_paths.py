@@ -277,3 +277,21 @@ def test_batches_around_the_materials_a_wave_holds(bcf, n_mats):
         part = slice(int(offsets[k]), int(offsets[k + 1]))
         assert torch.equal(bcf.decode(mats[k], bcf.prepare(mats[k], bcf.Precision.FP16), q[part], bcf.Precision.FP16),
                            touched[part])
+
+
+@pytest.mark.parametrize("n_tex,signed", [(4, False), (3, True)])
+def test_a_large_scratch_unpacks_the_same_past_the_caches(bcf, n_tex, signed):
+    """decode() of few queries stores a scratch above 64 MiB non-temporally,
+    unpack() ordinarily: the same texels, so the same bits."""
+    sizes, levels = [(2048, 2048)] * n_tex, [12] * n_tex
+    g = synth.rng(190)
+    block = synth.bounded_blocks(4096, g, signed=signed).reshape(-1)
+    texs = [np.resize(np.roll(block, 16 * 7 * t), 16 * synth.chain_blocks(2048, 2048, 12)) for t in range(n_tex)]
+    dims = (3 * n_tex, 16, 5)
+    mat = bcf.Material.from_host(texs, sizes, levels, dims, synth.mlp_params(dims, g), [0.0] * n_tex, signed)
+    ws = bcf.prepare(mat, bcf.Precision.FP16)
+    assert ws.numel() > 64 << 20
+    q = dev(synth.uniform_queries(5000, g, 11.0))
+    got = bcf.decode(mat, ws, q, bcf.Precision.FP16)
+    bcf.unpack(mat, ws)
+    assert torch.equal(bcf.decode_unpacked(mat, ws, q, bcf.Precision.FP16), got)
