@@ -273,15 +273,17 @@ void interleave_if_shared(bcf::MaterialDesc &d)
     d.interleaved = 1;
 }
 
-// Whether the unpack before a decode of n queries stores past the caches
-// (packed scratches; others always do). A scratch of a few times the L2s (32
-// MB) and less is best left in them for the decode. A larger one would only
-// write them back under its reads: 134 MB with 1,000 points 53.0 us ordinarily,
-// 38.1 so, 1920 x 1080 93.8 and 85.8, 3840 x 2160 203.7 and 192.5; 34 MB 18.3
-// and 19.4, 50.2 and 53.9 (fp16, four pyramids of 2048 and 1024). Scattered
-// points read it line by line, and once they read about as much as it holds,
+// Whether the unpack before a decode of n queries stores past the caches. A
+// scratch of up to twice the L2s (32 MB) is best left in them for the decode;
+// a larger one would only be written back under its reads. Fp16, ordinary and
+// past the caches: four pyramids of 2048 (134 MB) with 1,000 points 53.0 and
+// 38.1 us, 1920 x 1080 93.8 and 85.8, 3840 x 2160 203.7 and 192.5; two of 2048 (90
+// MB) 1280 x 720 48.6 and 44.1; 2048 to 256 (60 MB) 37.8 and 41.0; one of 2048
+// (45 MB) 28.8 and 33.1; four of 1024 (34 MB) 31.2 and 34.1. Scattered points
+// read the scratch line by line, and once they read about as much as it holds,
 // what the unpack left in the caches counts again: 134 MB with 600,000 80.2
-// and 73.1, with 1,000,000 94.2 and 95.3, with 2,000,000 128.9 and 138.5.
+// and 73.1, with 1,000,000 94.2 and 95.3, with 2,000,000 128.9 and 138.5. (The
+// unpack alone, n = 0: as for few points.)
 bool unpack_past_caches(const bcf::WsLayout &lay, size_t n, uint32_t grid_width)
 {
     constexpr size_t kPointBytes = 160;
@@ -386,9 +388,12 @@ uint2 *scratch_of(void *ws, const bcf::WsLayout &lay)
     return reinterpret_cast<uint2 *>(static_cast<uint8_t *>(ws) + lay.scratch_off);
 }
 
-bcf_status unpack(const bcf::MaterialDesc &d, const bcf::WsLayout &lay, void *ws, hipStream_t s, bool nt = false)
+// for a decode of n queries (grid_width as bcf_decode's; n = 0: not known)
+bcf_status unpack(const bcf::MaterialDesc &d, const bcf::WsLayout &lay, void *ws, size_t n, uint32_t grid_width,
+                  hipStream_t s)
 {
-    return device_status(bcf::launch_predecode(d, predecode_plan(d), scratch_of(ws, lay), nt, s), "unpack launch");
+    return device_status(bcf::launch_predecode(d, predecode_plan(d), scratch_of(ws, lay),
+                                               unpack_past_caches(lay, n, grid_width), s), "unpack launch");
 }
 
 
@@ -674,7 +679,7 @@ bcf_status bcf_decode(const bcf_material *m, bcf_precision p, void *ws, const fl
     if (st != BCF_OK || n == 0) return st;
     const bcf::WsLayout lay = layout(d, sh, kind);
     hipStream_t s = static_cast<hipStream_t>(stream);
-    st = unpack(d, lay, ws, s, unpack_past_caches(lay, n, grid_width));
+    st = unpack(d, lay, ws, n, grid_width, s);
     if (st != BCF_OK) return st;
     return device_status(bcf::launch_filter_mlp(d, sh, kind, lay, ws, queries, n, grid_width, out, s),
                          "decode launch");
@@ -699,7 +704,7 @@ bcf_status bcf_unpack(const bcf_material *m, void *ws, void *stream)
                         "workspace %p was prepared for another material: prepare it again for this one", ws);
     }
     const bcf::WsLayout lay = layout(d, sh, bcf::MLP_MFMA_F32);
-    return unpack(d, lay, ws, static_cast<hipStream_t>(stream));
+    return unpack(d, lay, ws, 0, 0, static_cast<hipStream_t>(stream));
 }
 
 bcf_status bcf_decode_unpacked(const bcf_material *m, bcf_precision p, const void *ws, const float *queries,
@@ -734,7 +739,7 @@ bcf_status bcf_calibrate(const bcf_material *m, void *ws, const float *queries, 
     st = device_status(bcf::launch_prepare_weights(m->params, nullptr, sh, bcf::MLP_VALU_F32, lay, ws, nullptr, s),
                        "prepare launch");
     if (st != BCF_OK) return st;
-    st = unpack(d, lay, ws, s);
+    st = unpack(d, lay, ws, n, 0, s);
     if (st != BCF_OK) return st;
     return device_status(bcf::launch_calibrate(d, sh, lay, ws, queries, n, act_absmax, s), "calibrate launch");
 }

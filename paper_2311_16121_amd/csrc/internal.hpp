@@ -79,7 +79,7 @@ struct PredecodePlan {
     uint32_t seg_lvl[kMaxTextures * kMaxLevels];
     uint32_t seg_wg[kMaxTextures * kMaxLevels + 1];     // first workgroup of each segment
 };
-// nt: a packed scratch is stored non-temporally (another one always is)
+// nt: the scratch is stored non-temporally
 hipError_t launch_predecode(const MaterialDesc &m, const PredecodePlan &p, uint2 *texels, bool nt,
                             hipStream_t s);
 

@@ -172,9 +172,9 @@ __device__ __forceinline__ void unpack_chunk(const UnpackSeg &sg, uint32_t chunk
                 if (y0 + r >= lh) break;          // a level shorter than 4 texels
                 const uint2 p0 = texel(lb, 4 * r + 2 * half), p1 = texel(lb, 4 * r + 2 * half + 1);
                 const uint32_t trow = __umul24(y0 + r, pitch);   // texel index, below 2^31
-                store_pair(dst + (trow + x0 + 2 * half), p0, p1);
+                store_pair<NT>(dst + (trow + x0 + 2 * half), p0, p1);
                 if (x0 == 0 && half == 0)         // wrap columns w and w+1: texels 0 and 1
-                    store_pair(dst + (trow + lw), p0, p1);
+                    store_pair<NT>(dst + (trow + lw), p0, p1);
             }
         }
     } else if (bi < n_blk) {
@@ -187,8 +187,8 @@ __device__ __forceinline__ void unpack_chunk(const UnpackSeg &sg, uint32_t chunk
             uint2 *row = dst + __umul24(y0 + r, pitch);
             const uint2 p0 = texel(threadIdx.x, 4 * r), p1 = texel(threadIdx.x, 4 * r + 1);
             if (lw == 2) {                        // pitch 4: texels 0 1 0 1
-                store_pair(row, p0, p1);
-                store_pair(row + 2, p0, p1);
+                store_pair<NT>(row, p0, p1);
+                store_pair<NT>(row + 2, p0, p1);
             } else {                              // pitch 3: texel 0 three times
                 global_texel *g = (global_texel *)row;
                 const u32x2_t v = {p0.x, p0.y};

@@ -21,24 +21,22 @@ typedef __attribute__((address_space(1))) const u32x4_t global_block;
 typedef uint32_t u32x2_t __attribute__((ext_vector_type(2)));
 typedef __attribute__((address_space(1))) u32x2_t global_texel;
 
-// Two texels to the scratch as one 16-byte non-temporal store: the unpack
-// never reads them back, and the decode that follows it runs faster when the
-// unpack's writes have not been left dirty in the caches (measured on the
-// frame benchmark's unpack-then-decode step).
+// Two texels to the scratch as one 16-byte store. NT: non-temporal, past the
+// caches (unpack_past_caches in api.cpp says when; a batch's unpacks always).
+template <bool NT>
 __device__ __forceinline__ void store_pair(uint2 *dst, uint2 t0, uint2 t1)
 {
-    __builtin_nontemporal_store((u32x4_t){t0.x, t0.y, t1.x, t1.y}, (global_u32x4 *)dst);
+    const u32x4_t v = {t0.x, t0.y, t1.x, t1.y};
+    if (NT) __builtin_nontemporal_store(v, (global_u32x4 *)dst);
+    else *(global_u32x4 *)dst = v;
 }
 
 typedef uint32_t u32x3_t __attribute__((ext_vector_type(3)));
 typedef __attribute__((address_space(1))) u32x3_t global_u32x3;
 
 // Two pyramids' texels of one position of a packed scratch, (r, g, b) halves
-// each, as one 12-byte store (dst 4-byte aligned). NT: non-temporal. Small
-// scratches are stored ordinarily, for the decode that reads them next, large
-// ones past the caches (unpack_past_caches in api.cpp), and a batch's unpacks,
-// gigabytes of scratch, too (batch64: the decode 2.85 -> 2.79 ms, the whole
-// unpack 4.06 -> 3.45 ms).
+// each, as one 12-byte store (dst 4-byte aligned). NT: as store_pair (batch64,
+// gigabytes of scratch: the decode 2.85 -> 2.79 ms, the whole unpack 4.06 -> 3.45 ms).
 template <bool NT>
 __device__ __forceinline__ void store_packed_pair(uint32_t *dst, uint2 t0, uint2 t1)
 {

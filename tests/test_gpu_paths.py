@@ -279,10 +279,10 @@ def test_batches_around_the_materials_a_wave_holds(bcf, n_mats):
                            touched[part])
 
 
-@pytest.mark.parametrize("n_tex,signed", [(4, False), (3, True)])
+@pytest.mark.parametrize("n_tex,signed", [(4, False), (3, True), (2, False)])
 def test_a_large_scratch_unpacks_the_same_past_the_caches(bcf, n_tex, signed):
-    """decode() of few queries stores a scratch above 64 MiB non-temporally,
-    unpack() ordinarily: the same texels, so the same bits."""
+    """decode() of few queries stores a scratch above 64 MiB non-temporally, of
+    many ordinarily: the same texels, so the same bits."""
     sizes, levels = [(2048, 2048)] * n_tex, [12] * n_tex
     g = synth.rng(190)
     block = synth.bounded_blocks(4096, g, signed=signed).reshape(-1)
@@ -291,7 +291,8 @@ def test_a_large_scratch_unpacks_the_same_past_the_caches(bcf, n_tex, signed):
     mat = bcf.Material.from_host(texs, sizes, levels, dims, synth.mlp_params(dims, g), [0.0] * n_tex, signed)
     ws = bcf.prepare(mat, bcf.Precision.FP16)
     assert ws.numel() > 64 << 20
-    q = dev(synth.uniform_queries(5000, g, 11.0))
-    got = bcf.decode(mat, ws, q, bcf.Precision.FP16)
+    q = dev(synth.uniform_queries(900_000, g, 11.0))
+    many = bcf.decode(mat, ws, q, bcf.Precision.FP16)
+    assert torch.equal(bcf.decode(mat, ws, q[:5000], bcf.Precision.FP16), many[:5000])
     bcf.unpack(mat, ws)
-    assert torch.equal(bcf.decode_unpacked(mat, ws, q, bcf.Precision.FP16), got)
+    assert torch.equal(bcf.decode_unpacked(mat, ws, q, bcf.Precision.FP16), many)
