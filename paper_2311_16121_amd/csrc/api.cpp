@@ -273,6 +273,8 @@ void interleave_if_shared(bcf::MaterialDesc &d)
     d.interleaved = 1;
 }
 
+constexpr size_t kCachedScratch = (size_t)64 << 20;
+
 // Whether the unpack before a decode of n queries stores past the caches. A
 // scratch of up to twice the L2s (32 MB) is best left in them for the decode;
 // a larger one would only be written back under its reads. Fp16, ordinary and
@@ -287,7 +289,7 @@ void interleave_if_shared(bcf::MaterialDesc &d)
 bool unpack_past_caches(const bcf::WsLayout &lay, size_t n, uint32_t grid_width)
 {
     constexpr size_t kPointBytes = 160;
-    if (lay.scratch_bytes <= (size_t)64 << 20) return false;
+    if (lay.scratch_bytes <= kCachedScratch) return false;
     return (grid_width >= 16 && grid_width <= n) || n < lay.scratch_bytes / kPointBytes;
 }
 
@@ -551,6 +553,17 @@ struct BatchLayout {
     bcf::WsLayout rel;
     bcf::MlpKind kind;
 };
+
+// Likewise for a batch, by the scratch of all its materials: whole unpack and
+// decode, ordinarily and past the caches, 8 materials of 35 MB 29.2 and 31.2 us,
+// 3 of 63 MB 37.1 and 40.9, 8 of 78 MB 61.4 and 61.2, 4 of 109 MB 47.6 and 37.2,
+// 20 of 274 MB 150.0 and 136.6, 24 of 906 MB 594.5 and 527.0.
+bool unpack_past_caches(const BatchLayout &b)
+{
+    size_t scratch = 0;
+    for (const bcf::BatchSlot &s : b.slots) scratch += s.scratch_bytes;
+    return scratch > kCachedScratch;
+}
 
 constexpr uint32_t kMaxBatch = 4096;
 
@@ -928,7 +941,8 @@ bcf_status bcf_unpack_batch(const bcf_material *mats, uint32_t n_mats, void *ws,
     const uint8_t *base = static_cast<const uint8_t *>(ws);
     const bcf::UnpackSeg *segs = reinterpret_cast<const bcf::UnpackSeg *>(base + b.segs_off);
     const uint32_t *chunk_seg = reinterpret_cast<const uint32_t *>(base + b.chunk_seg_off);
-    return device_status(bcf::launch_predecode_batch(segs, chunk_seg, b.n_chunks, static_cast<hipStream_t>(stream)),
+    return device_status(bcf::launch_predecode_batch(segs, chunk_seg, b.n_chunks, unpack_past_caches(b),
+                                                     static_cast<hipStream_t>(stream)),
                          "unpack launch");
 }
 
@@ -977,7 +991,7 @@ bcf_status bcf_unpack_batch_touched(const bcf_material *mats, uint32_t n_mats, v
                                                        reinterpret_cast<const uint32_t *>(base + b.chunk_seg_off),
                                                        b.n_seg, b.n_chunks,
                                                        reinterpret_cast<const uint32_t *>(base + b.units_off),
-                                                       b.n_units, base + b.marks_off, s),
+                                                       b.n_units, base + b.marks_off, unpack_past_caches(b), s),
                          "unpack launch");
 }
 

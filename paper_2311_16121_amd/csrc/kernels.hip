@@ -249,6 +249,7 @@ __global__ void __launch_bounds__(256) k_predecode(PredecodeArgs a)
 // workgroup). One chunk per workgroup lets the hardware start a workgroup as
 // soon as another retires, which keeps the stores of one chunk in flight
 // beside the loads of the next (a persistent loop serialises them).
+template <bool NT>
 __global__ void __launch_bounds__(256) k_predecode_batch(const UnpackSeg *segs, const uint32_t *chunk_seg,
                                                          uint32_t n_chunks)
 {
@@ -258,8 +259,8 @@ __global__ void __launch_bounds__(256) k_predecode_batch(const UnpackSeg *segs, 
     load_table(table);
     for (uint32_t c = blockIdx.x; c < n_chunks; c += gridDim.x) {
         const UnpackSeg sg = segs[chunk_seg[c]];
-        if (sg.flags & kSegSigned) unpack_chunk<true, true>(sg, c - sg.wg0, table, palette, slots);
-        else unpack_chunk<false, true>(sg, c - sg.wg0, table, palette, slots);
+        if (sg.flags & kSegSigned) unpack_chunk<true, NT>(sg, c - sg.wg0, table, palette, slots);
+        else unpack_chunk<false, NT>(sg, c - sg.wg0, table, palette, slots);
         __syncthreads();                          // palette and slots are reused by the next chunk
     }
 }
@@ -270,6 +271,11 @@ __global__ void __launch_bounds__(256) k_predecode_batch(const UnpackSeg *segs, 
 // positions it gathers in LDS and unpacks, 64 positions per pass (most
 // windows need one pass with one or two busy waves); for any other segment,
 // one whole chunk. marks[64 c + p] != 0: position p of chunk c is needed.
+// Scattered positions are stored ordinarily at any size, so that the L2s
+// gather their 12-byte pieces into lines (24 materials of 906 MB in all, 5.5
+// million queries, with marking and decode: past the caches 438.0 us,
+// ordinarily 425.0; 20 of 274 MB 127.5 and 121.8); NT: whole chunks.
+template <bool NT>
 __global__ void __launch_bounds__(256) k_predecode_touched(const UnpackSeg *segs, const uint32_t *chunk_seg,
                                                            uint32_t n_seg, uint32_t n_chunks, const uint32_t *units,
                                                            uint32_t n_units, const uint8_t *marks)
@@ -287,8 +293,8 @@ __global__ void __launch_bounds__(256) k_predecode_touched(const UnpackSeg *segs
         const UnpackSeg sg = segs[sidx];
         const bool sgn = (sg.flags & kSegSigned) != 0;
         if (!(sg.flags & kSegInterleaved)) {
-            if (sgn) unpack_chunk<true, true>(sg, c0 - sg.wg0, table, palette, slots);
-            else unpack_chunk<false, true>(sg, c0 - sg.wg0, table, palette, slots);
+            if (sgn) unpack_chunk<true, NT>(sg, c0 - sg.wg0, table, palette, slots);
+            else unpack_chunk<false, NT>(sg, c0 - sg.wg0, table, palette, slots);
             __syncthreads();                      // palette and slots are reused by the next unit
             continue;
         }
@@ -311,8 +317,8 @@ __global__ void __launch_bounds__(256) k_predecode_touched(const UnpackSeg *segs
         __syncthreads();
         for (uint32_t p0 = 0; p0 < total; p0 += 64) {
             const uint32_t n = min(64u, total - p0);
-            if (sgn) unpack_chunk<true, true>(sg, 0, table, palette, slots, list + p0, n);
-            else unpack_chunk<false, true>(sg, 0, table, palette, slots, list + p0, n);
+            if (sgn) unpack_chunk<true, false>(sg, 0, table, palette, slots, list + p0, n);
+            else unpack_chunk<false, false>(sg, 0, table, palette, slots, list + p0, n);
             __syncthreads();
         }
     }
@@ -320,20 +326,21 @@ __global__ void __launch_bounds__(256) k_predecode_touched(const UnpackSeg *segs
 
 hipError_t launch_predecode_touched(const UnpackSeg *segs, const uint32_t *chunk_seg, uint32_t n_seg,
                                     uint32_t n_chunks, const uint32_t *units, uint32_t n_units, const uint8_t *marks,
-                                    hipStream_t s)
+                                    bool nt, hipStream_t s)
 {
     if (n_units == 0) return hipSuccess;
     const unsigned grid = std::min<unsigned>(n_units, 1u << 22);
-    k_predecode_touched<<<grid, 256, 0, s>>>(segs, chunk_seg, n_seg, n_chunks, units, n_units, marks);
+    (nt ? k_predecode_touched<true> : k_predecode_touched<false>)<<<grid, 256, 0, s>>>(segs, chunk_seg, n_seg, n_chunks, units, n_units, marks);
     return hipGetLastError();
 }
 
-hipError_t launch_predecode_batch(const UnpackSeg *segs, const uint32_t *chunk_seg, uint32_t n_chunks, hipStream_t s)
+hipError_t launch_predecode_batch(const UnpackSeg *segs, const uint32_t *chunk_seg, uint32_t n_chunks, bool nt,
+                                  hipStream_t s)
 {
     if (n_chunks == 0) return hipSuccess;
     // a grid of at most 2^22 workgroups (2^30 threads); larger tables loop
     const unsigned grid = std::min<unsigned>(n_chunks, 1u << 22);
-    k_predecode_batch<<<grid, 256, 0, s>>>(segs, chunk_seg, n_chunks);
+    (nt ? k_predecode_batch<true> : k_predecode_batch<false>)<<<grid, 256, 0, s>>>(segs, chunk_seg, n_chunks);
     return hipGetLastError();
 }
 

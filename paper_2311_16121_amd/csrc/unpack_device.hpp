@@ -22,7 +22,7 @@ typedef uint32_t u32x2_t __attribute__((ext_vector_type(2)));
 typedef __attribute__((address_space(1))) u32x2_t global_texel;
 
 // Two texels to the scratch as one 16-byte store. NT: non-temporal, past the
-// caches (unpack_past_caches in api.cpp says when; a batch's unpacks always).
+// caches (unpack_past_caches in api.cpp says when).
 template <bool NT>
 __device__ __forceinline__ void store_pair(uint2 *dst, uint2 t0, uint2 t1)
 {
@@ -35,8 +35,7 @@ typedef uint32_t u32x3_t __attribute__((ext_vector_type(3)));
 typedef __attribute__((address_space(1))) u32x3_t global_u32x3;
 
 // Two pyramids' texels of one position of a packed scratch, (r, g, b) halves
-// each, as one 12-byte store (dst 4-byte aligned). NT: as store_pair (batch64,
-// gigabytes of scratch: the decode 2.85 -> 2.79 ms, the whole unpack 4.06 -> 3.45 ms).
+// each, as one 12-byte store (dst 4-byte aligned). NT: as store_pair.
 template <bool NT>
 __device__ __forceinline__ void store_packed_pair(uint32_t *dst, uint2 t0, uint2 t1)
 {
