@@ -12,7 +12,7 @@ One step = one decode of the whole frame with textures, MLP and queries
 already resident in HBM, issued as its two calls (bcf_unpack, then
 bcf_decode_unpacked) so that HIP events time each kernel; the step time is
 the median over the timed steps. The headline value is the FP16-MFMA rate;
-the plain FP32 rate is timed on the same inputs. The FP16 output is compared
+the FP32 rate is timed on the same inputs. The FP16 output is compared
 with the FP32 output over the whole frame, and (in the CPU-baseline leg) both
 with the fp64 oracle on the oracle's sample; the rate is reported only when
 FP16 stays within 2e-3 of both. The same decode of full-range random blocks
@@ -107,7 +107,7 @@ def all_blocks(textures):
 
 
 FRAME_SOURCES = ("api.cpp", "bc6h_device.hpp", "filter_device.hpp", "frame_f16.hip", "frame_kernels.hpp",
-                 "internal.hpp", "kernels.hip", "mlp_device.hpp")
+                 "internal.hpp", "kernels.hip", "mlp_device.hpp", "unpack_device.hpp")
 
 
 def sources_digest():

@@ -729,8 +729,8 @@ __global__ void __launch_bounds__(kBinThreads) k_train_bin_scatter(const float *
 // of 2^20 samples with 12-32-32-10 at their rate) and the filter's texel
 // reads, which two waves per SIMD overlap. The version before kept one row per
 // sample in LDS between all products, at strides of 32 and 33 floats (up to
-// 16 lanes on one bank): 390 -> 170 us for those 2^20 samples, 173 -> 36 us
-// for 2^18 with 12-16-16-8 (where the waves' own flushes, 3072 atomics a
+// 16 lanes on one bank): 390 -> 170 us for those 2^20 samples (150
+// from packed texels), 173 -> 36 us for 2^18 with 12-16-16-8 (where the waves' own flushes, 3072 atomics a
 // parameter, weighed more; now one per workgroup, 512).
 __host__ __device__ constexpr uint32_t hidden_unit(uint32_t m) { return 4u * (m & 3u) + (m >> 2); }
 
