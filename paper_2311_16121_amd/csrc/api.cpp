@@ -284,12 +284,17 @@ constexpr size_t kCachedScratch = (size_t)64 << 20;
 // (45 MB) 28.8 and 33.1; four of 1024 (34 MB) 31.2 and 34.1. Scattered points
 // read the scratch line by line, and once they read about as much as it holds,
 // what the unpack left in the caches counts again: 134 MB with 600,000 80.2
-// and 73.1, with 1,000,000 94.2 and 95.3, with 2,000,000 128.9 and 138.5. (The
-// unpack alone, n = 0: as for few points.)
-bool unpack_past_caches(const bcf::WsLayout &lay, size_t n, uint32_t grid_width)
+// and 73.1, with 1,000,000 94.2 and 95.3, with 2,000,000 128.9 and 138.5.
+// These alternate between three materials. One that is decoded over and over
+// keeps its 134 MB in the memory-side cache when stored ordinarily (3840 x 2160
+// 173.5 and 186.4 us), which is what a caller of the unpack by itself (n = 0) is
+// taken to do: packed scratches are then stored ordinarily (unpack and decode
+// of that frame 160 and 193 us).
+bool unpack_past_caches(const bcf::MaterialDesc &d, const bcf::WsLayout &lay, size_t n, uint32_t grid_width)
 {
     constexpr size_t kPointBytes = 160;
     if (lay.scratch_bytes <= kCachedScratch) return false;
+    if (n == 0) return !d.interleaved;
     return (grid_width >= 16 && grid_width <= n) || n < lay.scratch_bytes / kPointBytes;
 }
 
@@ -395,7 +400,7 @@ bcf_status unpack(const bcf::MaterialDesc &d, const bcf::WsLayout &lay, void *ws
                   hipStream_t s)
 {
     return device_status(bcf::launch_predecode(d, predecode_plan(d), scratch_of(ws, lay),
-                                               unpack_past_caches(lay, n, grid_width), s), "unpack launch");
+                                               unpack_past_caches(d, lay, n, grid_width), s), "unpack launch");
 }
 
 
