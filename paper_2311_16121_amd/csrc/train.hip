@@ -350,7 +350,6 @@ __global__ void __launch_bounds__(kTrainThreads) k_train_blocks(TrainDesc d)
 #pragma unroll
             for (int k = 0; k < 4; ++k) x[k] = xp[k];
         }
-        // texels that a level below 4x4 does not have: zero gradients
         const float *gp = d.g_texels + 3u * s.tex;
         if (s.valid && s.wl >= 4u) {
 #pragma unroll
@@ -371,6 +370,10 @@ __global__ void __launch_bounds__(kTrainThreads) k_train_blocks(TrainDesc d)
         for (int i = 0; i < 4; ++i) {
             const bool sub = (pmask >> i) & 1u;
             gx[i] = 0.0f;
+            // not as a product with a zero gradient: the index of a texel that
+            // the level does not have, and a subset's endpoints without a
+            // texel, may hold anything
+            if (!s.valid || (uint32_t)i >= s.wl) continue;
 #pragma unroll
             for (int c = 0; c < 3; ++c) {
                 const TexelChan t = texel_chan<STE>(sub ? e[6 + c] : e[c], sub ? e[9 + c] : e[3 + c], x[i]);

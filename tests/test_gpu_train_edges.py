@@ -1,0 +1,59 @@
+"""Training edges: parameters that no texel uses, gradients of very different
+size side by side, pyramids whose scatter windows do not fit, and batches of
+samples, against the binary64 oracle or the call's own parts."""
+import numpy as np
+import pytest
+
+import synth
+from oracle import train as T
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def bcf():
+    if not torch.cuda.is_available():
+        pytest.fail("GPU tests need a visible MI355X")
+    import paper_2311_16121_amd as bcf
+    return bcf
+
+
+def dev(x):
+    return torch.from_numpy(np.ascontiguousarray(x)).cuda()
+
+
+@pytest.mark.parametrize("n_tex", [1, 3])
+@pytest.mark.parametrize("straight", [False, True])
+@pytest.mark.parametrize("bad", [np.nan, np.inf, 3e38])
+def test_parameters_that_no_texel_uses_change_nothing(bcf, n_tex, straight, bad):
+    """The 2 x 2 and 1 x 1 levels keep the top left of their blocks. Whatever
+    the other texels' indices and the endpoints of a subset without a texel
+    hold, the other gradients are what they are without it, bit for bit (one
+    sample a call: no sum has an order to differ in), and theirs are 0."""
+    g = synth.rng(1200)
+    dims, levels, first = (3 * n_tex, 16, 4), 4, 4 + 1          # 8 x 8: four blocks, then one per level
+    nb = synth.chain_blocks(8, 8, levels)
+    assert nb == first + 2
+    ends = [g.uniform(0.0, 63.0, (nb, 4, 3)).astype(np.float32) for _ in range(n_tex)]
+    idxs = [g.uniform(0.0, 1.0, (nb, 16)).astype(np.float32) for _ in range(n_tex)]
+    parts = [np.zeros(nb, np.uint8) for _ in range(n_tex)]       # mask 0xCCCC: subset 1 is columns 2 and 3
+    params = synth.mlp_params(dims, g).astype(np.float32)
+    geo = bcf.TrainGeometry([8] * n_tex, [levels] * n_tex, [dev(p) for p in parts], dims, straight_through=straight)
+    unused = np.ones((2, 16), bool)
+    unused[0, [0, 1, 4, 5]] = False                              # 2 x 2
+    unused[1, 0] = False                                         # 1 x 1
+    bad_ends, bad_idxs = [e.copy() for e in ends], [x.copy() for x in idxs]
+    for e, x in zip(bad_ends, bad_idxs):
+        e[first:, 2:] = bad
+        x[first:][unused] = bad
+    for q in synth.uniform_queries(8, g, 1.0) + np.array([0.0, 0.0, 2.0], np.float32):
+        go = dev(g.standard_normal((1, 4)).astype(np.float32))
+        want = bcf.train_backward(geo, [dev(e) for e in ends], [dev(x) for x in idxs], dev(params), dev(q[None]), go)
+        got = bcf.train_backward(geo, [dev(e) for e in bad_ends], [dev(x) for x in bad_idxs], dev(params),
+                                 dev(q[None]), go)
+        for a, b in zip(got[0] + got[1] + [got[2]], want[0] + want[1] + [want[2]]):
+            assert torch.equal(a, b)
+        for ge, gi in zip(got[0], got[1]):
+            assert not ge[first:, 2:].any() and not gi[first:][dev(unused)].any()
+            assert ge[first:, :2].any() and gi[first:].any()
