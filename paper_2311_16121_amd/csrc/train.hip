@@ -1076,6 +1076,29 @@ __host__ __device__ inline uint32_t window_side(uint32_t wl, uint32_t cells)
     return wl < span ? wl : span;
 }
 
+// The least e with |x| < 2^e, of a finite |x| as bits (-125 for those below
+// 2^-125).
+__device__ __forceinline__ int exponent_above(uint32_t bits) { return max((int)(bits >> 23), 1) - 126; }
+
+// The wave's largest value, in its last lane.
+__device__ __forceinline__ uint32_t wave_max_63(uint32_t v)
+{
+    auto up = [&](auto ctrl) {                      // lanes without a source read 0
+        return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, decltype(ctrl)::value, 0xF, 0xF, true);
+    };
+    v = max(v, up(std::integral_constant<int, 0x111>()));       // row_shr 1, 2, 4, 8
+    v = max(v, up(std::integral_constant<int, 0x112>()));
+    v = max(v, up(std::integral_constant<int, 0x114>()));
+    v = max(v, up(std::integral_constant<int, 0x118>()));
+    v = max(v, up(std::integral_constant<int, 0x142>()));       // row_bcast 15, 31
+    return max(v, up(std::integral_constant<int, 0x143>()));
+}
+
+__device__ __forceinline__ int bit_width(uint32_t n) { return 32 - __clz((int)n); }
+
+// Bits of a fixed-point contribution so that n of them sum up in 63.
+__device__ __forceinline__ int fixed_bits(uint32_t n) { return min(51, 62 - bit_width(n)); }
+
 // One workgroup per region (1 << region_log2 cells of the sample sort a side,
 // consecutive in the sort) and pyramid: the region's samples (sorted positions
 // begin .. end) add wt * dL/dz to the texels of their taps. Every tap of a
@@ -1097,19 +1120,28 @@ __host__ __device__ inline uint32_t window_side(uint32_t wl, uint32_t cells)
 // sums meet on few LDS addresses). LDS float atomics cost about 40 times
 // integer ones on this GPU, so the windows sum in fixed point: contribution v
 // adds rint(v 2^k), with 2^k chosen from the largest |dL/dz| so that a
-// contribution (whose weight is at most 1) stays below 2^30; the 64-bit sums
-// cannot overflow. Non-finite gradients take float atomics.
+// contribution (whose weight is at most 1) stays below 2^51, in which it is
+// exact or within 2^-51 of that largest one, and the 64-bit sums cannot
+// overflow (a float times 2^k plus 1.5 2^52 as doubles has the integer in its
+// low bits: as many instructions as a 32-bit integer takes, which kept 30
+// bits). A region whose cells differ by more than that leaves room for is
+// taken cell by cell, each at its own scale. Non-finite gradients take float
+// atomics.
 __global__ void __launch_bounds__(kScatterThreads) k_train_scatter(TrainDesc d, uint32_t region_log2,
                                                                    uint32_t pool_sums)
 {
     extern __shared__ unsigned long long pool[];
     __shared__ TexWindow win[kMaxLevels];
-    __shared__ uint32_t pool_used, dz_max_bits;
+    __shared__ uint32_t pool_used, cell_at[5], cell_max[4];     // of the region's cells (at most four)
     // the pyramids of one region on one XCD (workgroups are dealt to the 8 in turn)
     const uint32_t k8 = blockIdx.x >> 3, t = k8 % d.n_tex, region = (k8 / d.n_tex) * 8u + (blockIdx.x & 7u);
-    const uint32_t cell0 = region << (2u * region_log2), cells = 1u << region_log2;
-    const uint32_t begin = cell0 ? d.bin_next[cell0 - 1u] : 0u, end = d.bin_next[cell0 + cells * cells - 1u];
+    const uint32_t cell0 = region << (2u * region_log2), cells = 1u << region_log2, n_cells = cells * cells;
+    const uint32_t begin = cell0 ? d.bin_next[cell0 - 1u] : 0u, end = d.bin_next[cell0 + n_cells - 1u];
     if (begin == end) return;                          // uniform over the workgroup
+    // where the second, third and fourth cell's samples start
+    uint32_t from[3];
+#pragma unroll
+    for (uint32_t c = 0; c < 3; ++c) from[c] = c + 1u < n_cells ? d.bin_next[cell0 + c] : end;
     const TrainTexDesc &tx = d.tex[t];
     const uint32_t levels = tx.levels;
     const float bias = tx.bias;
@@ -1148,108 +1180,128 @@ __global__ void __launch_bounds__(kScatterThreads) k_train_scatter(TrainDesc d, 
         uint32_t in_use = have && upto <= pool_sums ? upto : 0u;
 #pragma unroll
         for (uint32_t k = 1; k < kMaxLevels; k <<= 1) in_use = max(in_use, __shfl_xor(in_use, k));
-        if (i == 0u) {
-            pool_used = in_use;
-            dz_max_bits = 0u;
-        }
+        if (i == 0u) pool_used = in_use;
+        if (i < 4u) cell_max[i] = 0u;
+        if (i < 5u) cell_at[i] = i == 0u ? begin : i == 1u ? from[0] : i == 2u ? from[1] : i == 3u ? from[2] : end;
     }
-    // the largest |dL/dz| of the samples (as bits: NaN and infinity
+    // the largest |dL/dz| of each cell's samples (as bits: NaN and infinity
     // above every finite value)
-    uint32_t mb = 0;
+    uint32_t mb[4] = {0u, 0u, 0u, 0u};
     for (uint32_t j = begin + threadIdx.x; j < end; j += blockDim.x) {
         const uint4 z = *reinterpret_cast<const uint4 *>(dzs + j);
-        mb = max(mb, max(max(z.x & 0x7FFFFFFFu, z.y & 0x7FFFFFFFu), z.z & 0x7FFFFFFFu));
+        const uint32_t m = max(max(z.x & 0x7FFFFFFFu, z.y & 0x7FFFFFFFu), z.z & 0x7FFFFFFFu);
+        const uint32_t c = (j >= from[0] ? 1u : 0u) + (j >= from[1] ? 1u : 0u) + (j >= from[2] ? 1u : 0u);
+#pragma unroll
+        for (uint32_t i = 0; i < 4; ++i) mb[i] = max(mb[i], c == i ? m : 0u);
     }
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) mb = max(mb, (uint32_t)__shfl_xor((int)mb, o));
+    for (uint32_t i = 0; i < 4; ++i) mb[i] = wave_max_63(mb[i]);
     __syncthreads();
-    if ((threadIdx.x & 63u) == 0) atomicMax(&dz_max_bits, mb);
+    if ((threadIdx.x & 63u) == 63u) {
+#pragma unroll
+        for (uint32_t i = 0; i < 4; ++i) atomicMax(&cell_max[i], mb[i]);
+    }
     const uint32_t used = pool_used;
     for (uint32_t e = threadIdx.x; e < used; e += blockDim.x) pool[e] = 0ull;
     __syncthreads();
-    const uint32_t mbits = dz_max_bits;
-    const bool fixed = mbits < 0x7F800000u;
-    int kexp = 0;
-    if (fixed && mbits != 0u) {
-        int em;
-        frexpf(__uint_as_float(mbits), &em);                  // |dL/dz| < 2^em
-        kexp = min(max(30 - em, -120), 120);
+    uint32_t region_max = 0;
+#pragma unroll
+    for (uint32_t i = 0; i < 4; ++i) region_max = max(region_max, uniform(cell_max[i]));
+    // One scale for the region, unless it is coarser for some cell than 2^-29
+    // of the cell's largest gradient times its samples (rounded up to powers of
+    // two), or a cell's gradients are not finite: then cell by cell.
+    bool apart = region_max >= 0x7F800000u;
+#pragma unroll
+    for (uint32_t i = 0; i < 4; ++i) {
+        const uint32_t m = uniform(cell_max[i]);
+        apart = apart || (m != 0u && exponent_above(region_max) - fixed_bits(end - begin) >
+                                         exponent_above(m) + bit_width(uniform(cell_at[i + 1] - cell_at[i])) - 29);
     }
-    const float scale = ldexpf(1.0f, kexp), unscale = ldexpf(1.0f, -kexp);
-    for (uint32_t j = begin + threadIdx.x; j < end; j += blockDim.x) {
-        const float4 q = d.bin_q[j], z4 = dzs[j];
-        const float dz[3] = {z4.x, z4.y, z4.z};
-        const float uf = q.x - floorf(q.x), vf = q.y - floorf(q.y);       // wrap addressing
-        // the two levels of eq. (10) as the forward takes them
-        const float si = fminf(fmaxf(q.z + bias, 0.0f), (float)(levels - 1u));   // NaN -> 0
-        const uint32_t l0 = (uint32_t)floorf(si);
-        const uint32_t l1 = min(l0 + 1u, levels - 1u);
-        const float lam = si - (float)l0;
+    const uint32_t passes = apart ? n_cells : 1u;
+    for (uint32_t pass = 0;;) {
+        const uint32_t first = apart ? uniform(cell_at[pass]) : begin, last = apart ? uniform(cell_at[pass + 1]) : end;
+        const uint32_t mbits = apart ? uniform(cell_max[pass]) : region_max;
+        const bool fixed = mbits < 0x7F800000u;
+        const int kexp = fixed ? fixed_bits(last - first) - exponent_above(mbits) : 0;
+        const double scale = ldexp(1.0, kexp), unscale = ldexp(1.0, -kexp);
+        for (uint32_t j = first + threadIdx.x; j < last; j += blockDim.x) {
+            const float4 q = d.bin_q[j], z4 = dzs[j];
+            const float dz[3] = {z4.x, z4.y, z4.z};
+            const float uf = q.x - floorf(q.x), vf = q.y - floorf(q.y);       // wrap addressing
+            // the two levels of eq. (10) as the forward takes them
+            const float si = fminf(fmaxf(q.z + bias, 0.0f), (float)(levels - 1u));   // NaN -> 0
+            const uint32_t l0 = (uint32_t)floorf(si);
+            const uint32_t l1 = min(l0 + 1u, levels - 1u);
+            const float lam = si - (float)l0;
 #pragma unroll
-        for (int k = 0; k < 2; ++k) {
-            const uint32_t l = k ? l1 : l0;
-            const float lw = k ? lam : 1.0f - lam;
-            // a zero weight (an unused second level) adds nothing
-            if (lw == 0.0f) continue;
-            const uint32_t wl = max(tx.w >> l, 1u), hl = max(tx.h >> l, 1u);
-            const LevelTaps lt = level_taps(make_uint4(wl, hl, 0u, 0u), uf, vf, lw);
-            const TexWindow W = win[l];
-            const uint32_t dxa = (lt.xa - W.x0) & (wl - 1u), dxb = (lt.xb - W.x0) & (wl - 1u);
-            const uint32_t dya = (lt.ya - W.y0) & (hl - 1u), dyb = (lt.yb - W.y0) & (hl - 1u);
-            const bool inside = W.off != ~0u && max(dxa, dxb) < W.w && max(dya, dyb) < W.h;
-            const uint32_t ra = W.off + 3u * __umul24(dya, W.w), rb = W.off + 3u * __umul24(dyb, W.w);
-            const uint32_t at[4] = {ra + 3u * dxa, ra + 3u * dxb, rb + 3u * dxa, rb + 3u * dxb};
-            if (inside && fixed) {
+            for (int k = 0; k < 2; ++k) {
+                const uint32_t l = k ? l1 : l0;
+                const float lw = k ? lam : 1.0f - lam;
+                // a zero weight (an unused second level) adds nothing
+                if (lw == 0.0f) continue;
+                const uint32_t wl = max(tx.w >> l, 1u), hl = max(tx.h >> l, 1u);
+                const LevelTaps lt = level_taps(make_uint4(wl, hl, 0u, 0u), uf, vf, lw);
+                const TexWindow W = win[l];
+                const uint32_t dxa = (lt.xa - W.x0) & (wl - 1u), dxb = (lt.xb - W.x0) & (wl - 1u);
+                const uint32_t dya = (lt.ya - W.y0) & (hl - 1u), dyb = (lt.yb - W.y0) & (hl - 1u);
+                const bool inside = W.off != ~0u && max(dxa, dxb) < W.w && max(dya, dyb) < W.h;
+                const uint32_t ra = W.off + 3u * __umul24(dya, W.w), rb = W.off + 3u * __umul24(dyb, W.w);
+                const uint32_t at[4] = {ra + 3u * dxa, ra + 3u * dxb, rb + 3u * dxa, rb + 3u * dxb};
+                if (inside && fixed) {
 #pragma unroll
-                for (int i = 0; i < 4; ++i)
+                    for (int i = 0; i < 4; ++i)
 #pragma unroll
-                    for (int c = 0; c < 3; ++c)
-                        atomicAdd(pool + at[i] + c,
-                                  (unsigned long long)(long long)(int32_t)rintf(lt.w[i] * dz[c] * scale));
-            } else {
+                        for (int c = 0; c < 3; ++c) {
+                            const double sum = fma((double)(lt.w[i] * dz[c]), scale, 6755399441055744.0);
+                            atomicAdd(pool + at[i] + c,
+                                      (unsigned long long)__double_as_longlong(sum) - 0x4338000000000000ull);
+                        }
+                } else {
 #pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const float wt = lt.w[i];
-                    if (wt == 0.0f) continue;
-                    const uint32_t x = i & 1 ? lt.xb : lt.xa, y = i & 2 ? lt.yb : lt.ya;
-                    float *gp = d.g_texels + 3u * (tx.tex_off[l] + y * wl + x);
+                    for (int i = 0; i < 4; ++i) {
+                        const float wt = lt.w[i];
+                        if (wt == 0.0f) continue;
+                        const uint32_t x = i & 1 ? lt.xb : lt.xa, y = i & 2 ? lt.yb : lt.ya;
+                        float *gp = d.g_texels + 3u * (tx.tex_off[l] + y * wl + x);
 #pragma unroll
-                    for (int c = 0; c < 3; ++c) {
-                        if (inside) atomicAdd(reinterpret_cast<float *>(pool + at[i] + c), wt * dz[c]);
-                        else unsafeAtomicAdd(gp + c, wt * dz[c]);
+                        for (int c = 0; c < 3; ++c) {
+                            if (inside) atomicAdd(reinterpret_cast<float *>(pool + at[i] + c), wt * dz[c]);
+                            else unsafeAtomicAdd(gp + c, wt * dz[c]);
+                        }
                     }
                 }
             }
         }
-    }
-    __syncthreads();
-    // Sums e = first, first + step, ... of level l's window to memory, the
-    // lanes along the channels of a row's texels.
-    auto flush = [&](uint32_t l, uint32_t first, uint32_t step) {
-        const TexWindow W = win[l];
-        const uint32_t wl = max(tx.w >> l, 1u), hl = max(tx.h >> l, 1u), base = tx.tex_off[l];
-        for (uint32_t e = first; e < 3u * W.w * W.h; e += step) {
-            const unsigned long long raw = pool[W.off + e];
-            const uint32_t lo = (uint32_t)raw;
-            // the signed sum as hi 2^32 + signed low half: both exact unless
-            // far above the last bit of the result
-            const float v = fixed ? fmaf((float)(int32_t)((uint32_t)(raw >> 32) + (lo >> 31)), 4294967296.0f,
-                                         (float)(int32_t)lo) * unscale
-                                  : __uint_as_float(lo);
-            const uint32_t p = e / 3u, c = e - 3u * p;
-            const uint32_t dy = W.w > 1u ? __umulhi(p, W.div_w) : p, dx = p - dy * W.w;
-            if (v != 0.0f)
-                unsafeAtomicAdd(
-                    d.g_texels + 3u * (base + ((W.y0 + dy) & (hl - 1u)) * wl + ((W.x0 + dx) & (wl - 1u))) + c, v);
+        __syncthreads();
+        // Sums e = first, first + step, ... of level l's window to memory, the
+        // lanes along the channels of a row's texels.
+        auto flush = [&](uint32_t l, uint32_t first, uint32_t step) {
+            const TexWindow W = win[l];
+            const uint32_t wl = max(tx.w >> l, 1u), hl = max(tx.h >> l, 1u), base = tx.tex_off[l];
+            for (uint32_t e = first; e < 3u * W.w * W.h; e += step) {
+                const unsigned long long raw = pool[W.off + e];
+                const uint32_t lo = (uint32_t)raw;
+                const float v = fixed ? (float)(fma((double)(int32_t)(raw >> 32), 4294967296.0, (double)lo) * unscale)
+                                      : __uint_as_float(lo);
+                const uint32_t p = e / 3u, c = e - 3u * p;
+                const uint32_t dy = W.w > 1u ? __umulhi(p, W.div_w) : p, dx = p - dy * W.w;
+                if (v != 0.0f)
+                    unsafeAtomicAdd(
+                        d.g_texels + 3u * (base + ((W.y0 + dy) & (hl - 1u)) * wl + ((W.x0 + dx) & (wl - 1u))) + c, v);
+            }
+        };
+        // the large windows by every wave, the small ones by one wave each
+        constexpr uint32_t kWaveSums = 256;
+        const uint32_t wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+        for (uint32_t l = 0; l < levels; ++l) {
+            if (win[l].off == ~0u) continue;
+            if (3u * win[l].w * win[l].h > kWaveSums) flush(l, threadIdx.x, blockDim.x);
+            else if (l % (blockDim.x / 64) == wv) flush(l, threadIdx.x & 63u, 64u);
         }
-    };
-    // the large windows by every wave, the small ones by one wave each
-    constexpr uint32_t kWaveSums = 256;
-    const uint32_t wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    for (uint32_t l = 0; l < levels; ++l) {
-        if (win[l].off == ~0u) continue;
-        if (3u * win[l].w * win[l].h > kWaveSums) flush(l, threadIdx.x, blockDim.x);
-        else if (l % (blockDim.x / 64) == wv) flush(l, threadIdx.x & 63u, 64u);
+        if (++pass == passes) return;
+        __syncthreads();
+        for (uint32_t e = threadIdx.x; e < used; e += blockDim.x) pool[e] = 0ull;
+        __syncthreads();
     }
 }
 

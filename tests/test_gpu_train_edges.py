@@ -57,3 +57,36 @@ def test_parameters_that_no_texel_uses_change_nothing(bcf, n_tex, straight, bad)
         for ge, gi in zip(got[0], got[1]):
             assert not ge[first:, 2:].any() and not gi[first:][dev(unused)].any()
             assert ge[first:, :2].any() and gi[first:].any()
+
+
+@pytest.mark.parametrize("ratio", [1e-4, 1e-9, 1e-13, 1e-20])
+@pytest.mark.parametrize("count", [3, 200])
+def test_small_gradients_beside_large_ones(bcf, ratio, count):
+    """Samples of one 64th of the material whose dL/dG is `ratio` times that of
+    the samples next to it: the gradients of the texels that only they touch
+    are as accurate (2e-4 of their largest, the training tests' bar) as without
+    the neighbours."""
+    g = synth.rng(1250 + count)
+    res, dims = 256, (3, 16, 4)                                  # a 64th is four texels
+    nb = synth.chain_blocks(res, res, 1)
+    tex = T.TrainTexture(res, res, 1, endpoints=g.uniform(0.0, 63.0, (nb, 4, 3)).astype(np.float32),
+                         indices=g.uniform(0.0, 1.0, (nb, 16)).astype(np.float32),
+                         partitions=g.integers(0, 32, nb).astype(np.uint8), lod_bias=0.0)
+    params = synth.mlp_params(dims, g).astype(np.float32)
+    geo = bcf.TrainGeometry([res], [1], [dev(tex.partitions)], dims)
+    for loud, quiet in (((0, 0), (1, 0)), ((10, 21), (10, 20)), ((33, 33), (32, 32))):
+        def inside(cell, n):
+            return np.concatenate([(np.array(cell) + g.uniform(0.15, 0.85, (n, 2))) / 64.0, np.zeros((n, 1))],
+                                  axis=1).astype(np.float32)
+        q = np.concatenate([inside(loud, count), inside(quiet, count)])
+        go = g.standard_normal((2 * count, 4))
+        go[count:] *= ratio
+        order = g.permutation(2 * count)
+        q, go = q[order], go[order].astype(np.float32)
+        got = bcf.train_backward(geo, [dev(tex.endpoints)], [dev(tex.indices)], dev(params), dev(q), dev(go))
+        _, r_end, r_idx, _ = T.gradients([tex], dims, params, q, go, False)
+        block = quiet[1] * 64 + quiet[0]                         # texels 4 cell .. 4 cell + 3: one block
+        for a, ref in ((got[0][0], r_end[0]), (got[1][0], r_idx[0])):
+            a, ref = a.cpu().numpy()[block].reshape(-1), ref[block].reshape(-1)
+            assert np.abs(ref).max() > 0.0
+            assert np.abs(a - ref).max() <= 2e-4 * np.abs(ref).max()
