@@ -153,11 +153,13 @@ bcf_status bcf_decode(const bcf_material *m, bcf_precision p, void *ws,
  * as in bcf_decode. No call allocates or frees memory (the first call on a
  * device looks up the array's device address once).
  * Returns BCF_ERR_UNSUPPORTED, before any launch, for a material whose
- * workspace (texel scratch and MLP operands, the size bcf_prepare reports)
- * exceeds BCF_NOALLOC_BYTES -- up to four 1024 x 1024 pyramids with full
- * chains fit. All calls on one GPU share its array and leave their data in
- * it: calls that overlap in time on one GPU (other streams, other threads)
- * race and give undefined results; order them on one stream. */
+ * workspace exceeds BCF_NOALLOC_BYTES -- up to four 1024 x 1024 pyramids with
+ * full chains fit. The workspace is the texel scratch and the MLP operands, the
+ * size bcf_prepare reports; for BCF_FP32, which bcf_prepare lays out twice, the
+ * operands count once, with 10 or 16 output rows. All calls on one GPU share
+ * its array and leave their data in it: calls that overlap in time on one GPU
+ * (other streams, other threads) race and give undefined results; order them
+ * on one stream. */
 #define BCF_NOALLOC_BYTES ((size_t)64 << 20)
 bcf_status bcf_decode_noalloc(const bcf_material *m, bcf_precision p, const float *queries, size_t n,
                               uint32_t grid_width, float *out, void *stream);

@@ -780,11 +780,12 @@ bcf_status bcf_decode_noalloc(const bcf_material *m, bcf_precision p, const floa
     if (m->act_absmax && !aligned(m->act_absmax, 4))
         return fail(BCF_ERR_INVALID_ARG, "act_absmax not 4-byte aligned");
     const bcf::WsLayout lay = layout(d, sh, kind);
-    if (lay.total > bcf::kNoAllocBytes)
+    const size_t need = p == BCF_FP32 ? layout(d, sh, bcf::MLP_VALU_F32).total : lay.total;
+    if (need > bcf::kNoAllocBytes)
         return fail(BCF_ERR_UNSUPPORTED,
                     "bcf_decode_noalloc: this material needs a %zu-byte workspace, the library's own holds %zu "
                     "(use bcf_prepare and bcf_decode with a caller workspace)",
-                    lay.total, bcf::kNoAllocBytes);
+                    need, bcf::kNoAllocBytes);
     void *ws = nullptr;
     if ((st = device_status(bcf::noalloc_workspace(&ws), "library workspace lookup")) != BCF_OK) return st;
     hipStream_t s = static_cast<hipStream_t>(stream);

@@ -62,8 +62,11 @@ struct WsLayout {
 };
 
 // The workspace bcf_decode_noalloc uses: a file-scope device array of
-// kNoAllocBytes (noalloc.hip), one per GPU, held until the process ends.
-constexpr size_t kNoAllocBytes = (size_t)64 << 20;
+// kNoAllocBytes (noalloc.hip), one per GPU, held until the process ends, and
+// kNoAllocSlack for BCF_FP32's output layer: the limit counts its true rows
+// (padded to 10 or 16), the matrix cores' operands have 16 of up to 64 columns.
+constexpr size_t kNoAllocBytes = (size_t)64 << 20, kNoAllocSlack = 2048;
+static_assert((kMaxOut - 10) * kMaxHidden * sizeof(float) <= kNoAllocSlack, "six more rows of operands");
 // its device address on the current device (looked up on the first call per device)
 hipError_t noalloc_workspace(void **ptr);
 

@@ -9,7 +9,7 @@
 
 namespace bcf {
 
-static __device__ __align__(256) uint8_t scratch[kNoAllocBytes];
+static __device__ __align__(256) uint8_t scratch[kNoAllocBytes + kNoAllocSlack];
 
 namespace {
 

@@ -1,0 +1,48 @@
+"""Edges of the decode calls: the largest materials that fit the library's own
+workspace, and unpacks that must store every texel."""
+import numpy as np
+import pytest
+
+import synth
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def bcf():
+    if not torch.cuda.is_available():
+        pytest.fail("GPU tests need a visible MI355X")
+    import paper_2311_16121_amd as bcf
+    return bcf
+
+
+def dev(x):
+    return torch.from_numpy(np.ascontiguousarray(x)).cuda()
+
+
+def material(bcf, sizes, levels, dims, seed, signed=False):
+    """Pyramids of the same bounded random blocks over and over, each rolled."""
+    g = synth.rng(seed)
+    block = synth.bounded_blocks(4096, g, signed=signed).reshape(-1)
+    texs = [np.resize(np.roll(block, 16 * 7 * t), 16 * synth.chain_blocks(w, h, n))
+            for t, ((w, h), n) in enumerate(zip(sizes, levels))]
+    return bcf.Material.from_host(texs, sizes, levels, dims, synth.mlp_params(dims, g), [0.0] * len(sizes), signed)
+
+
+@pytest.mark.parametrize("sizes,levels,dims,fits", [
+    # texel scratch and row-major operands 67,107,584, 67,108,608 and 67,108,864 (= 64 MiB) bytes
+    ([(512, 4096), (512, 8192)], [3, 5], (6, 64, 64, 10), True),
+    ([(1, 1), (8192, 256), (512, 8192)], [1, 4, 4], (9, 32, 32, 10), True),
+    ([(8192, 256), (4096, 1024)], [9, 5], (6, 16, 16, 8), True),
+    ([(8192, 256), (4096, 1024)], [9, 5], (6, 16, 16, 11), False)])
+def test_fp32_materials_that_just_fit_the_librarys_workspace(bcf, sizes, levels, dims, fits):
+    """BCF_FP32 counts its operands' true rows against the 64 MiB."""
+    mat = material(bcf, sizes, levels, dims, 300)
+    q = dev(synth.uniform_queries(2000, synth.rng(301), max(levels) - 1.0))
+    if not fits:
+        with pytest.raises(bcf.BcfError, match="status 2.*workspace"):
+            bcf.decode_noalloc(mat, q)
+        return
+    want = bcf.decode(mat, bcf.prepare(mat), q)
+    assert torch.equal(bcf.decode_noalloc(mat, q).view(torch.int32), want.view(torch.int32))
