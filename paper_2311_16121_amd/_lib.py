@@ -136,11 +136,14 @@ def texture_bytes(width: int, height: int, levels: int) -> int:
 def _stream(stream):
     """The stream's handle; None: torch's current stream on the current device."""
     import torch
-    if stream is not None:
-        return C.c_void_p(stream.cuda_stream)
-    # torch.cuda.current_stream() builds a Stream object for this: 2.9 us, a
-    # fifth of a small decode; the handle alone 0.2 us
-    return C.c_void_p(torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice()))
+    if stream is None:
+        # torch.cuda.current_stream() builds a Stream object for this: 2.9 us, a
+        # fifth of a small decode; the handle alone 0.2 us, where torch has the call
+        try:
+            return C.c_void_p(torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice()))
+        except AttributeError:
+            stream = torch.cuda.current_stream()
+    return C.c_void_p(stream.cuda_stream)
 
 
 class Material:

@@ -1,0 +1,25 @@
+"""The Python binding's own choices, on the CPU."""
+import types
+
+import pytest
+
+torch = pytest.importorskip("torch")
+
+
+@pytest.fixture(scope="module")
+def binding():
+    import paper_2311_16121_amd._lib as binding
+    return binding
+
+
+@pytest.mark.parametrize("missing", ["_cuda_getCurrentRawStream", "_cuda_getDevice"])
+def test_stream_handle_without_torchs_private_calls(binding, monkeypatch, missing):
+    """A torch without one of the private calls gives its current stream's
+    handle through the public one."""
+    monkeypatch.setattr(torch._C, "_cuda_getDevice", lambda: 3, raising=False)
+    monkeypatch.setattr(torch._C, "_cuda_getCurrentRawStream", lambda d: 1000 + d, raising=False)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: types.SimpleNamespace(cuda_stream=77))
+    assert binding._stream(None).value == 1003
+    assert binding._stream(types.SimpleNamespace(cuda_stream=55)).value == 55
+    monkeypatch.delattr(torch._C, missing)
+    assert binding._stream(None).value == 77
