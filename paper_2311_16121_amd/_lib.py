@@ -233,7 +233,10 @@ def _queries(queries):
 def _out(mat: Material, q, out):
     import torch
     if out is None:
-        return q.new_empty((q.shape[0], mat.out_dim))
+        # new_empty: 2.6 us less; of a subclass it would be one too
+        if type(q) is torch.Tensor:
+            return q.new_empty((q.shape[0], mat.out_dim))
+        return torch.empty((q.shape[0], mat.out_dim), dtype=torch.float32, device=q.device)
     if (out.dtype != torch.float32 or not out.is_cuda or not out.is_contiguous()
             or tuple(out.shape) != (q.shape[0], mat.out_dim)):
         raise TypeError(f"out must be a contiguous float32 device tensor of shape [{q.shape[0]}, {mat.out_dim}]")

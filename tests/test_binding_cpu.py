@@ -23,3 +23,15 @@ def test_stream_handle_without_torchs_private_calls(binding, monkeypatch, missin
     assert binding._stream(types.SimpleNamespace(cuda_stream=55)).value == 55
     monkeypatch.delattr(torch._C, missing)
     assert binding._stream(None).value == 77
+
+
+def test_outputs_are_plain_tensors(binding):
+    """Queries of a tensor subclass decode into an ordinary tensor."""
+    class Queries(torch.Tensor):
+        pass
+
+    mat = types.SimpleNamespace(out_dim=5)
+    for q in (torch.zeros(3, 3), torch.zeros(3, 3).as_subclass(Queries), torch.nn.Parameter(torch.zeros(3, 3))):
+        out = binding._out(mat, q, None)
+        assert type(out) is torch.Tensor and out.shape == (3, 5) and out.dtype == torch.float32
+        assert not out.requires_grad
