@@ -346,8 +346,10 @@ bcf::WsLayout layout(const bcf::MaterialDesc &d, const bcf::MlpShape &sh, bcf::M
     return lay;
 }
 
-// Where a BCF_FP32 workspace keeps the calibration's operands (bcf_calibrate
-// writes them itself): after everything the decode reads.
+// Where a BCF_FP32 workspace keeps the calibration's operands: after everything
+// the decode reads. bcf_prepare writes both sets in one launch; written by each
+// bcf_calibrate instead, the calibration's scalar loads met cold caches (100
+// queries of 12-64-64-64-16 on 4 x 64^2: 145 us a call against 87).
 bcf::WsLayout calibration_layout(const bcf::WsLayout &decode, const bcf::MlpShape &sh)
 {
     bcf::WsLayout lay = weights_layout(sh, bcf::MLP_VALU_F32, decode.total);
@@ -665,7 +667,8 @@ bcf_status bcf_prepare(const bcf_material *m, bcf_precision p, void *ws, size_t 
     if (!kind_of(p, &kind)) return fail(BCF_ERR_UNSUPPORTED, "precision %d not supported", (int)p);
     if (!ws_bytes) return fail(BCF_ERR_INVALID_ARG, "ws_bytes is NULL");
     const bcf::WsLayout lay = layout(d, sh, kind);
-    const size_t total = p == BCF_FP32 ? calibration_layout(lay, sh).total : lay.total;
+    const bcf::WsLayout cal = calibration_layout(lay, sh);      // BCF_FP32 only
+    const size_t total = p == BCF_FP32 ? cal.total : lay.total;
     if (!ws) {
         *ws_bytes = total;
         return BCF_OK;
@@ -680,7 +683,7 @@ bcf_status bcf_prepare(const bcf_material *m, bcf_precision p, void *ws, size_t 
     const uint64_t hash = material_hash(kFnvOffset, m, p);
     const bcf::WsHeader header = ws_header(p, 1, hash, lay.scratch_off, lay.scratch_bytes, total);
     st = device_status(bcf::launch_prepare_weights(m->params, m->act_absmax, sh, kind, lay, ws, &header,
-                                                   static_cast<hipStream_t>(stream)),
+                                                   static_cast<hipStream_t>(stream), p == BCF_FP32 ? &cal : nullptr),
                        "prepare launch");
     if (st == BCF_OK) remember_ws(ws, WsTag{(int)p, 1u, hash});
     return st;
@@ -754,9 +757,6 @@ bcf_status bcf_calibrate(const bcf_material *m, void *ws, const float *queries, 
         return st;
     const bcf::WsLayout lay = calibration_layout(layout(d, sh, bcf::MLP_MFMA_F32), sh);
     hipStream_t s = static_cast<hipStream_t>(stream);
-    st = device_status(bcf::launch_prepare_weights(m->params, nullptr, sh, bcf::MLP_VALU_F32, lay, ws, nullptr, s),
-                       "prepare launch");
-    if (st != BCF_OK) return st;
     st = unpack(d, lay, ws, n, 0, s);
     if (st != BCF_OK) return st;
     return device_status(bcf::launch_calibrate(d, sh, lay, ws, queries, n, act_absmax, s), "calibrate launch");

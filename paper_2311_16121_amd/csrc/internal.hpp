@@ -131,10 +131,11 @@ struct WsHeader {
 };
 constexpr uint32_t kWsMagic = 0x57464342u;   // "BCFW"
 
-// header: written to the workspace's first bytes by the same launch (NULL: not written)
+// header: written to the workspace's first bytes by the same launch (NULL: not written);
+// calibration: the row-major operands too, where this layout puts them (NULL: not)
 hipError_t launch_prepare_weights(const float *params, const float *act_absmax, const MlpShape &sh,
                                   MlpKind kind, const WsLayout &lay, void *ws, const WsHeader *header,
-                                  hipStream_t s);
+                                  hipStream_t s, const WsLayout *calibration = nullptr);
 // launch_prepare_weights and launch_predecode, in one launch where the operands allow
 hipError_t launch_prepare_unpack(const float *params, const float *act_absmax, const MlpShape &sh, MlpKind kind,
                                  const WsLayout &lay, void *ws, const WsHeader &header, const MaterialDesc &m,

@@ -529,6 +529,13 @@ __device__ __forceinline__ void prepare_weights(const PrepareArgs &a, uint32_t b
 
 __global__ void __launch_bounds__(256) k_prepare(PrepareArgs a) { prepare_weights(a, blockIdx.x); }
 
+// Two sets of operands from the same parameters, in one launch.
+__global__ void __launch_bounds__(256) k_prepare_both(PrepareArgs a, PrepareArgs b)
+{
+    if (blockIdx.x < kPrepareBlocks) prepare_weights(a, blockIdx.x);
+    else prepare_weights(b, blockIdx.x - kPrepareBlocks);
+}
+
 // The unpack and the operands of a call that needs both, in one launch: the
 // workgroups past the unpack's convert the weights (65,536 queries without a
 // caller's workspace, where three launches were the cost: 17.8 -> 13.5 us).
@@ -549,7 +556,7 @@ __global__ void __launch_bounds__(256) k_predecode_prepare(PredecodeArgs a, Prep
 
 hipError_t launch_prepare_weights(const float *params, const float *act_absmax, const MlpShape &sh,
                                   MlpKind kind, const WsLayout &lay, void *ws, const WsHeader *header,
-                                  hipStream_t s)
+                                  hipStream_t s, const WsLayout *calibration)
 {
     PrepareArgs a{params, act_absmax, sh, kind, lay, static_cast<uint8_t *>(ws), {}, 0u};
     if (header) {
@@ -561,7 +568,12 @@ hipError_t launch_prepare_weights(const float *params, const float *act_absmax, 
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
-    k_prepare<<<kPrepareBlocks, 256, 0, s>>>(a);
+    if (calibration) {
+        const PrepareArgs b{params, nullptr, sh, MLP_VALU_F32, *calibration, static_cast<uint8_t *>(ws), {}, 0u};
+        k_prepare_both<<<2 * kPrepareBlocks, 256, 0, s>>>(a, b);
+    } else {
+        k_prepare<<<kPrepareBlocks, 256, 0, s>>>(a);
+    }
     return hipGetLastError();
 }
 

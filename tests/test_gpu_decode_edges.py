@@ -46,3 +46,27 @@ def test_fp32_materials_that_just_fit_the_librarys_workspace(bcf, sizes, levels,
         return
     want = bcf.decode(mat, bcf.prepare(mat), q)
     assert torch.equal(bcf.decode_noalloc(mat, q).view(torch.int32), want.view(torch.int32))
+
+
+def test_calibration_evaluates_the_prepared_parameters(bcf):
+    """Until it is prepared again, a workspace decodes and calibrates with the
+    parameters that bcf_prepare converted."""
+    import ctypes as C
+    dims = (6, 33, 24, 7)
+    mat = material(bcf, [(64, 32)] * 2, [7, 7], dims, 310)
+    q = dev(synth.uniform_queries(700, synth.rng(311), 6.0))
+    ws = bcf.prepare(mat)
+
+    def evaluate():
+        absmax = torch.empty(len(dims) - 1, device="cuda")
+        assert bcf.lib.bcf_calibrate(C.byref(mat.c), C.c_void_p(ws.data_ptr()), C.c_void_p(q.data_ptr()), len(q),
+                                     C.c_void_p(absmax.data_ptr()), C.c_void_p(torch.cuda.current_stream().cuda_stream)) == 0
+        return bcf.decode(mat, ws, q), absmax
+
+    before = evaluate()
+    assert torch.equal(before[1], bcf.calibrate(mat, q))
+    mat.params.mul_(2.0)
+    after = evaluate()
+    assert all(torch.equal(a, b) for a, b in zip(before, after))
+    ws = bcf.prepare(mat)
+    assert float(evaluate()[1][1]) > 1.5 * float(before[1][1])
