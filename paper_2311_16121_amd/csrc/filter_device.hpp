@@ -253,16 +253,16 @@ constexpr int kLayoutSplit = 0, kLayoutShared = 1, kLayoutPacked = 2;
 // z[3t + c] = T_t(u, v, s) channel c for the four pyramid slots (slots past
 // the material's pyramids repeat slot 0, or are zero; their MLP weights are zero).
 // kLayoutShared / kLayoutPacked: every slot has the same w, h, levels and
-// bias, so one footprint serves all four. IN_TURN (kLayoutSplit): a
-// footprint's two loads are blended before the next footprint's are issued;
-// otherwise they are loaded four footprints ahead. An image's footprints share
-// lines, and the loads in flight hide the latency (1366 x 768 bf16 24.9 us in
-// turn, 23.5 ahead; two ahead and the compiler's own order are within the noise
-// of that, but that order changed with code around it and then took 26.3);
-// scattered points share none, and more of them in flight only evict each
-// other (300,000 points of 2048 to 256 texels 29.4 us in turn, 31.4 ahead), so
-// launches that declare no image take them in turn.
-template <int LAYOUT, bool IN_TURN = true>
+// bias, so one footprint serves all four. kLayoutSplit: a footprint is loaded
+// four footprints before it is blended, in this order whatever code is around
+// it; IN_TURN: one footprint's loads are blended before the next one's are
+// issued. 2^22 points of 1024 to 128 texels: fp32 12-32-32-10 197 us ahead, 258
+// in turn and 256 in the compiler's own order, fp16 174, 173 and 174; 12-64-8
+// 196 and 253, 12-64-64-10 539 and 600; a 1366 x 768 image in bf16 23.5 and
+// 24.9. Only k_batch takes them in turn, whose waves are at different materials
+// and evict each other's lines: 8 x 600,000 points of 512 to 64 texels (fp16)
+// 198 us in turn, 206 ahead, 24 x 230,000 250 and 253.
+template <int LAYOUT, bool IN_TURN = false>
 __device__ __forceinline__ void filter4(__amdgpu_buffer_rsrc_t rs, const LevelLut &lut,
                                         const float *levels_bias, uint32_t stride, float u, float v,
                                         float s, float z[12])

@@ -255,7 +255,7 @@ __device__ __forceinline__ void mlp_stage(const float z[12], const MfmaMlp<K, H,
 }
 
 // One wave's 64 queries: filter (eqs. 9, 10), concatenate, MLP.
-template <bool YIELD, MlpKind K, int H, int NH, int LAYOUT, bool IN_TURN = true>
+template <bool YIELD, MlpKind K, int H, int NH, int LAYOUT, bool IN_TURN = false>
 __device__ __forceinline__ void decode_wave(const Query &qq, __amdgpu_buffer_rsrc_t rs, const LevelLut &lut,
                                             const float *levels_bias, uint32_t stride,
                                             const MfmaMlp<K, H, NH> &mlp, float4_t (*feats)[4], float *st, uint32_t out_dim, uint32_t lane)
@@ -504,8 +504,8 @@ __global__ void __launch_bounds__(kFrameThreads) k_frame(FrameArgs a)
                 item = locate(k);
                 const Query qq = next;
                 if (k + items.step < items.end) next = query(k + items.step);
-                decode_wave<true, K, H, NH, kLayoutSplit, KIND == kItemLinear>(
-                    qq, rs, lut, a.levels_bias, a.stride, mlp, feats, st, a.out_dim, lane);
+                decode_wave<true, K, H, NH, kLayoutSplit>(qq, rs, lut, a.levels_bias, a.stride, mlp, feats, st,
+                                                          a.out_dim, lane);
                 store_item<KIND>(a, oob, st, ro, item, li, lane);
                 wave_lds_sync();
             }
@@ -725,7 +725,7 @@ __global__ void __launch_bounds__(64 * W) k_batch(BatchArgs a)
         else if (shared)
             decode_wave<false, K, H, NH, kLayoutShared>(qq, rs, lut[wv], lb, stride, mlp, feats, st, a.out_dim, lane);
         else
-            decode_wave<false, K, H, NH, kLayoutSplit>(qq, rs, lut[wv], lb, stride, mlp, feats, st, a.out_dim, lane);
+            decode_wave<false, K, H, NH, kLayoutSplit, true>(qq, rs, lut[wv], lb, stride, mlp, feats, st, a.out_dim, lane);
         store_run(stage[wv], ro, j, n_k, a.out_dim, lane);
         wave_lds_sync();
     }
