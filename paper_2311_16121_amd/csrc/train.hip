@@ -561,12 +561,15 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 // outputs come back through LDS to each query's lane.
 // Waves per SIMD the forward's registers are laid out for (the filter's loads
 // in flight against the waves beside it; 0: the compiler's choice). Measured,
-// 2^20 samples, default -> chosen: halves 12-32-32-10 82 -> 65 us and
-// 12-32-32-32-10 76 (4: 98); floats 130 -> 96 and 100 (3: 111); images of four
-// sizes 98 (3: 123) and 157 -> 129.
+// 2^20 samples, the compiler's choice -> this: halves 12-32-32-10 83 -> 78 us,
+// 12-16-16-10 66 -> 66, three hidden layers of 32 or 16 91 and 68 (4: 91, 67);
+// floats 126 -> 106 and 109 -> 101, one layer of 16 114 -> 100, of 32 96 -> 101,
+// three of 32 128 (3: 127), of 16 111 (3: 101). The images take the compiler's:
+// one pyramid, three layers of 16 91 (3: 129, 4: 100), of 32 113 (3: 124, 4:
+// 124); four sizes 100 (128, 114) and 120 (135, 131).
 constexpr int forward_waves(int NH, int PACK)
 {
-    return PACK == 1 ? (NH < 3 ? 4 : 0) : PACK == 2 ? (NH < 3 ? 3 : 0) : NH < 3 ? 0 : 3;
+    return NH == 3 || PACK == 0 ? 0 : PACK == 1 ? 4 : 3;
 }
 
 template <int H, int NH, int PACK>
