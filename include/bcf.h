@@ -258,19 +258,21 @@ bcf_status bcf_unpack_batch(const bcf_material *mats, uint32_t n_mats, void *ws,
  * other queries needs its own unpack. queries, offsets and n_total as for
  * bcf_decode_batch (device memory; offsets read on the device). For the
  * position-interleaved materials the footprints' block positions are first
- * marked in a byte table of the workspace (three launches: clear, item
- * prefix, mark), then one launch unpacks the marked positions and every
- * block of the other materials. Asynchronous, no allocation or host
- * synchronisation: it can be captured in a graph with bcf_decode_batch.
+ * marked in a byte table of the workspace (two launches, of more than 64
+ * materials three), then one launch unpacks the marked positions and every
+ * block of the other materials. A batch in which marking costs more than it
+ * saves (nothing to mark, or three pyramids of little scratch alone) is
+ * unpacked whole. Asynchronous, no allocation or host synchronisation: it can
+ * be captured in a graph with bcf_decode_batch.
  * Errors as for bcf_unpack_batch, and BCF_ERR_INVALID_ARG for NULL or
  * misaligned queries (n_total > 0) or offsets. */
 bcf_status bcf_unpack_batch_touched(const bcf_material *mats, uint32_t n_mats, void *ws, const float *queries,
                                     const uint32_t *offsets, uint32_t n_total, void *stream);
 
-/* Decodes every material's queries in one persistent launch (after a small
- * launch that turns offsets into work items). Asynchronous and free of host
- * synchronisation and allocation, so it can be captured in a graph together
- * with bcf_unpack_batch. plan may be NULL. */
+/* Decodes every material's queries in one persistent launch (of more than 64
+ * materials after a small one that turns offsets into work items).
+ * Asynchronous and free of host synchronisation and allocation, so it can be
+ * captured in a graph together with bcf_unpack_batch. plan may be NULL. */
 bcf_status bcf_decode_batch(const bcf_material *mats, uint32_t n_mats, bcf_precision p, void *ws,
                             const float *queries, const uint32_t *offsets, uint32_t n_total,
                             float *out, const bcf_batch_plan *plan, void *stream);

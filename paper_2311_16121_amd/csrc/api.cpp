@@ -554,6 +554,7 @@ struct BatchLayout {
     size_t table_off, items_off, segs_off, chunk_seg_off, marks_off, units_off, total;
     uint32_t n_seg, n_chunks;               // unpack segments of every material, their chunks of 256 lanes
     uint32_t n_units;                       // work units of the touched-blocks unpack
+    bool touched_whole;                     // it unpacks every block instead (kWholeScratch3)
     std::vector<bcf::BatchSlot> slots;
     std::vector<bcf::MaterialDesc> descs;
     bcf::MlpShape sh;
@@ -571,6 +572,16 @@ bool unpack_past_caches(const BatchLayout &b)
     for (const bcf::BatchSlot &s : b.slots) scratch += s.scratch_bytes;
     return scratch > kCachedScratch;
 }
+
+// bcf_unpack_batch_touched unpacks every block where no block would be marked,
+// and where only materials of three pyramids would be and their scratch is at
+// most this: marking is a chain of three launches, with which the unpack of a
+// few megabytes is done (and before those were packed, it was whole). With
+// the decode, marked and whole: one material of 256 x 256 (2 MB), 5,000 queries
+// 34.9 and 10.2 us; 24 (50 MB), 100 queries each 38.2 and 23.5, 60,000 106.7 and
+// 70.0; one of 1024 x 1024 (34 MB), 100 queries 25.4 and 18.2. Eight of 512 x
+// 512 (67 MB) with 100 queries 28.4 marked, 41 whole when they were unpacked.
+constexpr size_t kWholeScratch3 = (size_t)64 << 20;
 
 constexpr uint32_t kMaxBatch = 4096;
 
@@ -592,6 +603,8 @@ bcf_status describe_batch(const bcf_material *mats, uint32_t n_mats, bcf_precisi
     b->n_seg = 0;
     b->n_chunks = 0;
     b->n_units = 0;
+    size_t scratch3 = 0;                    // of the packed materials of three pyramids
+    bool four = false;                      // some packed material has four
     for (uint32_t k = 0; k < n_mats; ++k) {
         bcf::MlpShape sh;
         const bcf_status st = describe(&mats[k], &b->descs[k], &sh);
@@ -613,7 +626,10 @@ bcf_status describe_batch(const bcf_material *mats, uint32_t n_mats, bcf_precisi
             const uint32_t chunks = plan.seg_wg[j + 1] - plan.seg_wg[j];
             b->n_units += b->descs[k].interleaved ? (chunks + 3) / 4 : chunks;
         }
+        if (b->descs[k].interleaved && b->descs[k].n_tex == 3) scratch3 += scratch_texels(b->descs[k]) * 8;
+        else four = four || b->descs[k].interleaved;
     }
+    b->touched_whole = !four && scratch3 <= kWholeScratch3;
     off = align_up(off + sizeof(bcf::UnpackSeg) * b->n_seg, 256);
     b->chunk_seg_off = off;                 // segment of each unpack chunk
     off = align_up(off + sizeof(uint32_t) * b->n_chunks, 256);
@@ -633,6 +649,16 @@ bcf_status describe_batch(const bcf_material *mats, uint32_t n_mats, bcf_precisi
     }
     b->total = off;
     return BCF_OK;
+}
+
+// every block, in one launch over the segment table bcf_prepare_batch wrote
+bcf_status unpack_batch(const BatchLayout &b, const void *ws, hipStream_t s)
+{
+    const uint8_t *base = static_cast<const uint8_t *>(ws);
+    const bcf::UnpackSeg *segs = reinterpret_cast<const bcf::UnpackSeg *>(base + b.segs_off);
+    const uint32_t *chunk_seg = reinterpret_cast<const uint32_t *>(base + b.chunk_seg_off);
+    return device_status(bcf::launch_predecode_batch(segs, chunk_seg, b.n_chunks, unpack_past_caches(b), s),
+                         "unpack launch");
 }
 
 uint64_t batch_hash(const bcf_material *mats, uint32_t n_mats, bcf_precision p)
@@ -943,13 +969,7 @@ bcf_status bcf_unpack_batch(const bcf_material *mats, uint32_t n_mats, void *ws,
     // either batch precision: the texel scratch layout is the same (and so is the hash)
     if ((st = check_ws(ws, -1, n_mats, batch_hash(mats, n_mats, BCF_FP16), "bcf_prepare_batch")) != BCF_OK)
         return st;
-    // one launch over the segment table bcf_prepare_batch wrote
-    const uint8_t *base = static_cast<const uint8_t *>(ws);
-    const bcf::UnpackSeg *segs = reinterpret_cast<const bcf::UnpackSeg *>(base + b.segs_off);
-    const uint32_t *chunk_seg = reinterpret_cast<const uint32_t *>(base + b.chunk_seg_off);
-    return device_status(bcf::launch_predecode_batch(segs, chunk_seg, b.n_chunks, unpack_past_caches(b),
-                                                     static_cast<hipStream_t>(stream)),
-                         "unpack launch");
+    return unpack_batch(b, ws, static_cast<hipStream_t>(stream));
 }
 
 namespace {
@@ -987,8 +1007,9 @@ bcf_status bcf_unpack_batch_touched(const bcf_material *mats, uint32_t n_mats, v
     // either batch precision: the tables and the scratch layout are the same (and so is the hash)
     if ((st = check_ws(ws, -1, n_mats, batch_hash(mats, n_mats, BCF_FP16), "bcf_prepare_batch")) != BCF_OK)
         return st;
-    uint8_t *base = static_cast<uint8_t *>(ws);
     const hipStream_t s = static_cast<hipStream_t>(stream);
+    if (b.touched_whole) return unpack_batch(b, ws, s);
+    uint8_t *base = static_cast<uint8_t *>(ws);
     st = device_status(bcf::launch_batch_mark(ws, b.table_off, b.items_off, queries, offsets, n_mats, n_total,
                                               base + b.marks_off, (size_t)64 * b.n_chunks, s),
                        "mark launch");

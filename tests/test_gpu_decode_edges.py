@@ -70,3 +70,45 @@ def test_calibration_evaluates_the_prepared_parameters(bcf):
     assert all(torch.equal(a, b) for a, b in zip(before, after))
     ws = bcf.prepare(mat)
     assert float(evaluate()[1][1]) > 1.5 * float(before[1][1])
+
+
+def three_pyramids(bcf, n_mats, res, per, seed):
+    """(batch on a workspace of ones, materials, queries, offsets) of three pyramids of one geometry."""
+    levels = res.bit_length()
+    mats = [material(bcf, [(res, res)] * 3, [levels] * 3, (9, 16, 5), seed + k) for k in range(min(n_mats, 3))]
+    mats = [mats[k % len(mats)] for k in range(n_mats)]
+    q = synth.uniform_queries(n_mats * per, synth.rng(seed + 9), levels - 1.0)
+    q[:, :2] = q[:, :2] * 3.0 - 1.0
+    offsets = np.arange(0, n_mats * per + 1, per, dtype=np.int32)
+    return bcf.Batch(mats, bcf.Precision.FP16, ws_fill=0xFF), mats, dev(q), dev(offsets)
+
+
+@pytest.mark.parametrize("n_mats,res", [(9, 512), (5, 1024)])
+def test_three_pyramids_in_a_large_scratch_are_marked(bcf, n_mats, res):
+    """Above 64 MiB the touched unpack marks the blocks of packed materials of
+    three pyramids: decodes equal the single materials', on texels of NaN."""
+    per = 333
+    batch, mats, q, offsets = three_pyramids(bcf, n_mats, res, per, 320)
+    batch.unpack_touched(q, offsets)
+    got = batch.decode(q, offsets)
+    elsewhere = q.roll(per, 0) + torch.tensor([0.37, 0.37, 0.0], device="cuda")
+    partly = batch.decode(elsewhere, offsets)
+    batch.unpack()
+    assert not torch.equal(batch.decode(elsewhere, offsets), partly)      # blocks that no query touched were not there
+    for k, mat in enumerate(mats):
+        part = slice(k * per, (k + 1) * per)
+        want = bcf.decode(mat, bcf.prepare(mat, bcf.Precision.FP16), q[part], bcf.Precision.FP16)
+        assert torch.equal(got[part], want)
+
+
+@pytest.mark.parametrize("n_mats,res", [(1, 64), (7, 512), (70, 64)])
+def test_three_pyramids_in_a_small_scratch_are_unpacked_whole(bcf, n_mats, res):
+    """Up to 64 MiB it unpacks them whole: any decode equals the single one."""
+    per = 65
+    batch, mats, q, offsets = three_pyramids(bcf, n_mats, res, per, 340)
+    batch.unpack_touched(q[:1], torch.zeros_like(offsets))
+    got = batch.decode(q, offsets)
+    for k, mat in enumerate(mats):
+        part = slice(k * per, (k + 1) * per)
+        want = bcf.decode(mat, bcf.prepare(mat, bcf.Precision.FP16), q[part], bcf.Precision.FP16)
+        assert torch.equal(got[part], want)
