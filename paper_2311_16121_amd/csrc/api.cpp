@@ -562,16 +562,18 @@ struct BatchLayout {
     bcf::MlpKind kind;
 };
 
+size_t batch_scratch(const BatchLayout &b)
+{
+    size_t scratch = 0;
+    for (const bcf::BatchSlot &s : b.slots) scratch += s.scratch_bytes;
+    return scratch;
+}
+
 // Likewise for a batch, by the scratch of all its materials: whole unpack and
 // decode, ordinarily and past the caches, 8 materials of 35 MB 29.2 and 31.2 us,
 // 3 of 63 MB 37.1 and 40.9, 8 of 78 MB 61.4 and 61.2, 4 of 109 MB 47.6 and 37.2,
 // 20 of 274 MB 150.0 and 136.6, 24 of 906 MB 594.5 and 527.0.
-bool unpack_past_caches(const BatchLayout &b)
-{
-    size_t scratch = 0;
-    for (const bcf::BatchSlot &s : b.slots) scratch += s.scratch_bytes;
-    return scratch > kCachedScratch;
-}
+bool unpack_past_caches(const BatchLayout &b) { return batch_scratch(b) > kCachedScratch; }
 
 // bcf_unpack_batch_touched unpacks every block where no block would be marked,
 // and where only materials of three pyramids would be and their scratch is at
@@ -1018,7 +1020,8 @@ bcf_status bcf_unpack_batch_touched(const bcf_material *mats, uint32_t n_mats, v
                                                        reinterpret_cast<const uint32_t *>(base + b.chunk_seg_off),
                                                        b.n_seg, b.n_chunks,
                                                        reinterpret_cast<const uint32_t *>(base + b.units_off),
-                                                       b.n_units, base + b.marks_off, unpack_past_caches(b), s),
+                                                       b.n_units, base + b.marks_off, unpack_past_caches(b),
+                                                       batch_scratch(b), s),
                          "unpack launch");
 }
 

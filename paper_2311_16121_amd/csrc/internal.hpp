@@ -102,10 +102,11 @@ hipError_t launch_predecode_batch(const UnpackSeg *segs, const uint32_t *chunk_s
                                   hipStream_t s);
 // Unpacks the marked block positions of the interleaved segments and every
 // chunk of the others: units[u] = first chunk of unit u (a window of up to
-// four chunks of one interleaved segment, or one chunk of another segment).
+// four chunks of one interleaved segment, or one chunk of another segment);
+// scratch_bytes: of the whole batch.
 hipError_t launch_predecode_touched(const UnpackSeg *segs, const uint32_t *chunk_seg, uint32_t n_seg,
                                     uint32_t n_chunks, const uint32_t *units, uint32_t n_units, const uint8_t *marks,
-                                    bool nt, hipStream_t s);
+                                    bool nt, size_t scratch_bytes, hipStream_t s);
 // Clears marks[0..mark_bytes) (a multiple of 16), fills the batch's item
 // prefix, and marks the block positions the queries of the interleaved
 // materials read.

@@ -271,11 +271,10 @@ __global__ void __launch_bounds__(256) k_predecode_batch(const UnpackSeg *segs, 
 // positions it gathers in LDS and unpacks, 64 positions per pass (most
 // windows need one pass with one or two busy waves); for any other segment,
 // one whole chunk. marks[64 c + p] != 0: position p of chunk c is needed.
-// Scattered positions are stored ordinarily at any size, so that the L2s
-// gather their 12-byte pieces into lines (24 materials of 906 MB in all, 5.5
-// million queries, with marking and decode: past the caches 438.0 us,
-// ordinarily 425.0; 20 of 274 MB 127.5 and 121.8); NT: whole chunks.
-template <bool NT>
+// NT: whole chunks are stored non-temporally, LIST_NT: scattered positions too.
+// Their 12-byte pieces are best gathered into lines by the L2s and left in the
+// memory-side cache (256 MB) until far more of them come (launch_predecode_touched).
+template <bool NT, bool LIST_NT>
 __global__ void __launch_bounds__(256) k_predecode_touched(const UnpackSeg *segs, const uint32_t *chunk_seg,
                                                            uint32_t n_seg, uint32_t n_chunks, const uint32_t *units,
                                                            uint32_t n_units, const uint8_t *marks)
@@ -317,8 +316,8 @@ __global__ void __launch_bounds__(256) k_predecode_touched(const UnpackSeg *segs
         __syncthreads();
         for (uint32_t p0 = 0; p0 < total; p0 += 64) {
             const uint32_t n = min(64u, total - p0);
-            if (sgn) unpack_chunk<true, false>(sg, 0, table, palette, slots, list + p0, n);
-            else unpack_chunk<false, false>(sg, 0, table, palette, slots, list + p0, n);
+            if (sgn) unpack_chunk<true, LIST_NT>(sg, 0, table, palette, slots, list + p0, n);
+            else unpack_chunk<false, LIST_NT>(sg, 0, table, palette, slots, list + p0, n);
             __syncthreads();
         }
     }
@@ -326,11 +325,19 @@ __global__ void __launch_bounds__(256) k_predecode_touched(const UnpackSeg *segs
 
 hipError_t launch_predecode_touched(const UnpackSeg *segs, const uint32_t *chunk_seg, uint32_t n_seg,
                                     uint32_t n_chunks, const uint32_t *units, uint32_t n_units, const uint8_t *marks,
-                                    bool nt, hipStream_t s)
+                                    bool nt, size_t scratch_bytes, hipStream_t s)
 {
     if (n_units == 0) return hipSuccess;
     const unsigned grid = std::min<unsigned>(n_units, 1u << 22);
-    (nt ? k_predecode_touched<true> : k_predecode_touched<false>)<<<grid, 256, 0, s>>>(segs, chunk_seg, n_seg, n_chunks, units, n_units, marks);
+    // Scattered positions, ordinarily and past the caches, with marking and
+    // decode: 8 materials of 270 MB 84.8 and 100.3 us, 65 of 545 MB 422 and 417,
+    // 24 of 906 MB with 5.5 million queries 425 and 438, 8 of 1.08 GB 148 and 145
+    // (1.8 million queries 318 and 310), 65 of 2.2 GB 678 and 647 (1.3 million
+    // 350 and 325), 100 of 3.4 GB 523 and 482.
+    const bool list_nt = scratch_bytes > (size_t)1 << 30;
+    auto *kernel = list_nt ? k_predecode_touched<true, true>
+                 : nt ? k_predecode_touched<true, false> : k_predecode_touched<false, false>;
+    kernel<<<grid, 256, 0, s>>>(segs, chunk_seg, n_seg, n_chunks, units, n_units, marks);
     return hipGetLastError();
 }
 

@@ -112,3 +112,17 @@ def test_three_pyramids_in_a_small_scratch_are_unpacked_whole(bcf, n_mats, res):
         part = slice(k * per, (k + 1) * per)
         want = bcf.decode(mat, bcf.prepare(mat, bcf.Precision.FP16), q[part], bcf.Precision.FP16)
         assert torch.equal(got[part], want)
+
+
+def test_touched_blocks_of_more_than_a_gigabyte(bcf):
+    """Above 1 GiB of scratch the touched blocks are stored past the caches:
+    decodes equal the single material's, on texels of ones."""
+    mat = material(bcf, [(2048, 2048)] * 4, [12] * 4, (12, 16, 5), 360)
+    n_mats, per = 9, 1111
+    batch = bcf.Batch([mat] * n_mats, bcf.Precision.FP16, ws_fill=0xFF)
+    assert batch.ws.numel() > 1 << 30
+    q = dev(synth.uniform_queries(n_mats * per, synth.rng(361), 11.0))
+    offsets = dev(np.arange(0, n_mats * per + 1, per, dtype=np.int32))
+    batch.unpack_touched(q, offsets)
+    want = bcf.decode(mat, bcf.prepare(mat, bcf.Precision.FP16), q, bcf.Precision.FP16)
+    assert torch.equal(batch.decode(q, offsets), want)
