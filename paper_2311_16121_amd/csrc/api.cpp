@@ -273,26 +273,32 @@ void interleave_if_shared(bcf::MaterialDesc &d)
     d.interleaved = 1;
 }
 
-constexpr size_t kCachedScratch = (size_t)64 << 20;
+// Whether the unpack before a decode of n queries stores past the caches
+// (grid_width as bcf_decode's; n = 0: bcf_unpack, the decode is not known). Up
+// to half of the memory-side cache (256 MB) the scratch is best left there for
+// the decode. A larger one only evicts what else is there, unless the decode
+// reads about as much as it holds; one that is decoded over and over would
+// still find part of itself. fp16, one material after itself and three in turn
+// (us a decode), ordinary and past the caches:
+//   67 MB (four of 2048 x 1024): 1,000 points 25 24 and 25 24, 2^20 61 69 and 59
+//     69, 1920 x 1080 51 58 and 55 59, 3840 x 2160 114 165 and 138 165
+//   90 MB (two of 2048): 1,000 points 25 31 and 28 31, 1920 x 1080 54 61 and 62
+//     64, 3840 x 2160 114 154 and 151 156; 112 MB likewise
+//   134 MB (four of 2048): 1,000 points 37 42 and 53 38, 500,000 58 63 and 71 69,
+//     2^20 78 86 and 88 96; 1920 x 1080 73 76 and 95 85, 3840 x 2160 140 182 and
+//     196 188 (199 185 with other queries each time), 4096 x 3000 262 256 and
+//     263 249
+//   269 MB (four of 4096 x 2048): 1,000 points 92 71 and 91 72, 2^20 138 121 and
+//     143 131, 3840 x 2160 239 223 and 240 223
+// bcf_unpack of packed pyramids is taken to be followed by decodes of the same
+// material that read much of it: with a 3840 x 2160 frame of three pyramids at
+// 134 MB 139 ordinarily and 181 past the caches, with 2^20 points 76 and 87;
+// three materials in turn without a decode 45 and 31 each.
+constexpr size_t kCachedScratch = (size_t)128 << 20;
 
-// Whether the unpack before a decode of n queries stores past the caches. A
-// scratch of up to twice the L2s (32 MB) is best left in them for the decode;
-// a larger one would only be written back under its reads. Fp16, ordinary and
-// past the caches: four pyramids of 2048 (134 MB) with 1,000 points 53.0 and
-// 38.1 us, 1920 x 1080 93.8 and 85.8, 3840 x 2160 203.7 and 192.5; two of 2048 (90
-// MB) 1280 x 720 48.6 and 44.1; 2048 to 256 (60 MB) 37.8 and 41.0; one of 2048
-// (45 MB) 28.8 and 33.1; four of 1024 (34 MB) 31.2 and 34.1. Scattered points
-// read the scratch line by line, and once they read about as much as it holds,
-// what the unpack left in the caches counts again: 134 MB with 600,000 80.2
-// and 73.1, with 1,000,000 94.2 and 95.3, with 2,000,000 128.9 and 138.5.
-// These alternate between three materials. One that is decoded over and over
-// keeps its 134 MB in the memory-side cache when stored ordinarily (3840 x 2160
-// 173.5 and 186.4 us), which is what a caller of the unpack by itself (n = 0) is
-// taken to do: packed scratches are then stored ordinarily (unpack and decode
-// of that frame 160 and 193 us).
 bool unpack_past_caches(const bcf::MaterialDesc &d, const bcf::WsLayout &lay, size_t n, uint32_t grid_width)
 {
-    constexpr size_t kPointBytes = 160;
+    constexpr size_t kPointBytes = 200;
     if (lay.scratch_bytes <= kCachedScratch) return false;
     if (n == 0) return !d.interleaved;
     return (grid_width >= 16 && grid_width <= n) || n < lay.scratch_bytes / kPointBytes;
@@ -573,7 +579,11 @@ size_t batch_scratch(const BatchLayout &b)
 // decode, ordinarily and past the caches, 8 materials of 35 MB 29.2 and 31.2 us,
 // 3 of 63 MB 37.1 and 40.9, 8 of 78 MB 61.4 and 61.2, 4 of 109 MB 47.6 and 37.2,
 // 20 of 274 MB 150.0 and 136.6, 24 of 906 MB 594.5 and 527.0.
-bool unpack_past_caches(const BatchLayout &b) { return batch_scratch(b) > kCachedScratch; }
+bool unpack_past_caches(const BatchLayout &b)
+{
+    constexpr size_t kCachedBatch = (size_t)64 << 20;
+    return batch_scratch(b) > kCachedBatch;
+}
 
 // bcf_unpack_batch_touched unpacks every block where no block would be marked,
 // and where only materials of three pyramids would be and their scratch is at

@@ -126,3 +126,45 @@ def test_touched_blocks_of_more_than_a_gigabyte(bcf):
     batch.unpack_touched(q, offsets)
     want = bcf.decode(mat, bcf.prepare(mat, bcf.Precision.FP16), q, bcf.Precision.FP16)
     assert torch.equal(batch.decode(q, offsets), want)
+
+
+@pytest.mark.parametrize("sizes,signed", [([(2048, 2048)] * 4, False), ([(2048, 2048)] * 3, True), ([(4096, 4096)], False),
+                                          ([(4096, 2048), (2048, 2048), (2048, 1024)], True)])
+def test_unpacks_past_the_caches_store_every_texel(bcf, sizes, signed):
+    """Above 128 MiB of scratch the unpack of few points, of an image and by
+    itself (of pyramids of their own) stores past the caches, of many points and
+    of a large image ordinarily: on a scratch of ones each leaves texels from
+    which every query decodes to the same bits, within 2e-3 of the oracle."""
+    import oracle
+    levels, dims, bias = [s[0].bit_length() for s in sizes], (3 * len(sizes), 16, 5), [0.0] * len(sizes)
+    g = synth.rng(380)
+    block = synth.bounded_blocks(4096, g, signed=signed).reshape(-1)
+    texs = [np.resize(np.roll(block, 16 * 7 * t), 16 * synth.chain_blocks(w, h, n))
+            for t, ((w, h), n) in enumerate(zip(sizes, levels))]
+    params = synth.mlp_params(dims, g)
+    mat = bcf.Material.from_host(texs, sizes, levels, dims, params, bias, signed)
+    p = bcf.Precision.FP16
+    ws = bcf.prepare(mat, p)
+    offset, size = (int(x) for x in ws[24:40].cpu().numpy().view(np.uint64))     # of the scratch, from the header
+    assert size > 128 << 20
+    q = synth.uniform_queries(6 * (1 << 20), g, levels[0] - 1.0)
+    q[:4000, :2] = np.round(q[:4000, :2] * 256) / 256                            # block corners and wrap columns
+    qd, few = dev(q), 5000
+
+    def decode(**kw):
+        return bcf.decode_unpacked(mat, ws, qd, p, **kw).view(torch.int32)
+
+    def spoil():
+        ws[offset:offset + size] = 0xFF
+
+    want = None
+    for unpack in (lambda: bcf.decode(mat, ws, qd, p), lambda: bcf.decode(mat, ws, qd[:few], p),
+                   lambda: bcf.decode(mat, ws, qd[:few], p, grid_width=100), lambda: bcf.unpack(mat, ws),
+                   lambda: bcf.decode(mat, ws, qd, p, grid_width=4096)):
+        spoil()
+        unpack()
+        got = decode()
+        want = got if want is None else want
+        assert torch.equal(got, want)
+    host = oracle.Material(texs, sizes, levels, dims, params, bias, signed)
+    assert np.abs(want[:few].view(torch.float32).cpu().numpy() - oracle.decode(host, q[:few])).max() <= 2e-3
