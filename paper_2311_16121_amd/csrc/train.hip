@@ -620,12 +620,15 @@ __launch_bounds__(kTrainThreads) k_train_forward_mfma(TrainDesc d, const float *
 // gradient lines update them while the lines sit in one L2.
 
 constexpr int kBinThreads = 1024;
-// Samples a thread of the count and placement kernels takes. Eight from 3 * 2^17
+// Samples a thread of the count and placement kernels takes. Eight from 3 * 2^16
 // samples on: a workgroup's histogram covers 8K of them, so that fewer cells of
 // it reach memory (one atomic per touched cell and workgroup). Below, one: the
-// workgroups would be too few. (2^20 samples, count + placement: 24 + 35 us with
-// one, 10 + 17 with eight, 14 + 21 with sixteen; 2^18: 3 + 4, 6 + 7, 10 + 10.)
-constexpr uint32_t kBinMany = 3u << 17;
+// workgroups would be too few. Backward of 4 x 1024^2, one and eight: 2^16 147
+// and 155 us, 2^17 172 and 177, 2^18 210 and 204, 3 * 2^17 247 and 234, 2^20 388
+// and 349; 4 x 256^2 and one of 1024^2 cross between 2^17 and 2^18 too. (2^20
+// samples, the two kernels alone: 24 + 35 us with one, 10 + 17 with eight, 14 +
+// 21 with sixteen.)
+constexpr uint32_t kBinMany = 3u << 16;
 constexpr uint32_t bin_per_thread(uint32_t n) { return n >= kBinMany ? 8u : 1u; }
 
 // A query's cell: its wrapped (u, v) on the kTrainBinSide grid (NaN and
@@ -1057,9 +1060,13 @@ __global__ void __launch_bounds__(64 * kBwdWaves, 2) k_train_backward(TrainDesc 
 // ---------------------------------------------------------------------------
 // dL/dz -> dL/d texel
 
-// Threads of a region's workgroup: 512 from 2^19 samples on (512 a region and
-// more: 122 us of 2^20 samples, 147 with 256), else 256 (36 us of 2^18, 41)
+// Threads of a region's workgroup: 512 where its windows take more than 8 KB of
+// LDS (fewer workgroups are then resident) and there are 2^18 samples, else 256.
+// Backward with 256 and 512: 4 x 1024^2 (40 KB) 2^16 samples 147 and 145 us, 2^18
+// 209 and 206, 2^20 367 and 347; 4 x 512^2 (12 KB) 2^12 87 and 94, 2^18 177 and
+// 175, 2^20 389 and 381; 4 x 256^2 (5 KB) 2^18 146 and 148, 2^20 343 and 362.
 constexpr unsigned kScatterThreads = 512;
+constexpr uint32_t kScatterWide = 1u << 18, kScatterWidePool = 8 * 1024;
 // LDS for a workgroup's windows at most: two workgroups a CU
 constexpr uint32_t kScatterPoolMax = 72 * 1024;
 // A window of one level: the texels x0 .. x0 + w - 1 (wrapped) of rows y0 ..
@@ -1314,6 +1321,38 @@ unsigned grid_for(size_t work, unsigned per_block, unsigned cap)
     return (unsigned)(g < 1 ? 1 : (g > cap ? cap : g));
 }
 
+// The scatter's regions: 2 x 2 cells, where a window then still spans at most
+// 34 texels (level 0 of 1024) or samples are few, else single cells. Backward
+// with single cells and 2 x 2: 4 x 512^2 2^18 samples 284 and 177 us, 2^20 631
+// and 381; 4 x 1024^2 303 and 211, 436 and 348; 4 x 2048^2 (whose level 0 goes
+// straight to memory from 2 x 2) 2^14 421 and 317, 2^18 505 and 449, 2^19 548 and
+// 551, 2^20 654 and 734; one of 4096^2 2^14 450 and 421, 2^18 610 and 543, 2^20
+// 753 and 757.
+uint32_t scatter_region_log2(const TrainDesc &d, uint32_t samples)
+{
+    uint32_t side = 0;
+    for (uint32_t t = 0; t < d.n_tex; ++t) side = std::max(side, std::max(d.tex[t].w, d.tex[t].h));
+    return side <= 1024 || samples < (1u << 19) ? 1u : 0u;
+}
+
+// LDS sums for the windows of the largest pyramid, the coarsest levels first,
+// as far as two workgroups share a CU.
+uint32_t scatter_pool_sums(const TrainDesc &d, uint32_t region_log2)
+{
+    uint32_t pool_sums = 0;
+    for (uint32_t t = 0; t < d.n_tex; ++t) {
+        uint32_t sums = 0;
+        for (uint32_t l = d.tex[t].levels; l-- > 0;) {
+            const uint32_t more = 3u * window_side(std::max(d.tex[t].w >> l, 1u), 1u << region_log2) *
+                                  window_side(std::max(d.tex[t].h >> l, 1u), 1u << region_log2);
+            if ((sums + more) * 8u > kScatterPoolMax) break;
+            sums += more;
+        }
+        pool_sums = std::max(pool_sums, sums);
+    }
+    return pool_sums;
+}
+
 hipError_t launch_texels(const TrainDesc &d, hipStream_t s)
 {
     if (d.packed && !d.ste) {
@@ -1403,22 +1442,6 @@ hipError_t launch_train_backward(const TrainDesc &d, const float *queries, size_
     k_train_clear<<<grid_for(std::max<size_t>((size_t)d.n_texels / 4u * 3u, kTrainBins), 256, 8192), 256, 0, s>>>(d);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     const uint32_t c = d.dims[d.n_layers];
-    // the scatter's regions: 2 x 2 cells, where a window then still spans at
-    // most 34 texels (level 0 of 1024), else single cells; LDS for the windows
-    // of the largest pyramid, as far as two workgroups share a CU
-    uint32_t side = 0, pool_sums = 0;
-    for (uint32_t t = 0; t < d.n_tex; ++t) side = std::max(side, std::max(d.tex[t].w, d.tex[t].h));
-    const uint32_t region_log2 = side <= 1024 ? 1u : 0u;
-    for (uint32_t t = 0; t < d.n_tex; ++t) {
-        uint32_t sums = 0;
-        for (uint32_t l = d.tex[t].levels; l-- > 0;) {
-            const uint32_t more = 3u * window_side(std::max(d.tex[t].w >> l, 1u), 1u << region_log2) *
-                                  window_side(std::max(d.tex[t].h >> l, 1u), 1u << region_log2);
-            if ((sums + more) * 8u > kScatterPoolMax) break;
-            sums += more;
-        }
-        pool_sums = std::max(pool_sums, sums);
-    }
     // batches of one size
     const size_t batches = (n + d.bin_batch - 1) / d.bin_batch;
     const size_t batch = batches ? ((n + batches - 1) / batches + 63u) & ~(size_t)63u : 1;
@@ -1434,7 +1457,9 @@ hipError_t launch_train_backward(const TrainDesc &d, const float *queries, size_
         else k_train_bin_scatter<8><<<bins, kBinThreads, 0, s>>>(q, m, d.bin_next, d.bin_perm);
         if ((e = hipGetLastError()) != hipSuccess) return e;
         if ((e = dispatch_backward(d, q, m, grad_out + (size_t)c * off, s)) != hipSuccess) return e;
-        const unsigned threads = m >= (1u << 19) ? kScatterThreads : kScatterThreads / 2;
+        const uint32_t region_log2 = scatter_region_log2(d, m), pool_sums = scatter_pool_sums(d, region_log2);
+        const unsigned threads = m >= kScatterWide && pool_sums * 8u > kScatterWidePool ? kScatterThreads
+                                                                                       : kScatterThreads / 2;
         k_train_scatter<<<(kTrainBins >> (2 * region_log2)) * d.n_tex, threads, pool_sums * 8u, s>>>(
             d, region_log2, pool_sums);
         if ((e = hipGetLastError()) != hipSuccess) return e;
