@@ -163,35 +163,26 @@ __device__ __forceinline__ float neuron(const uint8_t *ws, const WsLayout &lay, 
     return acc;
 }
 
-template <int H, int NH, int C>
-__device__ __forceinline__ void mlp_valu(const uint8_t *ws, const WsLayout &lay, const float z[12], float o[C],
-                                         float *amax)
+// amax[l] = max(amax[l], the largest |input| of layer l) for the feature vector z.
+template <int H, int NH>
+__device__ __forceinline__ void mlp_maxima(const uint8_t *ws, const WsLayout &lay, const float z[12], float *amax)
 {
-    if (amax) {
 #pragma unroll
-        for (int i = 0; i < 12; ++i) amax[0] = fmaxf(amax[0], fabsf(z[i]));
-    }
+    for (int i = 0; i < 12; ++i) amax[0] = fmaxf(amax[0], fabsf(z[i]));
     float hcur[H];
 #pragma unroll
     for (int j = 0; j < H; ++j) hcur[j] = relu(neuron<12>(ws, lay, 0, j, z));
 #pragma unroll
-    for (int l = 1; l < NH; ++l) {
-        if (amax) {
+    for (int l = 1; l <= NH; ++l) {
 #pragma unroll
-            for (int i = 0; i < H; ++i) amax[l] = fmaxf(amax[l], hcur[i]);
-        }
+        for (int i = 0; i < H; ++i) amax[l] = fmaxf(amax[l], hcur[i]);
+        if (l == NH) break;                       // the outputs are no layer's input
         float hn[H];
 #pragma unroll
         for (int j = 0; j < H; ++j) hn[j] = relu(neuron<H>(ws, lay, l, j, hcur));
 #pragma unroll
         for (int j = 0; j < H; ++j) hcur[j] = hn[j];
     }
-    if (amax) {
-#pragma unroll
-        for (int i = 0; i < H; ++i) amax[NH] = fmaxf(amax[NH], hcur[i]);
-    }
-#pragma unroll
-    for (int j = 0; j < C; ++j) o[j] = neuron<H>(ws, lay, NH, j, hcur);
 }
 
 __device__ __forceinline__ void wave_lds_sync()
@@ -520,9 +511,10 @@ __global__ void __launch_bounds__(kFrameThreads) k_frame(FrameArgs a)
         run(std::integral_constant<ItemKind, kItemTile>());
 }
 
-// The plain fp32 decode that records each layer's largest input magnitude
-// (the static fp8 activation scales come from a calibration batch).
-template <int H, int NH, int C, int LAYOUT>
+// The fp32 features and hidden layers on the vector ALU, recording each layer's
+// largest input magnitude (the static fp8 activation scales come from a
+// calibration batch).
+template <int H, int NH, int LAYOUT>
 __global__ void __launch_bounds__(kFrameThreads) k_calibrate(FrameArgs a)
 {
     __shared__ LevelLut lut;
@@ -534,9 +526,9 @@ __global__ void __launch_bounds__(kFrameThreads) k_calibrate(FrameArgs a)
     for (int l = 0; l <= NH; ++l) amax[l] = 0.0f;
     for (uint32_t q = blockIdx.x * blockDim.x + threadIdx.x; q < a.n; q += gridDim.x * blockDim.x) {
         const Query qq = load_query(rq, q);
-        float z[12], o[C];
+        float z[12];
         filter4<LAYOUT>(rs, lut, a.levels_bias, a.stride, qq.u, qq.v, qq.s, z);
-        mlp_valu<H, NH, C>(a.ws, a.lay, z, o, amax);
+        mlp_maxima<H, NH>(a.ws, a.lay, z, amax);
     }
 #pragma unroll
     for (int l = 0; l <= NH; ++l) {
@@ -544,9 +536,6 @@ __global__ void __launch_bounds__(kFrameThreads) k_calibrate(FrameArgs a)
         atomicMax(reinterpret_cast<unsigned int *>(a.absmax) + l, __builtin_bit_cast(unsigned int, amax[l]));
     }
 }
-
-
-
 
 // ---------------------------------------------------------------------------
 // Many materials in one launch. Every material has its own pyramids, texel

@@ -499,7 +499,8 @@ __device__ __forceinline__ void prepare_weights(const PrepareArgs &a, uint32_t b
     const uint32_t stride = kPrepareBlocks / 4 * blockDim.x;
     const float *sc = reinterpret_cast<const float *>(a.ws + a.lay.scales_off);
     const uint32_t l = block % 4;
-    if (l <= a.sh.n_hidden) {
+    // the calibration needs no output layer
+    if (l < a.sh.n_hidden || (l == a.sh.n_hidden && a.kind != MLP_VALU_F32)) {
         const uint32_t ne = (uint32_t)layer_elems(a.sh, l, a.kind);    // at most 64 x 64
         const uint32_t rows = layer_out(a.sh, l, a.kind);
         uint8_t *wdst = a.ws + a.lay.layer_w_off[l];

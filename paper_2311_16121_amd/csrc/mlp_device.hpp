@@ -248,9 +248,11 @@ struct MfmaMlp {
         return M::pack_relu(x, inv);
     }
 
-    // run() for G independent groups of 16 queries at once, layer by layer,
-    // so that each layer's MFMAs of the different groups follow each other
-    // and hide one another's latency
+    // f[q]: this lane's layer-0 inputs (pyramid g = lane / 16, channels 0..2, 0)
+    // of query lane % 16 of group q; out[q]: output rows 4g..4g+3 of that query.
+    // G independent groups of 16 queries at once, layer by layer, so that each
+    // layer's MFMAs of the different groups follow each other and hide one
+    // another's latency
     template <int G>
     __device__ __forceinline__ void run_groups(const float (*f)[4], float4_t *out) const
     {
@@ -311,53 +313,6 @@ struct MfmaMlp {
             for (int kc = 0; kc < KCH; ++kc) acc = M::mma(wo[kc], xin[q][kc], acc);
             out[q] = finish(acc, bo, NH);
         }
-    }
-
-    // f: this lane's layer-0 inputs (pyramid g = lane / 16, channels 0..2, 0)
-    // of query lane % 16; returns output rows 4g..4g+3 of that query
-    __device__ __forceinline__ float4_t run(const float f[4]) const
-    {
-        const float4_t zero = {0.0f, 0.0f, 0.0f, 0.0f};
-        typename M::Op x0[KC0];
-        if (P == 1) {
-#pragma unroll
-            for (int kc = 0; kc < KC0; ++kc) x0[kc] = M::pack(f + kc, 1.0f);
-        } else {
-            const float x[8] = {f[0], f[1], f[2], 0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
-            x0[0] = M::pack(x, inv_in[0]);
-        }
-        float act[HB][4];                               // pre-activations of the hidden layer
-#pragma unroll
-        for (int mb = 0; mb < HB; ++mb) {
-            float4_t acc = M::SCALED ? zero : b0[mb];
-#pragma unroll
-            for (int kc = 0; kc < KC0; ++kc) acc = M::mma(w0[mb][kc], x0[kc], acc);
-            acc = finish(acc, b0[mb], 0);
-#pragma unroll
-            for (int j = 0; j < 4; ++j) act[mb][j] = acc[j];
-        }
-#pragma unroll
-        for (int l = 1; l < NH; ++l) {
-            typename M::Op xin[KCH];
-#pragma unroll
-            for (int kc = 0; kc < KCH; ++kc) xin[kc] = hidden_chunk(act, kc, inv_in[l]);
-#pragma unroll
-            for (int mb = 0; mb < HB; ++mb) {
-                float4_t acc = M::SCALED ? zero : bh[l - 1][mb];
-#pragma unroll
-                for (int kc = 0; kc < KCH; ++kc) acc = M::mma(wh[l - 1][mb][kc], xin[kc], acc);
-                acc = finish(acc, bh[l - 1][mb], l);
-#pragma unroll
-                for (int j = 0; j < 4; ++j) act[mb][j] = acc[j];
-            }
-        }
-        typename M::Op xin[KCH];
-#pragma unroll
-        for (int kc = 0; kc < KCH; ++kc) xin[kc] = hidden_chunk(act, kc, inv_in[NH]);
-        float4_t acc = M::SCALED ? zero : bo;
-#pragma unroll
-        for (int kc = 0; kc < KCH; ++kc) acc = M::mma(wo[kc], xin[kc], acc);
-        return finish(acc, bo, NH);
     }
 };
 
