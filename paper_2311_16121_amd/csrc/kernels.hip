@@ -906,9 +906,16 @@ hipError_t launch_batch_mark(void *ws, size_t table_off, size_t items_off, const
     // none waits for another round (24 materials, 5.5 million queries: 1350 of
     // them 455.9 us, unpack and decode included, 1024 437.9), and small batches
     // spread out (two materials of some thousand queries: ranges of at least
-    // 16 items 56.1 us, of 8 50.7, of 4 48.3, of 2 39.8)
+    // 16 items 56.1 us, of 8 50.7, of 4 48.3, of 2 39.8). Two rounds of them from
+    // 2^24 queries on when the marks outgrow an XCD's 4 MB of L2, of which the
+    // first round then touches half (marks and unpack, 1024 against 2048
+    // workgroups: 5.6 MB of marks, 22 and 50 million queries, 64 materials of
+    // 1024 x 1024: 823 and 1086 us against 791 and 1040, 16 of 2048 x 2048: 808
+    // and 1119 against 785 and 1055; 11 million: 569 and 550 against 577 and 557;
+    // 2.1 MB, 22 million: 397 against 404)
     const uint32_t items = (uint32_t)(((uint64_t)n_total + 63u) / 64u) + n_mats;
-    const unsigned grid = std::min<unsigned>((items + 7u) / 8u, 1024u);
+    const unsigned rounds = n_total >= 1u << 24 && mark_bytes > 4u << 20 ? 2u : 1u;
+    const unsigned grid = std::min<unsigned>((items + 7u) / 8u, 1024u * rounds);
     k_batch_mark<<<grid, 256, 0, s>>>(a, marks);
     return hipGetLastError();
 }

@@ -128,6 +128,21 @@ def test_touched_blocks_of_more_than_a_gigabyte(bcf):
     assert torch.equal(batch.decode(q, offsets), want)
 
 
+@pytest.mark.parametrize("n", [(1 << 24) - 1, 1 << 24, (1 << 24) + 4097])
+def test_marks_of_many_queries_beyond_an_l2(bcf, n):
+    """From 2^24 queries on, marks of more than 4 MiB are set by two rounds of
+    workgroups: decodes equal the single material's, on texels of ones."""
+    mat = material(bcf, [(2048, 2048)] * 4, [12] * 4, (12, 16, 5), 370)
+    n_mats, pool = 13, 65536
+    batch = bcf.Batch([mat] * n_mats, bcf.Precision.FP16, ws_fill=0xFF)
+    few = dev(synth.uniform_queries(pool, synth.rng(371), 11.0))
+    q = few.repeat(n // pool + 1, 1)[:n].contiguous()
+    offsets = dev(np.linspace(0, n, n_mats + 1).astype(np.int32))
+    batch.unpack_touched(q, offsets)
+    want = bcf.decode(mat, bcf.prepare(mat, bcf.Precision.FP16), few, bcf.Precision.FP16)
+    assert torch.equal(batch.decode(q, offsets), want.repeat(n // pool + 1, 1)[:n])
+
+
 @pytest.mark.parametrize("sizes,signed", [([(2048, 2048)] * 4, False), ([(2048, 2048)] * 3, True), ([(4096, 4096)], False),
                                           ([(4096, 2048), (2048, 2048), (2048, 1024)], True)])
 def test_unpacks_past_the_caches_store_every_texel(bcf, sizes, signed):
