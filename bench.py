@@ -307,7 +307,7 @@ def bench_batch(args):
                                    "achieved": unpack_bytes / (unpack_ms * 1e-3) / 1e9,
                                    "note": "every block of every material; not part of the step"},
                     "unpack_touched": {"ms": touched_ms, "blocks": alg_blocks,
-                                       "note": "clear + item prefix + mark + unpack launches"},
+                                       "note": "clear + mark + unpack launches"},
                     "decode": {"launch_ms": decode_ms},
                     "step": {"bound": "hbm", "achieved": step_bytes / (ms * 1e-3) / 1e9, "peak": HBM_PEAK_GBS,
                              "frac": step_bytes / (ms * 1e-3) / 1e9 / HBM_PEAK_GBS, "launch_ms": ms}},

@@ -334,7 +334,7 @@ typedef struct {
  * on this material: 32 bytes per texel and 52 MiB + 32 KiB, which hold the
  * texel values, their gradients, and the samples that the backward sorts by
  * position with their dL/d feature (as many at a time as there is room for,
- * 548,000 to 2^20), then the forward's MLP operands in the matrix-core layout
+ * 599,168 to 2^20), then the forward's MLP operands in the matrix-core layout
  * (a few KiB). */
 bcf_status bcf_train_workspace_size(const bcf_train_material *m, size_t *ws_bytes);
 

@@ -516,9 +516,11 @@ bcf_status describe_train(const bcf_train_material *m, bcf::TrainDesc *d, size_t
     }
     // 32 bytes a texel and 52 a sample of a full batch. The texel values and
     // gradients take 18 to 28 of the former (more only where levels are at most
-    // 4 texels wide), a sample 20 bytes and 16 per pyramid: four pyramids of 512
-    // or less have room for 650,000 to 880,000 samples a batch, larger ones and
-    // fewer pyramids for a full one.
+    // 4 texels wide), a sample 20 bytes and 16 per pyramid. One or two pyramids
+    // have room for a full batch (or all but 64 samples), as have four of 1024 or
+    // three of 2048; four of 64 to 512 for 650,000 to 880,000 samples, three of
+    // them for 800,000 to 990,000, four of 1024 to 128 for 737,000. The least over
+    // all accepted sizes is 599,168 (four of 1 x 32768).
     const size_t sort_end = 2 * align_up(unpadded * 16, 256) + (size_t)bcf::kTrainBinBatch * 52 +
                             2 * align_up((size_t)bcf::kTrainBins * 4, 256);
     const size_t samples = (sort_end - train_values_bytes(*d) - align_up(texels * 12, 256) -

@@ -41,8 +41,8 @@ struct MaterialDesc {
 enum MlpKind : uint32_t { MLP_VALU_F32 = 0, MLP_MFMA_F16 = 1, MLP_MFMA_BF16 = 2,
                           MLP_MFMA_FP8 = 3, MLP_MFMA_F32 = 4 };
 
-// Shapes after padding: every hidden layer has `hidden` units (16, 32 or 64),
-// the output has `out_pad` units (16 for MFMA, `out` rounded for VALU).
+// Shapes after padding: every hidden layer has `hidden` units (16, 32 or 64).
+// The matrix-core operands pad the output layer to 16 units.
 struct MlpShape {
     uint32_t n_hidden;              // hidden layers (1..3)
     uint32_t hidden;                // padded hidden width
@@ -107,9 +107,9 @@ hipError_t launch_predecode_batch(const UnpackSeg *segs, const uint32_t *chunk_s
 hipError_t launch_predecode_touched(const UnpackSeg *segs, const uint32_t *chunk_seg, uint32_t n_seg,
                                     uint32_t n_chunks, const uint32_t *units, uint32_t n_units, const uint8_t *marks,
                                     bool nt, size_t scratch_bytes, hipStream_t s);
-// Clears marks[0..mark_bytes) (a multiple of 16), fills the batch's item
-// prefix, and marks the block positions the queries of the interleaved
-// materials read.
+// Clears marks[0..mark_bytes) (a multiple of 16) and marks the block positions
+// the queries of the interleaved materials read; fills the batch's item prefix
+// only for more than 64 materials (up to 64, the lanes hold it).
 hipError_t launch_batch_mark(void *ws, size_t table_off, size_t items_off, const float *queries,
                              const uint32_t *offsets, uint32_t n_mats, uint32_t n_total, uint8_t *marks,
                              size_t mark_bytes, hipStream_t s);
@@ -145,8 +145,8 @@ hipError_t launch_prepare_unpack(const float *params, const float *act_absmax, c
 hipError_t launch_calibrate(const MaterialDesc &m, const MlpShape &sh, const WsLayout &lay, const void *ws,
                             const float *queries, size_t n, float *absmax, hipStream_t s);
 
-// grid_width >= 8: the queries are an image of that many columns (row-major);
-// results do not depend on it
+// grid_width: the queries are an image of that many columns (row-major), taken
+// in tiles from 16 columns on; results do not depend on it
 hipError_t launch_filter_mlp(const MaterialDesc &m, const MlpShape &sh, MlpKind kind,
                              const WsLayout &lay, const void *ws, const float *queries, size_t n,
                              uint32_t grid_width, float *out, hipStream_t s);

@@ -8,11 +8,12 @@
 //   k_train_bin_*     the backward's samples sorted by position (counting
 //                     sort over a grid of cells on the wrapped (u, v))
 //   k_train_backward  queries, dL/dG -> dL/d features per sample and dL/d MLP
-//                     parameters (per-wave sums on the matrix cores)
+//                     parameters (sums on the matrix cores, one atomic per
+//                     parameter and workgroup)
 //   k_train_scatter   dL/d features -> dL/d texel, one workgroup per pyramid
 //                     and region of cells: fixed-point sums in LDS windows over
-//                     the region's footprint, then stores inside it and one
-//                     float atomic per touched texel channel at its edges
+//                     the region's footprint, then one float atomic per touched
+//                     texel channel
 //   k_train_blocks    dL/d texel -> dL/d endpoints, dL/d indices (one lane
 //                     per block row, sums over a block's four lanes)
 //

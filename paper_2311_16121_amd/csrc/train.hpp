@@ -1,5 +1,5 @@
 // Training-time decode (Section 4.2, "Trainable BC6 decompression"): the
-// descriptors shared by the host API (train_api.cpp) and the kernels
+// descriptors shared by the host API (api.cpp) and the kernels
 // (train.hip).
 #pragma once
 
